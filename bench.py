@@ -41,11 +41,11 @@ sys.path.insert(0, ROOT)
 
 METRIC = "grid-point-steps/s (batched vs plain, 1 GPU) at max|Δψ|≤1e-4 vs FP64 oracle"
 HBM_PEAK_GBS = 8000.0
-# HBM bytes per grid-point-step of each workload's pass schedule (algorithmic): 2-D, a row
-# pass (psi read + write, f read: 24 B) and a column pass (psi read + write: 16 B); 3-D, an
+# HBM bytes per grid-point-step of each workload's pass schedule (algorithmic): 2-D, one pass
+# per step along either axis (psi read + write, f read: 24 B); 3-D, an
 # x-pass (24 B) and a (y, z)-plane pass (16 B), or with the matrix-core transforms an
-# x-pass and three single-axis passes y, z, y (72 B); QAA, the same two passes as 2-D QHD
-WORKLOAD_BYTES_PER_GP_STEP = {"batched2d": 40.0, "3d": 40.0, "3d_mfma": 72.0, "qaa": 40.0}
+# x-pass and three single-axis passes y, z, y (72 B); QAA, the same pass as 2-D QHD
+WORKLOAD_BYTES_PER_GP_STEP = {"batched2d": 24.0, "3d": 40.0, "3d_mfma": 72.0, "qaa": 24.0}
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 
 
@@ -57,7 +57,8 @@ def kernel_source_hash() -> str:
     """Hash of the pass kernels' code (comments and whitespace removed): the key under
     which HBM counter readings are kept."""
     h = hashlib.sha256()
-    for rel in ("paper_2303_01471_amd/csrc/qhd_kernels.hip", "paper_2303_01471_amd/csrc/qhd_kernels_3d.hip",
+    for rel in ("paper_2303_01471_amd/csrc/qhd_kernels.hip", "paper_2303_01471_amd/csrc/qhd_kernels_axis.hip",
+                "paper_2303_01471_amd/csrc/axis_line.h", "paper_2303_01471_amd/csrc/qhd_kernels_3d.hip",
                 "paper_2303_01471_amd/csrc/qhd_kernels_mfma.hip", "paper_2303_01471_amd/csrc/rqp_kernels.hip",
                 "paper_2303_01471_amd/csrc/line_fft.h", "paper_2303_01471_amd/csrc/pass_common.h",
                 "paper_2303_01471_amd/csrc/qhd_internal.h", "paper_2303_01471_amd/csrc/rqp_internal.h"):
@@ -661,8 +662,8 @@ def main():
             plain["single_256x256_10k_steps_gp_steps_per_s"] = round(c1_rate, 1)
             plain["single_256x256_norm_drift"] = abs(r1[0]["norm"] - 1.0)
             # the single-instance configuration at 256^2, 512^2 and 1024^2 (roofline scaling):
-            # 1000 steps after 200 warm ones, HBM rate at the 40 B per grid-point-step of the
-            # row and column passes
+            # 1000 steps after 200 warm ones, HBM rate at the 24 B per grid-point-step of the
+            # alternating row and column passes
             scaling = {}
             for n_s in (256, 512, 1024):
                 cs = qhd_inputs.single_2d(n_s)
@@ -675,9 +676,9 @@ def main():
                 torch.cuda.synchronize()
                 r_s = cs.points * 1000 / (time.perf_counter() - t)
                 ps_.close()
-                scaling[str(n_s)] = {"gp_steps_per_s": round(r_s, 1), "hbm_GBps_at_40B": round(r_s * 40 / 1e9, 1),
-                                     "frac_of_8TBs": round(r_s * 40 / (HBM_PEAK_GBS * 1e9), 4)}
-                log(f"single {n_s}x{n_s}: {r_s / 1e9:.2f} G gp-steps/s = {r_s * 40 / 1e9:.0f} GB/s at 40 B")
+                scaling[str(n_s)] = {"gp_steps_per_s": round(r_s, 1), "hbm_GBps_at_24B": round(r_s * 24 / 1e9, 1),
+                                     "frac_of_8TBs": round(r_s * 24 / (HBM_PEAK_GBS * 1e9), 4)}
+                log(f"single {n_s}x{n_s}: {r_s / 1e9:.2f} G gp-steps/s = {r_s * 24 / 1e9:.0f} GB/s at 24 B")
             plain["single_instance_roofline_scaling"] = scaling
         plain.update({
                  "method": "per-size rates of the single-instance solver (one plan per instance, "

@@ -146,9 +146,9 @@ typedef struct {
                                     in LDS (n_y (9 n_x / 8 + 1) 8 bytes, ~148 KB and one
                                     instance per CU at 128^2), so psi crosses HBM only
                                     at the start and the end of the call (the scope's
-                                    resident mode of the two-pass step, App. C.2.1).
+                                    resident mode of the split-operator step, App. C.2.1).
                                     Same arithmetic as the streaming passes with 8
-                                    points per lane.  With QHD_OPT_AUTOTUNE as well,
+                                    points per lane (16 on 128-point lines).  With QHD_OPT_AUTOTUNE as well,
                                     each such class keeps resident steps only if 16 of
                                     them beat 16 streaming steps on its own batch (one
                                     CU per 128^2 instance loses against the whole GPU
@@ -218,8 +218,9 @@ qhd_status qhd_set_steps_done(qhd_plan plan, int32_t i, int64_t j);
 
 /* Advance every instance by min(max_steps, remaining) steps (max_steps < 0:
  * to the end).  Asynchronous on `stream`; allocates nothing.  Between evolve
- * calls the state may carry a pending half step; the result does not depend on
- * how the steps are split into calls.
+ * calls the state may carry a pending half step, and on 2-D meshes the kinetic
+ * factor of the last step along one axis; the result does not depend on how the
+ * steps are split into calls.
  * The steps run in chunks of at most K steps (K = 64 / the most stages per step of
  * any instance; qhd_plan_info reports it).  Inside a chunk every shape class runs
  * on a stream of its own, forked from `stream` and joined back before the chunk's
@@ -230,7 +231,8 @@ qhd_status qhd_set_steps_done(qhd_plan plan, int32_t i, int64_t j);
  * rest runs as direct launches.  The arithmetic is the same, so the results are
  * bitwise identical to direct launches.  Not with QHD_OPT_NO_GRAPH, and not while
  * `stream` is itself being captured (the passes are then launched directly into
- * the caller's capture).  With QHD_OPT_TIME_PASSES one chunk in timing_stride is
+ * the caller's capture; a capture of an odd number of steps may be replayed any
+ * number of times, later evolves then pay what is owed along the other axis first).  With QHD_OPT_TIME_PASSES one chunk in timing_stride is
  * launched directly with its classes serialised and every pass timed. */
 qhd_status qhd_evolve(qhd_plan plan, int64_t max_steps, void *stream);
 
@@ -264,7 +266,7 @@ qhd_status qhd_plan_info(qhd_plan plan, qhd_class_info *out, int32_t cap, int32_
  * are kept.  Asynchronous on `stream`; allocates nothing. */
 qhd_status qhd_reset(qhd_plan plan, void *stream);
 
-/* Readouts for every instance.  Closes any pending half step on a copy (the
+/* Readouts for every instance.  Closes whatever the state owes on a copy (the
  * plan state is untouched, evolution can continue).  host_out: `batch` entries.
  * rho_dev / psi_dev: optional caller-owned device buffers receiving |psi|^2
  * (FP32) and psi (interleaved FP32), instances concatenated in order; NULL to

@@ -18,10 +18,10 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqhd.so")
 OBJDIR = os.path.join(ROOT, "_build", "qhd")
 
-SOURCES = ["qhd_api.cpp", "qhd_kernels.hip", "qhd_kernels_3d.hip", "qhd_kernels_mfma.hip", "qhd_kernels_resident.hip",
+SOURCES = ["qhd_api.cpp", "qhd_kernels.hip", "qhd_kernels_axis.hip", "qhd_kernels_3d.hip", "qhd_kernels_mfma.hip", "qhd_kernels_resident.hip",
            "qhd_static.hip", "qhd_spectrum.cpp", "qhd_spectrum_kernels.hip", "sno.cpp",
            "sno_gemm.hip", "sno_kernels.hip", "rqp.cpp", "rqp_kernels.hip"]
-HEADERS = ["line_fft.h", "qhd_internal.h", "pass_common.h", "sno_internal.h", "rqp_internal.h"]
+HEADERS = ["line_fft.h", "axis_line.h", "launch_util.h", "qhd_internal.h", "pass_common.h", "sno_internal.h", "rqp_internal.h"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -1,0 +1,148 @@
+// The line operator of an alternating pass (see qhd_kernels_axis.hip): F^{-1} E F along one
+// mesh line, E the kinetic factor of one axis, and what a line does in a sub-step.
+#pragma once
+
+#include "line_fft.h"
+#include "pass_common.h"
+#include "qhd_internal.h"
+
+namespace qhd {
+
+// entries of one kinetic-factor table of an axis of N points
+template <int N, int MODEL>
+__host__ __device__ constexpr int etab_len() {
+  return MODEL == kModelQAA ? ilog2_c(N) + 1 : N / 2 + 1;
+}
+
+// Tables of instances i0 .. i0 + count - 1: per instance E(a_{j-1}) then E(a_j), j = the
+// stage of sub-step s, by the whole block (the caller synchronises around it).  The entry
+// of |frequency| N / 2 is the fourth power of that of N / 4 (its phase is four times as
+// large), so that a block of N threads or half as many has whole rounds.
+template <int N, int MODEL, bool Y4>
+__device__ __forceinline__ void fill_etab(double2* __restrict__ tab, const InstDev* __restrict__ inst, int i0, int count,
+                                          int axis, long long s) {
+  constexpr int H = etab_len<N, MODEL>();
+  constexpr int R = MODEL == kModelQAA ? H : N / 2;  // entries evaluated per table
+  constexpr double inv_n = 1.0 / N;
+  for (int d = 0; d < count; ++d, tab += 2 * H) {
+    const InstDev& I = inst[i0 + d];
+    const long long j = I.steps_done + s;
+    double a0, a1, b;
+    sched_ab<Y4>(I, j - 1, a0, b);
+    sched_ab<Y4>(I, j, a1, b);
+    const double unit = MODEL == kModelQAA ? I.dt * kInv2Pi : I.kin_turns[axis];
+    for (int e = threadIdx.x; e < 2 * R; e += blockDim.x) {
+      const int cur = e >= R ? 1 : 0, k = e - cur * R;
+      const double c = (cur ? a1 : a0) * unit;
+      const double turns = c * (double)(MODEL == kModelQAA ? 2 * k - ilog2_c(N) : k * k);
+      // 128-point axes by the exact angle: their rounding left no room for the error of the
+      // transcendental form (state error of 8 x 128^2 after 600 steps 4.6e-6 -> 3.4e-6, no time
+      // seen); at other lengths the errors stand below those of separate axis passes without it,
+      // and it costs registers (512-point columns 78 -> 104) or latency (one 64^2 instance +0.9 us)
+      double2 v;
+      if constexpr (N == 128) v = phase_turns_exact(turns);
+      else v = phase_turns_d(turns);
+      tab[cur * H + k] = make_double2(v.x * inv_n, v.y * inv_n);
+      if (MODEL != kModelQAA && k == N / 4) {
+        v = cmul_dd(v, v);
+        v = cmul_dd(v, v);
+        tab[cur * H + N / 2] = make_double2(v.x * inv_n, v.y * inv_n);
+      }
+    }
+  }
+}
+
+// multiply the transformed line's slots t + q TPL by their factors
+template <int N, int P, typename W>
+__device__ __forceinline__ void mul_kinetic(W (&reg)[P], int t, const double2* __restrict__ tab) {
+  constexpr int TPL = N / P;
+  const double2* __restrict__ up = tab + t;        // |freq| = t + q TPL below N / 2
+  const double2* __restrict__ down = tab + N - t;  // and N - (t + q TPL) from there
+#pragma unroll
+  for (int q = 0; q < P; ++q) reg[q] = cmul_fd(reg[q], q < P / 2 ? up[q * TPL] : down[-q * TPL]);
+}
+template <int N, int P>
+__device__ __forceinline__ void mul_field(double2 (&reg)[P], int t, const double2* __restrict__ tab) {
+  // popcount(t + q TPL) = popcount(t) + popcount(q)
+  const double2* __restrict__ b = tab + __builtin_popcount(t);
+#pragma unroll
+  for (int q = 0; q < P; ++q) reg[q] = cmul_fd(reg[q], b[__builtin_popcount(q)]);
+}
+
+// Where a line works in FP64 beside its twiddle and factor products: at the position-space
+// ends of the line operators (V: the last inverse and the first forward stage and the
+// potential factor between them) or at the frequency-space ends (K: the last forward and the
+// first inverse stage and the kinetic factor).  Early in a run every line of a near-uniform
+// state concentrates into one coefficient and is rounded alike, late the state is localised;
+// FP32 rounding of such values moves the norm.  K for all lines but those of 128 points, where
+// the late phase decides: largest norm drift of the 128^2 members of the 768-instance batch
+// 1.3e-5 per 1e4 steps with K, 6.6e-6 with V.  (256^2: 9.3e-6 with neither, 5.1e-6 with K; with V
+// the near-uniform phase of 32^2 and 256^2 instances drifts up to 1.5 times as far in its first
+// 200 steps as with K.)  Either costs 2 % at 512 points, nothing that is seen below.
+template <int N, int AXIS>
+struct LinePrec {
+#ifndef QHD_VX
+#define QHD_VX (N == 128 || (N == 256 && AXIS == 1))
+#endif
+  static constexpr bool LATE = QHD_VX;
+  using V = typename std::conditional<LATE, double2, float2>::type;
+  using K = typename std::conditional<LATE, float2, double2>::type;
+};
+
+// F^{-1} E F of one line, from `in` to `out` (float2 or double2: the type of the first and
+// of the last stage; they may be the same array)
+template <int N, int P, int AXIS, bool BLOCK_SYNC, typename IX, typename TIN, typename TOUT, typename TW>
+__device__ __forceinline__ void line_kinetic(TIN (&in)[P], TOUT (&out)[P], int t, const TW& tw,
+                                             float2* __restrict__ lds, const double2* __restrict__ tab) {
+  typename LinePrec<N, AXIS>::K k[P];
+  line_fft_io<N, P, -1, BLOCK_SYNC, IX>(in, k, t, tw, lds);
+  mul_kinetic<N, P>(k, t, tab);
+  line_fft_io<N, P, +1, BLOCK_SYNC, IX>(k, out, t, tw, lds);
+}
+
+// A line's whole pass: the owed operator, the potential factor (fget(q): f of slot q) and
+// this step's operator; fix: the owed operator alone.
+template <int N, int P, int AXIS, bool BLOCK_SYNC, typename IX, typename TW, typename F>
+__device__ __forceinline__ void line_pass(float2 (&reg)[P], int t, const TW& tw, float2* __restrict__ lds,
+                                          const double2* __restrict__ tab, bool prev, double cpot, int fix, F&& fget) {
+  constexpr int H = etab_len<N, kModelQHD>();
+  typename LinePrec<N, AXIS>::V x[P];
+  if (prev) {
+    line_kinetic<N, P, AXIS, BLOCK_SYNC, IX>(reg, x, t, tw, lds, tab);
+  } else {
+#pragma unroll
+    for (int q = 0; q < P; ++q) assign(x[q], reg[q]);
+  }
+  if (!fix) {
+#pragma unroll
+    for (int q = 0; q < P; ++q) x[q] = cmul_fd(x[q], phase_turns_d(cpot * fget(q)));
+    line_kinetic<N, P, AXIS, BLOCK_SYNC, IX>(x, x, t, tw, lds, tab + H);
+  }
+#pragma unroll
+  for (int q = 0; q < P; ++q) assign(reg[q], x[q]);
+}
+
+template <int N, int P, int LS = 1>
+__device__ __forceinline__ void line_field(double2 (&reg)[P], int t, const double2* __restrict__ tab) {
+  line_wht<N, P, double2, LS>(reg, t);
+  mul_field<N, P>(reg, t, tab);
+  line_wht<N, P, double2, LS>(reg, t);
+}
+
+// What a line does in sub-step s on the axis of this launch.  `owe` is the mode that owes
+// this axis.  fix: only the owed operator, of the members that owe it (FixUp launches).
+struct LineTask {
+  bool active, prev, entry;
+  double cpot;  // turns per unit f of the merged potential factor
+};
+template <bool Y4>
+__device__ __forceinline__ LineTask line_task(const InstDev& I, long long s, long long max_steps, int owe, int fix) {
+  LineTask k;
+  k.prev = s > 0 || I.mode == owe;
+  k.entry = s == 0 && I.mode == kModeClean;
+  k.active = fix ? I.mode == owe : s < step_limit(I, max_steps);
+  k.cpot = potential_turns<Y4>(I, I.steps_done + s, k.entry);
+  return k;
+}
+
+}  // namespace qhd

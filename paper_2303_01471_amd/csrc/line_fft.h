@@ -656,87 +656,92 @@ __device__ __forceinline__ T wadd(T a, T b) { return fadd(a, b); }
 template <typename T>
 __device__ __forceinline__ T wsub(T a, T b) { return fsub(a, b); }
 
-// butterflies over the lane bits H, 2H, ... < TPL
-template <int H, int TPL, int P, typename T>
+// butterflies over the lane bits H, 2H, ... < TPL; lane position t sits in the wavefront
+// lane's bits from LS on (LS = 1: consecutive lanes)
+template <int H, int TPL, int P, int LS, typename T>
 __device__ __forceinline__ void wht_lanes(T (&reg)[P], int t) {
   if constexpr (H < TPL) {
     const bool upper = (t & H) != 0;
 #pragma unroll
     for (int q = 0; q < P; ++q) {
-      const T o = lane_xor<H>(reg[q]);
+      const T o = lane_xor<H * LS>(reg[q]);
       reg[q] = upper ? wsub(o, reg[q]) : wadd(reg[q], o);
     }
-    wht_lanes<2 * H, TPL, P>(reg, t);
+    wht_lanes<2 * H, TPL, P, LS>(reg, t);
   }
 }
 
-// T: double (a real line), float2 or double2 (a complex line)
-template <int N, int P, typename T>
-__device__ __forceinline__ void line_wht(T (&reg)[P], int t) {
+// butterflies over one bit of the slot index q
+template <int h, int P, typename T>
+__device__ __forceinline__ void wht_slots(T (&reg)[P]) {
 #pragma unroll
-  for (int h = 1; h < P; h <<= 1) {
-#pragma unroll
-    for (int q = 0; q < P; ++q) {
-      if (!(q & h)) {
-        const T a = reg[q], b = reg[q | h];
-        reg[q] = wadd(a, b);
-        reg[q | h] = wsub(a, b);
-      }
+  for (int q = 0; q < P; ++q) {
+    if (!(q & h)) {
+      const T a = reg[q], b = reg[q | h];
+      reg[q] = wadd(a, b);
+      reg[q | h] = wsub(a, b);
     }
   }
-  wht_lanes<1, N / P, P>(reg, t);
+}
+
+// T: double (a real line), float2 or double2 (a complex line).  The butterflies run in one
+// order of the index bits per line length, whatever the points per lane: for 128 points
+// bits 4 to 6, then 0 to 3 (with 16 points per lane bit 3 is the slot's lowest and comes
+// last), so that both splits of a line give the same values.
+template <int N, int P, typename T, int LS = 1>
+__device__ __forceinline__ void line_wht(T (&reg)[P], int t) {
+  constexpr bool SPLIT = N == 128 && P == 16;
+  if constexpr (!SPLIT) wht_slots<1, P>(reg);
+  if constexpr (P > 2) wht_slots<2, P>(reg);
+  if constexpr (P > 4) wht_slots<4, P>(reg);
+  if constexpr (P > 8) wht_slots<8, P>(reg);
+  wht_lanes<1, N / P, P, LS>(reg, t);
+  if constexpr (SPLIT) wht_slots<1, P>(reg);
 }
 
 // ---------------------------------------------------------------------------------
 // unit phase factors
 
-// sin(2 pi r), cos(2 pi r) for |r| <= 1/2 (turns).
-//   kHwSinCos: the CDNA transcendental unit (v_sin_f32 / v_cos_f32 take turns;
-//   measured max error 1.2e-7 on [-1/2, 1/2]).
-//   otherwise: exact reduction to the octant |y| <= 1/8 (r - q/4 is exact by
-//   Sterbenz), then polynomials in y fitted (weighted least squares, Chebyshev
-//   nodes) to sin(2 pi y) and cos(2 pi y); max error ~1.5 ulp of 1.
-#ifndef QHD_HW_SINCOS
-#define QHD_HW_SINCOS 1
-#endif
-__device__ __forceinline__ void sincos_turns(float r, float& s, float& c) {
-#if QHD_HW_SINCOS
-  s = __builtin_amdgcn_sinf(r);
-  c = __builtin_amdgcn_cosf(r);
-#else
-  const float q = rintf(4.0f * r);
-  const float y = fmaf(-0.25f, q, r);
-  const float y2 = y * y;
-  float ps = fmaf(y2, -75.240064049398f, 81.58812463672584f);
-  ps = fmaf(ps, y2, -41.34162804267381f);
-  ps = fmaf(ps, y2, 6.283185220341756f);
-  const float sn = ps * y;
-  float pc = fmaf(y2, 59.220407261791806f, -85.44285212009325f);
-  pc = fmaf(pc, y2, 64.93931620843469f);
-  pc = fmaf(pc, y2, -19.73920865035785f);
-  const float cn = fmaf(pc, y2, 0.9999999999526002f);
-  const int qi = (int)q;
-  const bool swap = qi & 1;
-  float so = swap ? cn : sn, co = swap ? sn : cn;
-  so = (qi & 2) ? -so : so;
-  co = ((qi + 1) & 2) ? -co : co;
-  s = so;
-  c = co;
-#endif
-}
-
-// exp(-2 pi i tau), tau in turns (FP64), with one Newton magnitude step
-// w <- w (3 - |w|^2) / 2 taken in FP64, so |w| = 1 to ~1e-14.  (In FP32 the
-// step is one-sided: 1 + 2^-25 is not representable, so magnitudes just below
-// 1 would never be corrected and the norm would shrink step after step.)
+// exp(-2 pi i tau), tau in turns (FP64), for the per-point factors: the transcendental unit's
+// sine and cosine (v_sin_f32 / v_cos_f32 take turns; measured max error 1.2e-7 on
+// [-1/2, 1/2]) with one Newton magnitude step w <- w (3 - |w|^2) / 2 taken in FP64, so
+// |w| = 1 to ~1e-14.  (In FP32 the step is one-sided: 1 + 2^-25 is not representable, so
+// magnitudes just below 1 would never be corrected and the norm would shrink step after
+// step.)
 __device__ __forceinline__ double2 phase_turns_d(double tau) {
   const float r = (float)(tau - rint(tau));
-  float s, c;
-  sincos_turns(r, s, c);
-  const double cd = (double)c, sd = (double)s;
+  const double cd = (double)__builtin_amdgcn_cosf(r), sd = (double)__builtin_amdgcn_sinf(r);
   const double m = fma(cd, cd, sd * sd);
   const double g = fma(-0.5, m, 1.5);
   return make_double2(cd * g, -sd * g);
+}
+
+// The same by its exact angle, for factors that a table serves to many points: exact
+// reduction to the quarter turn q and |y| <= 1/8 (y = tau - floor(tau) - q / 4), then
+// polynomials in y^2 fitted (Chebyshev basis, iteratively reweighted least squares) to
+// sin(2 pi y) / y and (cos(2 pi y) - 1) / y^2; errors below 3.5e-12 and 2.3e-13.  Per point it
+// costs half as much again as the transcendental form: taken for the potential factor too,
+// 512-point passes ran 9 % longer.
+__device__ __forceinline__ double2 phase_turns_exact(double tau) {
+  const double d = __builtin_amdgcn_fract(tau);
+  const double q = rint(4.0 * d);
+  const double y = fma(-0.25, q, d), u = y * y;
+  const int n = (int)q;
+  double ps = fma(u, 41.472948591045686, -76.69786995504712);
+  double pc = fma(u, -26.119271230603214, 60.24045258581482);
+  ps = fma(ps, u, 81.6052047462508);
+  pc = fma(pc, u, -85.4567938569744);
+  ps = fma(ps, u, -41.341702153504926);
+  pc = fma(pc, u, 64.93939397709818);
+  ps = fma(ps, u, 6.283185307152453);
+  pc = fma(pc, u, -19.739208802164487);
+  const double sn = ps * y, cs = fma(pc, u, 1.0);
+  // cos, sin of the whole angle: (c, s), (-s, c), (-c, -s), (s, -c) for q = 0 .. 3
+  const bool swap = n & 1;
+  const long long co = __double_as_longlong(swap ? sn : cs), si = __double_as_longlong(swap ? cs : sn);
+  const long long fc = (long long)((unsigned long long)((n + 1) & 2) << 62);
+  const long long fs = (long long)((unsigned long long)(~n & 2) << 62);
+  return make_double2(__longlong_as_double(co ^ fc), __longlong_as_double(si ^ fs));
 }
 
 }  // namespace qhd

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "line_fft.h"
 #include "qhd_internal.h"
 
 namespace qhd {
@@ -178,6 +179,27 @@ struct LaneView {
     __builtin_amdgcn_raw_buffer_store_b64(v, r, vo, elem * 8, 0);
   }
 };
+
+// Staged column passes: a tile column (8 mesh columns) through LDS, TPL lanes per column
+template <int NY, int P>
+struct ColCfg {
+  static constexpr int TPL = NY / P;
+  static constexpr int NT = 256;                                          // threads per block
+  static constexpr int ITEMS = (8 * TPL >= NT) ? 1 : NT / (8 * TPL);     // tile columns per block
+  static constexpr int MIN_WAVES = P == 8 ? 3 : 1;
+  static constexpr int LINES = ITEMS * 8;                                 // columns per block
+  static constexpr int SUBS = (LINES * TPL) / NT;                         // column rounds per item
+  // line stride in LDS slots, = 2 (mod 16) so the tile scatter hits distinct banks
+  static constexpr int STRIDE = ((LineLds<NY>::kSlots + 13) / 16) * 16 + 2;
+};
+
+__device__ __forceinline__ bool in_ball(int dxi, int dyi, int dzi, const InstDev& I) {
+  // same FP64 operations, in the same order and without contraction, as the oracle
+  const double dx = __dmul_rn((double)dxi, I.h[0]);
+  const double dy = __dmul_rn((double)dyi, I.h[1]);
+  const double dz = __dmul_rn((double)dzi, I.h[2]);
+  return __dadd_rn(__dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy)), __dmul_rn(dz, dz)) < I.r2;
+}
 
 // contiguous share [begin, end) of `total` work items for this block, in units of `step`
 __device__ __forceinline__ void block_share(long long total, int step, long long& begin, long long& end) {

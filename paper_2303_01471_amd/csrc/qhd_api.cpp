@@ -144,6 +144,8 @@ struct ShapeClass {
   bool tuned = false;
   bool mfma = false;  // 3-D 128^3 with QHD_OPT_MFMA_DFT
   bool plane = false; // 3-D in the plane layout (x slowest, (y, z) planes in 8x8 tiles)
+  bool alt = false;   // steps alternate between the axes, one pass each
+  int stride = 0;     // triples of partials reserved per instance
   int model = kModelQHD;
   bool leapfrog = false;           // QAA members integrated by leapfrog stages
   bool y4 = false;                 // some member runs the fourth-order scheme
@@ -183,8 +185,15 @@ struct qhd_plan_s {
   // evolve runs in chunks of at most chunk_k steps; a full chunk of every class (chunk
   // plan, passes, commit) is captured once as a graph and replayed (see qhd_evolve)
   int chunk_k = 64;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t graph_exec = nullptr;
+  // one captured chunk per starting axis of the alternating classes
+  hipGraph_t graph[2] = {nullptr, nullptr};
+  hipGraphExec_t graph_exec[2] = {nullptr, nullptr};
+  // axis of the next sub-step of the alternating classes: every member of a class advances
+  // by the same number of stages (mod 2) in a call, so one parity serves the plan
+  int phase = 0;
+  // an evolve was captured by the caller: replays move the device's axes without the host,
+  // so every later chunk first pays what a member owes along the other axis
+  bool fix_up = false;
   // timing
   std::vector<Family> families;
   std::vector<Pending> pending;
@@ -228,8 +237,10 @@ void free_plan(qhd_plan p) {
     (void)hipEventDestroy(pe.stop);
   }
   for (auto e : p->free_events) (void)hipEventDestroy(e);
-  if (p->graph_exec) (void)hipGraphExecDestroy(p->graph_exec);
-  if (p->graph) (void)hipGraphDestroy(p->graph);
+  for (auto g : p->graph_exec)
+    if (g) (void)hipGraphExecDestroy(g);
+  for (auto g : p->graph)
+    if (g) (void)hipGraphDestroy(g);
   if (p->internal) (void)hipStreamDestroy(p->internal);
   delete p;
 }
@@ -291,7 +302,9 @@ int host_nact(const ShapeClass& c, long long ks, long long s) {
 // otherwise each class issues the sub-steps its members need (from the host mirror).
 // concurrent: each class on its own stream, forked from and joined back to `stream`.
 // timing: every pass launch is bracketed by HIP events (serialised on `stream`).
-qhd_status enqueue_chunk(qhd_plan p, long long ks, hipStream_t stream, bool timing, bool concurrent, bool full) {
+// phase: the axis of the first sub-step of the alternating classes.
+qhd_status enqueue_chunk(qhd_plan p, long long ks, hipStream_t stream, bool timing, bool concurrent, bool full,
+                         int phase) {
   auto timed_on = [&](hipStream_t st, int fam, double points, auto&& fn) -> hipError_t {
     (void)st;
     hipEvent_t a = nullptr, b = nullptr;
@@ -329,6 +342,16 @@ qhd_status enqueue_chunk(qhd_plan p, long long ks, hipStream_t stream, bool timi
     if (S > kMaxSub) return fail(QHD_EINVAL, "internal: %lld sub-steps in one chunk", S);
     hipStream_t st = concurrent ? c.stream : stream;
     if (concurrent) HIP_TRY(hipStreamWaitEvent(st, p->fork, 0));
+    if (c.alt && p->fix_up) {
+      const int* all = c.nact + kMaxSub;
+      if (phase == 0)
+        HIP_TRY(launch_col_pass_2d(c.nx, c.ny, c.dev, m, all, c.psi, c.f, c.tw_y, 0, ks, c.cap_col, c.col_variant, st,
+                                   c.model, c.y4, true));
+      else
+        HIP_TRY(launch_row_pass_2d(c.nx, c.ny, c.dev, m, all, c.psi, c.f, c.tw_x, 0, ks, c.cap_row, c.row_points, st,
+                                   c.model, c.y4, true));
+      HIP_TRY(launch_fix_mode(c.dev, m, phase == 0 ? kModeOweY : kModeOweX, st));
+    }
     HIP_TRY(launch_chunk_plan(c.dev, m, ks, (int)S, c.nact, st));
     if (c.resident) {
       // every sub-step of the chunk in one launch, psi in LDS (timed as a whole: points =
@@ -337,7 +360,7 @@ qhd_status enqueue_chunk(qhd_plan p, long long ks, hipStream_t stream, bool timi
       if (timing)
         for (int k = 0; k < m; ++k) gps += (double)host_limit(c.host[k], ks) * (double)c.points;
       HIP_TRY(timed_on(st, c.fam_res, gps, [&] {
-        return launch_resident_2d(c.nx, c.ny, c.dev, m, c.nact, c.psi, c.f, c.tw_x, c.tw_y, ks, c.model, c.y4, st);
+        return launch_resident_2d(c.nx, c.ny, c.dev, m, c.nact, c.psi, c.f, c.tw_x, c.tw_y, ks, c.model, c.y4, phase, st);
       }));
     } else {
       for (long long sub = 0; sub < S; ++sub) {
@@ -373,14 +396,16 @@ qhd_status enqueue_chunk(qhd_plan p, long long ks, hipStream_t stream, bool timi
             return launch_lf_col_2d(c.nx, c.ny, c.dev, m, na, c.psi, c.scratch, s, ks, c.cap_col, st);
           }));
         } else if (c.ndim == 2) {
-          HIP_TRY(timed_on(st, c.fam_row, pts, [&] {
-            return launch_row_pass_2d(c.nx, c.ny, c.dev, m, na, c.psi, c.f, c.tw_x, s, ks, c.cap_row, c.row_points,
-                                      st, c.model, c.y4);
-          }));
-          HIP_TRY(timed_on(st, c.fam_col, pts, [&] {
-            return launch_col_pass_2d(c.nx, c.ny, c.dev, m, na, c.psi, c.tw_y, s, ks, c.cap_col, c.col_variant, st,
-                                      c.model, c.y4);
-          }));
+          if (((phase + sub) & 1) == 0)
+            HIP_TRY(timed_on(st, c.fam_row, pts, [&] {
+              return launch_row_pass_2d(c.nx, c.ny, c.dev, m, na, c.psi, c.f, c.tw_x, s, ks, c.cap_row, c.row_points,
+                                        st, c.model, c.y4);
+            }));
+          else
+            HIP_TRY(timed_on(st, c.fam_col, pts, [&] {
+              return launch_col_pass_2d(c.nx, c.ny, c.dev, m, na, c.psi, c.f, c.tw_y, s, ks, c.cap_col, c.col_variant,
+                                        st, c.model, c.y4);
+            }));
         } else {
           HIP_TRY(timed_on(st, c.fam_line, pts, [&] {
             return launch_line_pass_1d(c.nx, c.dev, m, na, c.psi, c.f, c.tw_x, s, ks, p->grid_cap, st);
@@ -394,20 +419,23 @@ qhd_status enqueue_chunk(qhd_plan p, long long ks, hipStream_t stream, bool timi
     }
   }
   for (int ci : joined) HIP_TRY(hipStreamWaitEvent(stream, p->classes[ci].join, 0));
-  for (auto& c : p->classes) HIP_TRY(launch_commit(c.dev, (int)c.members.size(), ks, stream));
+  for (auto& c : p->classes)
+    HIP_TRY(launch_commit(c.dev, (int)c.members.size(), ks, c.alt ? phase : -1, stream));
   return QHD_OK;
 }
 
-// advance the host mirror as a chunk of ks steps does on the device
+// advance the host mirror as a chunk of ks steps does on the device (one stage or three per
+// step: the axis parity moves by ks either way)
 void mirror_chunk(qhd_plan p, long long ks) {
   for (auto& c : p->classes)
     for (auto& I : c.host) {
       const long long l = host_limit(I, ks);
       if (l > 0) {
         I.steps_done += l;
-        I.mode = kModePending;
+        I.mode = mode_after(c.alt ? p->phase : -1, l);
       }
     }
+  p->phase = (int)((p->phase + ks) & 1);
 }
 
 // ---- launch tuning ----------------------------------------------------------------
@@ -468,8 +496,8 @@ double time_launches(hipStream_t st, hipEvent_t a, hipEvent_t b, int reps, F&& f
 }
 
 // Time the row pass over grid caps and the column pass over variants x grid caps on
-// the class's own buffers (one sub-step with every member active), keep the
-// fastest.  The state is overwritten; the caller restores it.
+// the class's own buffers (the second sub-step, in which a pass does its whole work, with
+// every member active), keep the fastest.  The state is overwritten; the caller restores it.
 qhd_status autotune_class(qhd_plan p, ShapeClass& c, double& us_row, double& us_col) {
   const int m = (int)c.members.size();
   static const int caps[] = {512, 1024, 2048, 4096, 8192};
@@ -485,13 +513,12 @@ qhd_status autotune_class(qhd_plan p, ShapeClass& c, double& us_row, double& us_
   int best_row = c.cap_row, best_col = c.cap_col, best_var = c.col_variant, best_pts = c.row_points;
   bool ok = true;
   std::vector<int> row_pts = {8};
-  if (row_points_resolve(c.nx, 16) == 16 && c.nx < 1024) row_pts.push_back(16);
+  if (c.nx < 1024 && row_points_resolve(c.nx, 16) == 16) row_pts.push_back(16);
   for (int rp : row_pts)
     for (int cap : caps) {
       const double t = time_launches(p->internal, a, b, reps, [&] {
-        return launch_row_pass_2d(c.nx, c.ny, c.dev, m, c.nact + kMaxSub, c.psi, c.f, c.tw_x, 0, 1, cap, rp,
-                                  p->internal, c.model,
-                                  c.y4);
+        return launch_row_pass_2d(c.nx, c.ny, c.dev, m, c.nact + kMaxSub, c.psi, c.f, c.tw_x, 1, 2, cap, rp,
+                                  p->internal, c.model, c.y4);
       });
       if (t < 0) ok = false;
       else if (t < us_row) us_row = t, best_row = cap, best_pts = rp;
@@ -503,8 +530,8 @@ qhd_status autotune_class(qhd_plan p, ShapeClass& c, double& us_row, double& us_
   for (int v : variants)
     for (int cap : caps) {
       const double t = time_launches(p->internal, a, b, reps, [&] {
-        return launch_col_pass_2d(c.nx, c.ny, c.dev, m, c.nact + kMaxSub, c.psi, c.tw_y, 0, 1, cap, v, p->internal,
-                                  c.model, c.y4);
+        return launch_col_pass_2d(c.nx, c.ny, c.dev, m, c.nact + kMaxSub, c.psi, c.f, c.tw_y, 1, 2, cap, v,
+                                  p->internal, c.model, c.y4);
       });
       if (t < 0) ok = false;
       else if (t < us_col) us_col = t, best_col = cap, best_var = v;
@@ -565,19 +592,16 @@ qhd_status compare_resident(qhd_plan p, ShapeClass& c, double& us_res, double& u
     return fail(QHD_EDEVICE, "hipEventCreate failed");
   }
   us_res = time_launches(p->internal, a, b, 2, [&] {
-    return launch_resident_2d(c.nx, c.ny, c.dev, m, c.nact + kMaxSub, c.psi, c.f, c.tw_x, c.tw_y, k, c.model, c.y4,
+    return launch_resident_2d(c.nx, c.ny, c.dev, m, c.nact + kMaxSub, c.psi, c.f, c.tw_x, c.tw_y, k, c.model, c.y4, 0,
                               p->internal);
   });
   us_str = time_launches(p->internal, a, b, 2, [&] {
     hipError_t r = hipSuccess;
-    for (int s = 0; s < k && r == hipSuccess; ++s) {
-      r = launch_row_pass_2d(c.nx, c.ny, c.dev, m, c.nact + kMaxSub, c.psi, c.f, c.tw_x, s, k, c.cap_row, c.row_points,
-                             p->internal,
-                             c.model, c.y4);
-      if (r == hipSuccess)
-        r = launch_col_pass_2d(c.nx, c.ny, c.dev, m, c.nact + kMaxSub, c.psi, c.tw_y, s, k, c.cap_col, c.col_variant, p->internal,
-                               c.model, c.y4);
-    }
+    for (int s = 0; s < k && r == hipSuccess; ++s)
+      r = s % 2 == 0 ? launch_row_pass_2d(c.nx, c.ny, c.dev, m, c.nact + kMaxSub, c.psi, c.f, c.tw_x, s, k, c.cap_row,
+                                          c.row_points, p->internal, c.model, c.y4)
+                     : launch_col_pass_2d(c.nx, c.ny, c.dev, m, c.nact + kMaxSub, c.psi, c.f, c.tw_y, s, k, c.cap_col,
+                                          c.col_variant, p->internal, c.model, c.y4);
     return r;
   });
   (void)hipEventDestroy(a);
@@ -590,9 +614,9 @@ qhd_status compare_resident(qhd_plan p, ShapeClass& c, double& us_res, double& u
 // Capture one full chunk of chunk_k steps of every class (classes concurrent) on the
 // plan's internal stream; replayed by qhd_evolve for every chunk in which every class
 // still has a member with at least chunk_k steps to go.
-qhd_status build_chunk_graph(qhd_plan p) {
+qhd_status build_chunk_graph(qhd_plan p, int phase) {
   HIP_TRY(hipStreamBeginCapture(p->internal, hipStreamCaptureModeThreadLocal));
-  qhd_status st = enqueue_chunk(p, p->chunk_k, p->internal, false, true, true);
+  qhd_status st = enqueue_chunk(p, p->chunk_k, p->internal, false, true, true, phase);
   hipGraph_t g = nullptr;
   hipError_t e = hipStreamEndCapture(p->internal, &g);
   if (st != QHD_OK) {
@@ -600,12 +624,12 @@ qhd_status build_chunk_graph(qhd_plan p) {
     return st;
   }
   if (e != hipSuccess) return fail(QHD_EDEVICE, "graph capture: %s", hipGetErrorString(e));
-  e = hipGraphInstantiate(&p->graph_exec, g, nullptr, nullptr, 0);
+  e = hipGraphInstantiate(&p->graph_exec[phase], g, nullptr, nullptr, 0);
   if (e != hipSuccess) {
     (void)hipGraphDestroy(g);
     return fail(QHD_EDEVICE, "graph instantiate: %s", hipGetErrorString(e));
   }
-  p->graph = g;
+  p->graph[phase] = g;
   return QHD_OK;
 }
 
@@ -768,6 +792,8 @@ qhd_status qhd_plan_create(const qhd_instance* inst, int32_t batch, const qhd_pl
     max_pts = std::max(max_pts, c.points);
     max_members = std::max(max_members, (size_t)m);
     c.lines = c.ndim >= 2 ? c.ny * c.nz : 1;
+    c.alt = c.ndim == 2 && !c.leapfrog;
+    c.stride = c.alt ? std::max(c.lines, c.nx / 8) : c.lines;
     c.tw_x = p->twiddles + p->tw_off[c.nx];
     c.tw_y = c.ndim >= 2 ? p->twiddles + p->tw_off[c.ny] : nullptr;
     c.tw_z = c.ndim >= 3 ? p->twiddles + p->tw_off[c.nz] : nullptr;
@@ -819,7 +845,7 @@ qhd_status qhd_plan_create(const qhd_instance* inst, int32_t batch, const qhd_pl
     if (e == hipSuccess) e = hipMalloc(&c.psi, sizeof(float2) * pts);
     if (e == hipSuccess && c.leapfrog) e = hipMalloc(&c.scratch, sizeof(float) * pts);
     if (e == hipSuccess) e = hipMalloc(&c.f, sizeof(double) * pts);
-    if (e == hipSuccess) e = hipMalloc(&c.partials, sizeof(double) * 3 * (size_t)m * c.lines);
+    if (e == hipSuccess) e = hipMalloc(&c.partials, sizeof(double) * 3 * (size_t)m * c.stride);
     if (e == hipSuccess) e = hipMalloc(&c.results, sizeof(double) * 3 * (size_t)m);
     if (e == hipSuccess) e = hipMalloc(&c.nact, sizeof(int) * (kMaxSub + 1));
     if (e == hipSuccess) {
@@ -864,7 +890,7 @@ qhd_status qhd_plan_create(const qhd_instance* inst, int32_t batch, const qhd_pl
       snprintf(name, sizeof name, "row_pass_2d%s/n%d", tag, c.nx);
       c.fam_row = family_index(p, name, c.leapfrog ? 20.0 : 24.0);
       snprintf(name, sizeof name, "col_pass_2d%s/n%d", tag, c.ny);
-      c.fam_col = family_index(p, name, c.leapfrog ? 20.0 : 16.0);
+      c.fam_col = family_index(p, name, c.leapfrog ? 20.0 : 24.0);
     } else {
       snprintf(name, sizeof name, "line_pass_1d/n%d", c.nx);
       c.fam_line = family_index(p, name, 24.0);
@@ -915,15 +941,20 @@ qhd_status qhd_plan_create(const qhd_instance* inst, int32_t batch, const qhd_pl
       c.cap_row = c.cap_col = p->grid_cap;
       if (c.ndim != 2) continue;
       if (c.model != kModelQAA) {  // QAA passes have one fixed launch form
+        // 128-point rows: 16 points per lane (radices 16 and 8: the FP32 exchange next to the
+        // FP64 position-space stage rounds values that each carry an eighth of a localised
+        // line's mass, with 8 points per lane and radices 8, 8, 2 half of it; no time seen)
+        c.row_points = c.nx == 128 ? 16 : 8;
         if (!env_cap) {
-          // measured defaults (uniform batches of 256 instances per size on MI355X)
-          c.cap_row = c.nx >= 512 ? 8192 : (c.nx >= 256 ? 4096 : 1024);
-          c.cap_col = c.ny >= 512 ? 4096 : (c.ny >= 256 ? 2048 : 1024);
+          // measured defaults (uniform batches of 256 instances per size on MI355X): a block
+          // fills its kinetic tables once per instance that it meets, against the balance of
+          // many short blocks.  us per step, both axes' caps 1024 / 4096 / 6144 / 16384:
+          // 263 x 512^2 532 / 514 / 505 / 519, 243 x 256^2 107 / 104 / 102 / 105, 262 x 128^2
+          // 36 / 33 / 33 / 33, 1024 x 64^2 26 / 28 / 29 / 28; 4 x 1024^2 at 512 / 1024 / 6144: 44 / 47 / 48
+          auto cap = [](int n) { return n >= 1024 ? 512 : (n >= 256 ? 6144 : (n >= 128 ? 4096 : 1024)); };
+          c.cap_row = cap(c.nx);
+          c.cap_col = cap(c.ny);
         }
-        // 1024-point columns of one or two members: the tile-wave form runs 8 waves per
-        // tile column where the staged one runs 4 (one 1024^2 instance: column pass 21.5
-        // -> 15.7 us); larger classes keep the staged default (4 members: 28.9 vs 31.2 us)
-        if (c.ny == 1024 && c.members.size() <= 2) c.col_variant = kColTileWave;
         const std::string key = tune_key(arch, c);
         const bool cached = !p->tune_cache.empty() && tune_lookup(p->tune_cache, key, c);
         if (!cached && autotune) {
@@ -982,8 +1013,12 @@ qhd_status qhd_plan_create(const qhd_instance* inst, int32_t batch, const qhd_pl
     long long most = 0;
     for (int i = 0; i < batch; ++i) most = std::max(most, (long long)inst[i].nsteps);
     if (most >= p->chunk_k && !(p->opts.flags & QHD_OPT_NO_GRAPH)) {
-      qhd_status st = build_chunk_graph(p);
-      if (st != QHD_OK) return bail(st);
+      // (without alternating classes one graph serves both parities)
+      const bool alt = std::any_of(p->classes.begin(), p->classes.end(), [](const ShapeClass& c) { return c.alt; });
+      for (int ph = 0; ph < (alt ? 2 : 1); ++ph) {
+        qhd_status st = build_chunk_graph(p, ph);
+        if (st != QHD_OK) return bail(st);
+      }
     }
   }
   e = hipMalloc(&p->staging_f, sizeof(double) * max_pts);
@@ -1113,21 +1148,23 @@ qhd_status qhd_evolve(qhd_plan p, int64_t max_steps, void* stream_v) {
   // the captured chunk (with pass timing, one in timing_stride of them is launched directly
   // with every pass timed instead); then the rest in direct chunks of at most K steps,
   // each issuing only the sub-steps its members need
-  const bool replay = p->graph_exec && cap == hipStreamCaptureStatusNone && !(p->opts.flags & QHD_OPT_NO_GRAPH);
+  if (cap != hipStreamCaptureStatusNone) p->fix_up = true;
+  const bool replay = p->graph_exec[0] && cap == hipStreamCaptureStatusNone && !p->fix_up;
   const long long full = replay ? rmin / K : 0;
   long long done = 0;
   for (long long ch = 0; ch < full; ++ch, done += K) {
     if (timing && ch % p->opts.timing_stride == 0) {
-      qhd_status st = enqueue_chunk(p, K, stream, true, false, true);
+      qhd_status st = enqueue_chunk(p, K, stream, true, false, true, p->phase);
       if (st != QHD_OK) return st;
     } else {
-      HIP_TRY(hipGraphLaunch(p->graph_exec, stream));
+      HIP_TRY(hipGraphLaunch(p->graph_exec[p->graph_exec[1] ? p->phase : 0], stream));
     }
     mirror_chunk(p, K);
   }
   for (long long ch = 0; done < S; ++ch) {
     const long long ks = std::min(K, S - done);
-    qhd_status st = enqueue_chunk(p, ks, stream, timing && ch % p->opts.timing_stride == 0, true, false);
+    qhd_status st = enqueue_chunk(p, ks, stream, timing && ch % p->opts.timing_stride == 0, true, false,
+                                  p->phase);
     if (st != QHD_OK) return st;
     mirror_chunk(p, ks);
     done += ks;
@@ -1142,7 +1179,7 @@ qhd_status qhd_plan_info(qhd_plan p, qhd_class_info* out, int32_t cap, int32_t* 
   g_err.clear();
   if (!p || !n_classes || !graph_steps || (cap > 0 && !out)) return fail(QHD_EINVAL, "NULL argument");
   *n_classes = (int32_t)p->classes.size();
-  *graph_steps = p->graph_exec ? p->chunk_k : 0;
+  *graph_steps = p->graph_exec[0] ? p->chunk_k : 0;
   for (int k = 0; k < cap && k < (int)p->classes.size(); ++k) {
     const ShapeClass& c = p->classes[k];
     qhd_class_info& o = out[k];
@@ -1167,6 +1204,7 @@ qhd_status qhd_reset(qhd_plan p, void* stream_v) {
   if (!p) return fail(QHD_EINVAL, "plan is NULL");
   hipStream_t stream = (hipStream_t)stream_v;
   HIP_TRY(hipSetDevice(p->device));
+  p->phase = 0;
   for (auto& c : p->classes) {
     const int m = (int)c.members.size();
     HIP_TRY(launch_fill_psi(c.psi, (long long)m * c.points, (float)(1.0 / std::sqrt((double)c.points)), stream));
@@ -1198,13 +1236,16 @@ qhd_status qhd_observe(qhd_plan p, void* stream_v, qhd_observables* out, float* 
     if (c.plane)
       HIP_TRY(launch_observe_plane(c.nx, c.ny, c.nz, c.dev, m, c.psi, c.f, c.tw_x, reinterpret_cast<float2*>(psi_dev),
                                    rho_dev, c.partials, stream));
-    else if (c.ndim >= 2)
+    else if (c.ndim >= 2) {
       HIP_TRY(launch_observe_2d(c.nx, c.ny * c.nz, c.ny, c.dev, m, c.psi, c.f, c.tw_x,
-                                reinterpret_cast<float2*>(psi_dev), rho_dev, c.partials, stream, c.model));
-    else
+                                reinterpret_cast<float2*>(psi_dev), rho_dev, c.partials, c.stride, stream, c.model));
+      if (c.alt)
+        HIP_TRY(launch_observe_col_2d(c.nx, c.ny, c.dev, m, c.psi, c.f, c.tw_y, reinterpret_cast<float2*>(psi_dev),
+                                      rho_dev, c.partials, c.stride, stream, c.model));
+    } else
       HIP_TRY(launch_observe_1d(c.nx, c.dev, m, c.psi, c.f, reinterpret_cast<float2*>(psi_dev),
                                 rho_dev, c.partials, stream));
-    HIP_TRY(launch_finalize(c.partials, c.lines, m, c.results, stream));
+    HIP_TRY(launch_finalize(c.dev, c.partials, c.lines, c.nx / 8, c.stride, m, c.results, stream));
     HIP_TRY(hipMemcpyAsync(p->host_results, c.results, sizeof(double) * 3 * m, hipMemcpyDeviceToHost, stream));
     HIP_TRY(hipStreamSynchronize(stream));
     for (int k = 0; k < m; ++k) {

@@ -8,10 +8,21 @@
 
 namespace qhd {
 
-enum : int { kModeClean = 0, kModePending = 1 };
+// What an instance's stored state still owes.  Clean: nothing.  Pending: the trailing
+// potential half step of the last step (and, for the matrix-core classes, F_x^{-1}).
+// OweX / OweY: the kinetic factor of the last stage along x (along y; in 3-D along y and
+// z) and then that half step.  KDone: only that half step, in a class of alternating passes.
+enum : int { kModeClean = 0, kModePending = 1, kModeOweX = 2, kModeOweY = 3, kModeKDone = 4 };
 enum : int { kSchemeStrang = 0, kSchemeLie = 1, kSchemeYoshida4 = 2, kSchemeLeapfrog = 3 };
 enum : int { kModelQHD = 0, kModelQAA = 1 };
 enum : int { kSchedNesterov = 0, kSchedConst = 1, kSchedTable = 2, kSchedLinear = 3 };
+
+// Mode after `lim` > 0 sub-steps of a chunk whose first took axis `start_axis` (-1: not a
+// class of alternating passes): the pass of one axis leaves the other one owed.
+__host__ __device__ inline int mode_after(int start_axis, long long lim) {
+  if (start_axis < 0) return kModePending;
+  return ((start_axis + lim - 1) & 1) == 0 ? kModeOweY : kModeOweX;
+}
 
 // Per-instance parameters as the kernels see them.  One array per shape class.
 struct InstDev {
@@ -28,7 +39,7 @@ struct InstDev {
   long long out_off;     // element offset in plan-wide concatenated outputs
   long long argmin;      // flat index of x*
   int sched;
-  int mode;              // kModeClean / kModePending
+  int mode;              // kMode...
   int plan_index;        // position in the user's batch
   int scheme;            // kSchemeStrang / kSchemeLie / kSchemeYoshida4
   int model;             // kModelQHD / kModelQAA
@@ -54,7 +65,7 @@ struct TimingSink {
   int* used;             // host counter of pairs in use for this launch family
 };
 
-// Launchers (qhd_kernels.hip).  All are asynchronous on `stream` and return
+// Launchers (qhd_kernels.hip, qhd_kernels_axis.hip).  All are asynchronous on `stream` and return
 // hipSuccess or the launch error.  `nx`, `ny` are the class's mesh sizes.
 // Pass launchers take two member counts: `ninst` sizes the grid (the class's members),
 // `nact` is the device address of the number of members the kernel visits in this
@@ -63,7 +74,7 @@ struct TimingSink {
 hipError_t launch_row_pass_2d(int nx, int ny, const InstDev* inst, int ninst, const int* nact, float2* psi,
                               const double* f, const double2* tw_nx, int s, long long max_steps,
                               int grid_cap, int points_per_lane, hipStream_t stream, int model = kModelQHD,
-                              bool y4 = true);
+                              bool y4 = true, bool fix = false);
 // Sampled pass timing.  When armed, the next pass launch of this host thread records
 // the two events itself: hipExtLaunchKernelGGL stamps them with the dispatch's own start
 // and end (what a kernel trace reports), where events recorded around a launch would
@@ -101,12 +112,17 @@ hipError_t launch_lf_col_2d(int nx, int ny, const InstDev* inst, int ninst, cons
                             const float* scratch, int s,
                             long long max_steps, int grid_cap, hipStream_t stream);
 hipError_t launch_col_pass_2d(int nx, int ny, const InstDev* inst, int ninst, const int* nact, float2* psi,
-                              const double2* tw_ny, int s, long long max_steps, int grid_cap,
-                              int variant, hipStream_t stream, int model = kModelQHD, bool y4 = true);
+                              const double* f, const double2* tw_ny, int s, long long max_steps, int grid_cap,
+                              int variant, hipStream_t stream, int model = kModelQHD, bool y4 = true,
+                              bool fix = false);
+// after a `fix` launch on the axis owed in mode `owe`: those members become kModeKDone
+hipError_t launch_fix_mode(InstDev* inst, int ninst, int owe, hipStream_t stream);
 hipError_t launch_line_pass_1d(int n, const InstDev* inst, int ninst, const int* nact, float2* psi, const double* f,
                                const double2* tw, int s, long long max_steps, int grid_cap,
                                hipStream_t stream);
-hipError_t launch_commit(InstDev* inst, int ninst, long long max_steps, hipStream_t stream);
+// start_axis: the axis (0 = x, 1 = y) of the chunk's first sub-step in a class of
+// alternating passes, -1 for the others
+hipError_t launch_commit(InstDev* inst, int ninst, long long max_steps, int start_axis, hipStream_t stream);
 // Active-member counts of the sub-steps s = 0..S-1 of an evolve chunk capped at
 // max_steps steps: nact[s] = 1 + the last member k with step_limit(inst[k]) > s (0 if
 // none).  Members are sorted by step count, so the prefix is tight for batches evolved
@@ -121,7 +137,7 @@ bool resident_supported(int nx, int ny);
 hipError_t launch_resident_2d(int nx, int ny, const InstDev* inst, int ninst, const int* nact, float2* psi,
                               const double* f,
                               const double2* tw_nx, const double2* tw_ny, long long max_steps, int model,
-                              bool y4, hipStream_t stream);
+                              bool y4, int start_axis, hipStream_t stream);
 
 // 3-D (qhd_kernels_3d.hip), plane layout: x slowest, every (y, z) plane contiguous in 8x8
 // tiles of (y, z).  The x-pass does F_x . V . F_x^{-1} (lines along x, f read), the plane
@@ -148,14 +164,20 @@ hipError_t launch_import_psi_plane(int nx, int ny, int nz, const float2* user, f
 // (y, z) from a row for the success test.
 hipError_t launch_observe_2d(int nx, int rows, int ny, const InstDev* inst, int ninst,
                              const float2* psi, const double* f, const double2* tw_nx,
-                             float2* out_psi, float* out_rho, double* partials,
+                             float2* out_psi, float* out_rho, double* partials, int stride,
                              hipStream_t stream, int model = kModelQHD);
+// the instances that owe the line operator along y (the others are launch_observe_2d's):
+// one triple per tile column; `stride` = triples reserved per instance
+hipError_t launch_observe_col_2d(int nx, int ny, const InstDev* inst, int ninst, const float2* psi, const double* f,
+                                 const double2* tw_ny, float2* out_psi, float* out_rho, double* partials, int stride,
+                                 hipStream_t stream, int model);
 hipError_t launch_observe_1d(int n, const InstDev* inst, int ninst, const float2* psi,
                              const double* f, float2* out_psi, float* out_rho, double* partials,
                              hipStream_t stream);
-// Sum the per-line partials of each instance in a fixed order -> results[3*i + c].
-hipError_t launch_finalize(const double* partials, int lines_per_inst, int ninst, double* results,
-                           hipStream_t stream);
+// Sum the partials of each instance in a fixed order -> results[3*i + c]: `lines` triples,
+// or `lines_y` of an instance that owes y; `stride` triples apart.
+hipError_t launch_finalize(const InstDev* inst, const double* partials, int lines, int lines_y, int stride, int ninst,
+                           double* results, hipStream_t stream);
 
 // Potential / state upload helpers (user row-major <-> internal layout).
 hipError_t launch_import_f(int ndim, int nx, int ny, const double* user, double* dst,

@@ -1,25 +1,24 @@
 // Resident 2-D QHD steps (gfx950): one workgroup owns an instance of at most 128 x 128
 // points for a whole evolve call.
 //
-// The product formula's step (App. C.2.1, eq. prod_qhd_fft; App. E.1, Algorithm 1 in its
-// symmetric form with midpoint coefficients) is the same as in the streaming passes:
-// a row phase F_x . V_{j-1}^{1/2} V_j^{1/2} . F_x^{-1} and a column phase
-// F_y^{-1} . K_j . F_y, with the state kept in (k_x, y) space between steps.  Here the
-// state stays in LDS across all the steps of the call: it is read from HBM once at
-// the start (8x8-tiled layout), every step runs out of LDS, and it is written back
-// once at the end, so a step moves no HBM bytes for psi (f, FP64, is re-read every
-// step and stays in L2 / the last-level cache).  Small instances, whose streaming
-// passes are bound by launch latency, run at the speed of one CU.
+// The steps are those of the alternating passes (qhd_kernels_axis.hip; App. C.2.1, eq.
+// prod_qhd_fft; App. E.1, Algorithm 1 in its symmetric form with midpoint coefficients): a
+// step takes one axis, the line operator owed from the step before, the merged potential
+// half steps and its own operator.  Here the state stays in LDS across all the steps of the
+// call: it is read from HBM once at the start (8x8-tiled layout), every step runs out of
+// LDS with one block barrier, and it is written back once at the end, so a step moves no
+// HBM bytes for psi (f, FP64, is re-read every step and stays in L2 / the last-level cache).
+// Small instances, whose streaming passes are bound by launch latency, run at the speed of
+// one CU.
 //
 // LDS layout: row-major, point (x, y) at y * RS + slot(x), slot(x) = x + x / 8 (one pad
 // entry per 8, as the line transforms' exchange buffers use), RS odd, so both a row
 // (contiguous, padded) and a column (stride RS) are exchanged in place: a line loads
 // its points into registers, and its own storage then serves as the exchange buffer
-// of its transforms.  Every arithmetic step (line transforms, twiddles, phases, the
-// FP64 kinetic factor and the FP64 ends of the column transforms) is the one of the
-// streaming passes with 8 points per lane, so both paths give the same values.  The
-// QAA model (App. E.2's baseline) runs the same two phases with FP64 Walsh-Hadamard
-// lines, which need no LDS exchange.
+// of its transforms.  The QAA model (App. E.2's baseline) runs the same steps with FP64
+// Walsh-Hadamard lines, which need no LDS exchange.  Lines of 32 and 64 points, and every
+// QAA line, give the values of the streaming passes bit for bit.
+#include "axis_line.h"
 #include "line_fft.h"
 #include "pass_common.h"
 #include "qhd_internal.h"
@@ -28,15 +27,16 @@ namespace qhd {
 
 template <int NX, int NY, int MODEL = kModelQHD>
 struct ResCfg {
-  static constexpr int P = 8;
-  static constexpr int TX = NX / P, TY = NY / P;               // lanes per row / column line
+  // 128-point lines take 16 points per lane (radices 16 and 8: one exchange per transform)
+  static constexpr int PX = NX >= 128 ? 16 : 8, PY = NY >= 128 ? 16 : 8;
+  static constexpr int TX = NX / PX, TY = NY / PY;             // lanes per row / column line
+  static constexpr int LANES = NX * NY / PX > NX * NY / PY ? NX * NY / PX : NX * NY / PY;
   // 1024 threads (four waves per SIMD) where the registers fit in 128 per lane
-  static constexpr int MAXT = ((NX == 128 && NY == 64) || (MODEL == kModelQAA && NX * NY == 16384)) ? 512 : 1024;
-  static constexpr int NT = (NX * NY / P) < MAXT ? (NX * NY / P) : MAXT;
+  static constexpr int MAXT = MODEL == kModelQAA && (PX == 16 || PY == 16) ? 512 : 1024;
+  static constexpr int NT = LANES < MAXT ? LANES : MAXT;
   static constexpr int RS = ((NX + NX / 8) | 1);               // row stride in slots (odd)
   static constexpr int ROWS_PER_IT = NT / TX, COLS_PER_IT = NT / TY;
   static_assert(NX >= 32 && NY >= 32 && NX <= 128 && NY <= 128, "resident sizes: 32..128 per axis");
-  static_assert(NY % ROWS_PER_IT == 0 && NX % COLS_PER_IT == 0, "whole line rounds");
 };
 
 template <int NX, int NY, int MODEL, bool Y4>
@@ -45,22 +45,27 @@ __global__ void __launch_bounds__((ResCfg<NX, NY, MODEL>::NT)) k_resident_2d(con
                                                                      const double* __restrict__ f,
                                                                      const double2* __restrict__ twx,
                                                                      const double2* __restrict__ twy,
-                                                                     long long max_steps) {
+                                                                     long long max_steps, int start_axis) {
   const int ninst = *nact_p;  // members active in this sub-step (device, set per chunk)
   using C = ResCfg<NX, NY, MODEL>;
-  constexpr int P = C::P, TX = C::TX, TY = C::TY, NT = C::NT, RS = C::RS;
+  constexpr int PX = C::PX, PY = C::PY, TX = C::TX, TY = C::TY, NT = C::NT, RS = C::RS;
+  constexpr int HX = etab_len<NX, MODEL>(), HY = etab_len<NY, MODEL>();
+  constexpr bool SHARE_TW = NX == NY;
   __shared__ float2 st[NY * RS];
-  __shared__ double2 twlx[TwLdsSize<NX, P>::value];
-  __shared__ double2 twly[NX == NY ? 1 : TwLdsSize<NY, P>::value];
-  __shared__ double2 eyl[NY];  // E_y(k_y) / (nx ny) of the current step
+  __shared__ double2 twlx[MODEL == kModelQAA ? 1 : TwLdsSize<NX, PX>::value];
+  __shared__ double2 twly[MODEL == kModelQAA || SHARE_TW ? 1 : TwLdsSize<NY, PY>::value];
+  // E(a_{j-1}) and E(a_j) of the axis of the current step; the other axis's are filled for
+  // the next step meanwhile
+  __shared__ double2 ex[2 * HX], ey[2 * HY];
   const int tid = threadIdx.x;
-  const int rl = tid / TX, rt = tid % TX;  // row phase: line of this lane group, lane in the line
-  const int cl = tid / TY, ct = tid % TY;  // column phase
-  TwiddlesFor<NX, P> tx;
-  load_twiddles(tx, twx, twlx, rt);
-  TwiddlesFor<NY, P> ty;
-  load_twiddles(ty, twy, NX == NY ? twlx : twly, ct);  // equal sizes share one table
-  const double inv_n = 1.0 / ((double)NX * (double)NY);
+  const int rl = tid / TX, rt = tid % TX;  // row step: line of this lane group, lane in the line
+  const int cl = tid / TY, ct = tid % TY;  // column step
+  TwiddlesFor<NX, PX> tx;
+  TwiddlesFor<NY, PY> ty;
+  if constexpr (MODEL != kModelQAA) {
+    load_twiddles(tx, twx, twlx, rt);
+    load_twiddles(ty, twy, SHARE_TW ? twlx : twly, ct);  // equal sizes share one table
+  }
   for (int i = blockIdx.x; i < ninst; i += gridDim.x) {
     const InstDev& I = inst[i];
     const long long lim = step_limit(I, max_steps);
@@ -75,92 +80,66 @@ __global__ void __launch_bounds__((ResCfg<NX, NY, MODEL>::NT)) k_resident_2d(con
       st[y * RS + lds_slot(x)] = make_float2(v.x, v.y);
       st[y * RS + lds_slot(x) + 1] = make_float2(v.z, v.w);
     }
+    if (start_axis == 0) fill_etab<NX, MODEL, Y4>(ex, inst, i, 1, 0, 0);
+    else fill_etab<NY, MODEL, Y4>(ey, inst, i, 1, 1, 0);
     __syncthreads();
     for (long long s = 0; s < lim; ++s) {
-      const long long j = I.steps_done + s;
-      const bool entry = (s == 0 && I.mode == kModeClean);
-      double a, b;
-      sched_ab<Y4>(I, j, a, b);
-      const double cx = a * I.kin_turns[0];
-      if (tid < NY) {
-        // read in the column phase, after the barrier that ends the row phase
-        double arg;
-        if constexpr (MODEL == kModelQAA) {
-          arg = a * axis_turns<MODEL>(I, 1, tid, NY);
-        } else {
-          const int nyf = freq(tid, NY);
-          arg = a * I.kin_turns[1] * (double)(nyf * nyf);
-        }
-        const double2 e = phase_turns_d(arg);
-        eyl[tid] = make_double2(e.x * inv_n, e.y * inv_n);
-      }
-      // row phase: [F_x^{-1}] . merged potential half steps . F_x
-      const double cpot = potential_turns<Y4>(I, j, entry);
+      if (((start_axis + s) & 1) == 0) {
+        const LineTask k = line_task<Y4>(I, s, max_steps, kModeOweX, 0);
+        fill_etab<NY, MODEL, Y4>(ey, inst, i, 1, 1, s + 1);  // read after the barrier
 #pragma unroll 1
-      for (int y = rl; y < NY; y += C::ROWS_PER_IT) {
-        float2* my = st + y * RS;
-        if constexpr (MODEL == kModelQAA) {
-          double2 reg[P];
+        for (int y = rl; y < NY; y += C::ROWS_PER_IT) {
+          float2* my = st + y * RS;
+          if constexpr (MODEL == kModelQAA) {
+            double2 reg[PX];
 #pragma unroll
-          for (int q = 0; q < P; ++q) assign(reg[q], my[lds_slot(rt + q * TX)]);
-          if (!entry) line_wht<NX, P>(reg, rt);
+            for (int q = 0; q < PX; ++q) assign(reg[q], my[lds_slot(rt + q * TX)]);
+            if (k.prev) line_field<NX, PX>(reg, rt, ex);
 #pragma unroll
-          for (int q = 0; q < P; ++q)
-            reg[q] = cmul_fd(reg[q], phase_turns_d(cpot * fg[tile_index(rt + q * TX, y, NX)]));
-          line_wht<NX, P>(reg, rt);
+            for (int q = 0; q < PX; ++q)
+              reg[q] = cmul_fd(reg[q], phase_turns_d(k.cpot * fg[tile_index(rt + q * TX, y, NX)]));
+            line_field<NX, PX>(reg, rt, ex + HX);
 #pragma unroll
-          for (int q = 0; q < P; ++q) assign(my[lds_slot(rt + q * TX)], reg[q]);
-        } else {
-          float2 reg[P];
+            for (int q = 0; q < PX; ++q) assign(my[lds_slot(rt + q * TX)], reg[q]);
+          } else {
+            float2 reg[PX];
 #pragma unroll
-          for (int q = 0; q < P; ++q) reg[q] = my[lds_slot(rt + q * TX)];
-          wave_lds_sync();
-          if (!entry) line_fft<NX, P, +1>(reg, rt, tx, my);
+            for (int q = 0; q < PX; ++q) reg[q] = my[lds_slot(rt + q * TX)];
+            wave_lds_sync();
+            line_pass<NX, PX, 0, false, SlotIx>(reg, rt, tx, my, ex, k.prev, k.cpot, 0,
+                                             [&](int q) { return fg[tile_index(rt + q * TX, y, NX)]; });
 #pragma unroll
-          for (int q = 0; q < P; ++q)
-            reg[q] = cmul_fd(reg[q], phase_turns_d(cpot * fg[tile_index(rt + q * TX, y, NX)]));
-          line_fft<NX, P, -1>(reg, rt, tx, my);
-#pragma unroll
-          for (int q = 0; q < P; ++q) my[lds_slot(rt + q * TX)] = reg[q];
+            for (int q = 0; q < PX; ++q) my[lds_slot(rt + q * TX)] = reg[q];
+          }
         }
-      }
-      __syncthreads();
-      // column phase: F_y . K . F_y^{-1} with K = E_x E_y / (nx ny) in FP64
+      } else {
+        const LineTask k = line_task<Y4>(I, s, max_steps, kModeOweY, 0);
+        fill_etab<NX, MODEL, Y4>(ex, inst, i, 1, 0, s + 1);
 #pragma unroll 1
-      for (int x = cl; x < NX; x += C::COLS_PER_IT) {
-        float2* my = st + lds_slot(x);
-        float2 reg[P];
+        for (int x = cl; x < NX; x += C::COLS_PER_IT) {
+          float2* my = st + lds_slot(x);
+          if constexpr (MODEL == kModelQAA) {
+            double2 reg[PY];
 #pragma unroll
-        for (int q = 0; q < P; ++q) reg[q] = my[(ct + q * TY) * RS];
-        double2 kd[P];
-        double xarg;
-        if constexpr (MODEL == kModelQAA) {
+            for (int q = 0; q < PY; ++q) assign(reg[q], my[(ct + q * TY) * RS]);
+            if (k.prev) line_field<NY, PY>(reg, ct, ey);
 #pragma unroll
-          for (int q = 0; q < P; ++q) assign(kd[q], reg[q]);
-          line_wht<NY, P>(kd, ct);
-          xarg = a * axis_turns<MODEL>(I, 0, x, NX);
-        } else {
-          wave_lds_sync();
-          line_fft_io<NY, P, -1, false, StrideIx<RS>>(reg, kd, ct, ty, my);
-          const int nxf = freq(x, NX);
-          xarg = cx * (double)(nxf * nxf);
+            for (int q = 0; q < PY; ++q)
+              reg[q] = cmul_fd(reg[q], phase_turns_d(k.cpot * fg[tile_index(x, ct + q * TY, NX)]));
+            line_field<NY, PY>(reg, ct, ey + HY);
+#pragma unroll
+            for (int q = 0; q < PY; ++q) assign(my[(ct + q * TY) * RS], reg[q]);
+          } else {
+            float2 reg[PY];
+#pragma unroll
+            for (int q = 0; q < PY; ++q) reg[q] = my[(ct + q * TY) * RS];
+            wave_lds_sync();
+            line_pass<NY, PY, 1, false, StrideIx<RS>>(reg, ct, ty, my, ey, k.prev, k.cpot, 0,
+                                                   [&](int q) { return fg[tile_index(x, ct + q * TY, NX)]; });
+#pragma unroll
+            for (int q = 0; q < PY; ++q) my[(ct + q * TY) * RS] = reg[q];
+          }
         }
-        const double2 ex = phase_turns_d(xarg);
-#pragma unroll
-        for (int q = 0; q < P; ++q) {
-          const double2 ey = eyl[ct + q * TY];
-          const double2 k = make_double2(fma(ex.x, ey.x, -ex.y * ey.y), fma(ex.x, ey.y, ex.y * ey.x));
-          kd[q] = cmul_fd(kd[q], k);
-        }
-        if constexpr (MODEL == kModelQAA) {
-          line_wht<NY, P>(kd, ct);
-#pragma unroll
-          for (int q = 0; q < P; ++q) assign(reg[q], kd[q]);
-        } else {
-          line_fft_io<NY, P, +1, false, StrideIx<RS>>(kd, reg, ct, ty, my);
-        }
-#pragma unroll
-        for (int q = 0; q < P; ++q) my[(ct + q * TY) * RS] = reg[q];
       }
       __syncthreads();
     }
@@ -183,7 +162,7 @@ bool resident_supported(int nx, int ny) {
 hipError_t launch_resident_2d(int nx, int ny, const InstDev* inst, int ninst, const int* nact, float2* psi,
                               const double* f,
                               const double2* tw_nx, const double2* tw_ny, long long max_steps, int model,
-                              bool y4, hipStream_t stream) {
+                              bool y4, int start_axis, hipStream_t stream) {
   if (ninst <= 0) return hipSuccess;
   if (!resident_supported(nx, ny)) return hipErrorInvalidValue;
 #define QHD_RES_LAUNCH(NX_, NY_)                                                                              \
@@ -191,13 +170,13 @@ hipError_t launch_resident_2d(int nx, int ny, const InstDev* inst, int ninst, co
     constexpr int NT_ = ResCfg<NX_, NY_>::NT, NTQ_ = ResCfg<NX_, NY_, kModelQAA>::NT;                         \
     if (model == kModelQAA)                                                                                   \
       QHD_LAUNCH((k_resident_2d<NX_, NY_, kModelQAA, false>), dim3(ninst), dim3(NTQ_), 0, stream,     \
-                         inst, nact, psi, f, tw_nx, tw_ny, max_steps);                                       \
+                         inst, nact, psi, f, tw_nx, tw_ny, max_steps, start_axis);                                       \
     else if (y4)                                                                                              \
       QHD_LAUNCH((k_resident_2d<NX_, NY_, kModelQHD, true>), dim3(ninst), dim3(NT_), 0, stream,       \
-                         inst, nact, psi, f, tw_nx, tw_ny, max_steps);                                       \
+                         inst, nact, psi, f, tw_nx, tw_ny, max_steps, start_axis);                                       \
     else                                                                                                      \
       QHD_LAUNCH((k_resident_2d<NX_, NY_, kModelQHD, false>), dim3(ninst), dim3(NT_), 0, stream,      \
-                         inst, nact, psi, f, tw_nx, tw_ny, max_steps);                                       \
+                         inst, nact, psi, f, tw_nx, tw_ny, max_steps, start_axis);                                       \
     return hipGetLastError();                                                                                 \
   }
   QHD_RES_LAUNCH(32, 32)

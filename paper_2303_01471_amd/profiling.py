@@ -99,6 +99,13 @@ def _model_suffix(m, i=2):
 
 
 _FAMILY = [
+    # the alternating 2-D passes: each axis reads and writes psi and reads f
+    (re.compile(r"k_row_axis_2d<(\d+), \d+, (\d+), (?:true|false)>"),
+     lambda m: f"row_pass_2d{_model_suffix(m)}/n{m.group(1)}", 24.0),
+    (re.compile(r"k_col_axis_(?:2d|tw)<(\d+), \d+, (\d+), (?:true|false)>"),
+     lambda m: f"col_pass_2d{_model_suffix(m)}/n{m.group(1)}", 24.0),
+    (re.compile(r"k_col_axis_split<(\d+),"), lambda m: f"col_pass_2d/n{m.group(1)}", 24.0),
+    # the passes of kept traces, both axes of a step in turn
     (re.compile(r"k_row_pass_2d<(\d+), \d+(?:, (\d+))?(?:, (?:true|false))?>"),
      lambda m: f"row_pass_2d{_model_suffix(m)}/n{m.group(1)}", 24.0),
     (re.compile(r"k_col_pass_(?:2d|tw)<(\d+), \d+(?:, (\d+))?(?:, (?:true|false))?>"),
