@@ -74,17 +74,14 @@ __device__ __forceinline__ void mul_field(double2 (&reg)[P], int t, const double
 // potential factor between them) or at the frequency-space ends (K: the last forward and the
 // first inverse stage and the kinetic factor).  Early in a run every line of a near-uniform
 // state concentrates into one coefficient and is rounded alike, late the state is localised;
-// FP32 rounding of such values moves the norm.  K for all lines but those of 128 points, where
-// the late phase decides: largest norm drift of the 128^2 members of the 768-instance batch
+// FP32 rounding of such values moves the norm.  K for all lines but those of 128 points and the
+// columns of 256, where the late phase decides: largest norm drift of the 128^2 members of the 768-instance batch
 // 1.3e-5 per 1e4 steps with K, 6.6e-6 with V.  (256^2: 9.3e-6 with neither, 5.1e-6 with K; with V
 // the near-uniform phase of 32^2 and 256^2 instances drifts up to 1.5 times as far in its first
 // 200 steps as with K.)  Either costs 2 % at 512 points, nothing that is seen below.
 template <int N, int AXIS>
 struct LinePrec {
-#ifndef QHD_VX
-#define QHD_VX (N == 128 || (N == 256 && AXIS == 1))
-#endif
-  static constexpr bool LATE = QHD_VX;
+  static constexpr bool LATE = N == 128 || (N == 256 && AXIS == 1);
   using V = typename std::conditional<LATE, double2, float2>::type;
   using K = typename std::conditional<LATE, float2, double2>::type;
 };

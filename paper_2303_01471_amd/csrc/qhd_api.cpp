@@ -353,13 +353,15 @@ qhd_status enqueue_chunk(qhd_plan p, long long ks, hipStream_t stream, bool timi
       HIP_TRY(launch_fix_mode(c.dev, m, phase == 0 ? kModeOweY : kModeOweX, st));
     }
     HIP_TRY(launch_chunk_plan(c.dev, m, ks, (int)S, c.nact, st));
-    if (c.resident) {
-      // every sub-step of the chunk in one launch, psi in LDS (timed as a whole: points =
-      // the chunk's grid-point stages)
+    if (c.resident || c.ndim == 1) {
+      // every sub-step of the chunk in one launch, psi in LDS or (1-D) registers (timed as a
+      // whole: points = the chunk's grid-point stages)
       double gps = 0.0;
       if (timing)
         for (int k = 0; k < m; ++k) gps += (double)host_limit(c.host[k], ks) * (double)c.points;
-      HIP_TRY(timed_on(st, c.fam_res, gps, [&] {
+      HIP_TRY(timed_on(st, c.ndim == 1 ? c.fam_line : c.fam_res, gps, [&] {
+        if (c.ndim == 1)
+          return launch_line_steps_1d(c.nx, c.dev, m, c.nact, c.psi, c.f, c.tw_x, ks, p->grid_cap, st);
         return launch_resident_2d(c.nx, c.ny, c.dev, m, c.nact, c.psi, c.f, c.tw_x, c.tw_y, ks, c.model, c.y4, phase, st);
       }));
     } else {
@@ -406,10 +408,6 @@ qhd_status enqueue_chunk(qhd_plan p, long long ks, hipStream_t stream, bool timi
               return launch_col_pass_2d(c.nx, c.ny, c.dev, m, na, c.psi, c.f, c.tw_y, s, ks, c.cap_col, c.col_variant,
                                         st, c.model, c.y4);
             }));
-        } else {
-          HIP_TRY(timed_on(st, c.fam_line, pts, [&] {
-            return launch_line_pass_1d(c.nx, c.dev, m, na, c.psi, c.f, c.tw_x, s, ks, p->grid_cap, st);
-          }));
         }
       }
     }
@@ -892,8 +890,9 @@ qhd_status qhd_plan_create(const qhd_instance* inst, int32_t batch, const qhd_pl
       snprintf(name, sizeof name, "col_pass_2d%s/n%d", tag, c.ny);
       c.fam_col = family_index(p, name, c.leapfrog ? 20.0 : 24.0);
     } else {
+      // psi and f cross HBM once per launch of up to 64 sub-steps
       snprintf(name, sizeof name, "line_pass_1d/n%d", c.nx);
-      c.fam_line = family_index(p, name, 24.0);
+      c.fam_line = family_index(p, name, 24.0 / kMaxSub);
     }
   }
   for (int i = 0; i < batch; ++i) p->state_ready[i] = inst[i].init_kind == QHD_INIT_UNIFORM;

@@ -117,9 +117,9 @@ hipError_t launch_col_pass_2d(int nx, int ny, const InstDev* inst, int ninst, co
                               bool fix = false);
 // after a `fix` launch on the axis owed in mode `owe`: those members become kModeKDone
 hipError_t launch_fix_mode(InstDev* inst, int ninst, int owe, hipStream_t stream);
-hipError_t launch_line_pass_1d(int n, const InstDev* inst, int ninst, const int* nact, float2* psi, const double* f,
-                               const double2* tw, int s, long long max_steps, int grid_cap,
-                               hipStream_t stream);
+// 1-D: every sub-step of the chunk in one launch
+hipError_t launch_line_steps_1d(int n, const InstDev* inst, int ninst, const int* nact, float2* psi, const double* f,
+                                const double2* tw, long long max_steps, int grid_cap, hipStream_t stream);
 // start_axis: the axis (0 = x, 1 = y) of the chunk's first sub-step in a class of
 // alternating passes, -1 for the others
 hipError_t launch_commit(InstDev* inst, int ninst, long long max_steps, int start_axis, hipStream_t stream);

@@ -179,57 +179,71 @@ __global__ void __launch_bounds__(256) k_lf_col_2d(const InstDev* __restrict__ i
 }
 
 // ------------------------------------------------------------------------------------
-// 1-D pass: V (merged halves) . F . K . F^{-1}, the state stays in position space
-// with the trailing half step of the last step pending.
+// 1-D steps: V (merged halves) . F . K . F^{-1}, the state in position space with the
+// trailing half step of the last step pending.  A line (TPL lanes of one wavefront) needs
+// nothing from another, so one launch runs every sub-step of the chunk with psi and f in
+// registers: a serial chain per line, bound by its latency (two transforms, their LDS
+// exchanges and the phases), so blocks of one wavefront spread the lines over the CUs and a
+// lane holds few points.  Us per step, one launch per step -> this kernel: one 8-point line
+// 3.4 -> 1.2, 256 points 5.3 -> 1.7, 1024 points 10.4 -> 4.7; 200 lines of 256 5.8 -> 1.7.
+
+// Points per lane: 4 while a line then fits one wavefront (256 points: 1.7 us a step, 2.6
+// with 8; 5000 lines of 256, where the chip is full: 6.0 and 5.7), 8 and 16 above.
+constexpr int line_step_points(int n) { return n <= 256 ? 4 : n / 64; }
 
 template <int N, int P>
-__global__ void __launch_bounds__(256) k_line_pass_1d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p,
+__global__ void __launch_bounds__(64) k_line_steps_1d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p,
                                                       float2* __restrict__ psi,
                                                       const double* __restrict__ f,
-                                                      const double2* __restrict__ twtab, int s,
-                                                      long long max_steps) {
-  const int ninst = *nact_p;  // members active in this sub-step (device, set per chunk)
+                                                      const double2* __restrict__ twtab, long long max_steps) {
+  const int ninst = *nact_p;  // members active in the chunk (device, set per chunk)
   constexpr int TPL = N / P;
-  constexpr int LPW = (256 / TPL) > 0 ? 256 / TPL : 1;
+  constexpr int LPW = 64 / TPL;
   constexpr int SLOTS = LineLds<N>::kSlots;
   __shared__ float2 lds[LPW * SLOTS];
   const int ll = threadIdx.x / TPL, t = threadIdx.x % TPL;
   float2* my = lds + ll * SLOTS;
   Twiddles<N, P> tw;
   tw.load(twtab, t);
+  constexpr double inv_n = 1.0 / (double)N;
   for (long long l0 = (long long)blockIdx.x * LPW; l0 < ninst; l0 += (long long)gridDim.x * LPW) {
     const long long L = l0 + ll;
-    const bool valid = L < ninst;
-    const int i = (int)(valid ? L : ninst - 1);
-    const InstDev& I = inst[i];
-    const bool active = valid && s < step_limit(I, max_steps);
-    const long long j = I.steps_done + s;
-    const bool entry = (s == 0 && I.mode == kModeClean);
-    double a, b;
-    sched_ab(I, j, a, b);
-    const double cpot = potential_turns(I, j, entry);
-    const double ck = a * I.kin_turns[0];
-    const double inv_n = 1.0 / (double)N;
-    const long long base = I.psi_off;
+    if (L >= ninst) continue;  // (the lanes of a line leave together; no block barrier below)
+    const InstDev& I = inst[(int)L];
+    const long long lim = step_limit(I, max_steps), base = I.psi_off;
     float2 reg[P];
+    double fv[P];
 #pragma unroll
     for (int q = 0; q < P; ++q) {
-      const long long p = base + t + q * TPL;
-      reg[q] = cmul_fd(psi[p], phase_turns_d(cpot * f[p]));
+      reg[q] = psi[base + t + q * TPL];
+      fv[q] = f[base + t + q * TPL];
     }
-    double2 kd[P];
-    line_fft_io<N, P, -1>(reg, kd, t, tw, my);
+    // b of the stage before, carried along (potential_turns evaluates the schedule twice)
+    double a, b, b_prev = 0.0;
+    const bool lie = I.scheme == kSchemeLie;
+    if (I.steps_done > 0 && lim > 0) sched_ab(I, I.steps_done - 1, a, b_prev);
+    for (long long s = 0; s < lim; ++s) {
+      const long long j = I.steps_done + s;
+      sched_ab(I, j, a, b);
+      double beta = 0.5 * I.dt * b;
+      if (!(s == 0 && I.mode == kModeClean) && j > 0) beta += 0.5 * I.dt * b_prev;
+      const double cpot = (lie ? I.dt * b : beta) * kInv2Pi;
+      b_prev = b;
+      const double ck = a * I.kin_turns[0];
 #pragma unroll
-    for (int q = 0; q < P; ++q) {
-      const int nf = freq(t + q * TPL, N);
-      const double2 w = phase_turns_d(ck * (double)(nf * nf));
-      kd[q] = cmul_fd(kd[q], make_double2(w.x * inv_n, w.y * inv_n));
-    }
-    line_fft_io<N, P, +1>(kd, reg, t, tw, my);
-    if (active) {
+      for (int q = 0; q < P; ++q) reg[q] = cmul_fd(reg[q], phase_turns_d(cpot * fv[q]));
+      double2 kd[P];
+      line_fft_io<N, P, -1>(reg, kd, t, tw, my);
 #pragma unroll
-      for (int q = 0; q < P; ++q) psi[base + t + q * TPL] = reg[q];
+      for (int q = 0; q < P; ++q) {
+        const int nf = freq(t + q * TPL, N);
+        const double2 w = phase_turns_d(ck * (double)(nf * nf));
+        kd[q] = cmul_fd(kd[q], make_double2(w.x * inv_n, w.y * inv_n));
+      }
+      line_fft_io<N, P, +1>(kd, reg, t, tw, my);
     }
+#pragma unroll
+    for (int q = 0; q < P; ++q) psi[base + t + q * TPL] = reg[q];
   }
 }
 
@@ -597,16 +611,12 @@ hipError_t launch_lf_col_2d(int nx, int ny, const InstDev* inst, int ninst, cons
   });
 }
 
-hipError_t launch_line_pass_1d(int n, const InstDev* inst, int ninst, const int* nact, float2* psi, const double* f,
-                               const double2* tw, int s, long long max_steps, int grid_cap,
-                               hipStream_t stream) {
+hipError_t launch_line_steps_1d(int n, const InstDev* inst, int ninst, const int* nact, float2* psi, const double* f,
+                                const double2* tw, long long max_steps, int grid_cap, hipStream_t stream) {
   QHD_SWITCH_N(n, {
-    constexpr int P_ = pts_per_lane<N_>();
-    constexpr int TPL_ = N_ / P_;
-    constexpr int LPW_ = (256 / TPL_) > 0 ? 256 / TPL_ : 1;
-    const int blocks = blocks_for(ninst, LPW_, grid_cap);
-    QHD_LAUNCH((k_line_pass_1d<N_, P_>), dim3(blocks), dim3(256), 0, stream, inst, nact,
-                       psi, f, tw, s, max_steps);
+    constexpr int P_ = line_step_points(N_);
+    const int blocks = blocks_for(ninst, 64 / (N_ / P_), grid_cap);
+    QHD_LAUNCH((k_line_steps_1d<N_, P_>), dim3(blocks), dim3(64), 0, stream, inst, nact, psi, f, tw, max_steps);
     return hipGetLastError();
   });
 }

@@ -113,7 +113,7 @@ _FAMILY = [
     (re.compile(r"k_col_pass_split<(\d+),"), lambda m: f"col_pass_2d/n{m.group(1)}", 16.0),
     (re.compile(r"k_lf_row_2d<(\d+), \d+>"), lambda m: f"row_pass_2d_qaa_lf/n{m.group(1)}", 20.0),
     (re.compile(r"k_lf_col_2d<(\d+), \d+>"), lambda m: f"col_pass_2d_qaa_lf/n{m.group(1)}", 20.0),
-    (re.compile(r"k_line_pass_1d<(\d+),"), lambda m: f"line_pass_1d/n{m.group(1)}", 24.0),
+    (re.compile(r"k_line_(?:pass|steps)_1d<(\d+),"), lambda m: f"line_pass_1d/n{m.group(1)}", 24.0),
     # 3-D: the x-pass (psi read and written, f read) and the (y, z)-plane pass
     (re.compile(r"k_xpass_3d<(\d+),"), lambda m: f"xpass_3d/n{m.group(1)}", 24.0),
     (re.compile(r"k_plane(?:_direct)?_3d<(\d+), (\d+),"), lambda m: f"plane_3d/n{m.group(1)}x{m.group(2)}", 16.0),
