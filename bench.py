@@ -170,22 +170,29 @@ def timed_runs(plan, steps, warmup, stream, label):
     return time.perf_counter() - t0, last[0], last[1]
 
 
-RQP_FUSED_POINTS = 6561  # the library's LDS run of the fused leading-axes pass
-
-
-def rqp_fused_axes(d, np_):
-    """Leading axes the library applies in one LDS pass: the largest K <= d with
-    np_^K <= RQP_FUSED_POINTS."""
-    k, chunk = 0, np_
-    while k < d and chunk <= RQP_FUSED_POINTS:
-        k, chunk = k + 1, chunk * np_
-    return k
+def rqp_sets(d, np_):
+    """Number of sets the library splits the axes into: leading axes whose lattice fits
+    min(1024 np_, 8192) points, then sets of trailing axes with 8 inner points each."""
+    most = min(1024 * np_, 8192)
+    lead = max(k for k in range(1, d + 1) if k == 1 or np_ ** k <= most)
+    trail = max(k for k in range(1, d + 1) if k == 1 or np_ ** k * 8 <= most)
+    return 1 + -(-(d - lead) // trail)
 
 
 def RQP_BYTES_PER_POINT_STEP(d, np_):
-    """HBM bytes per lattice point and step: the fused pass reads f once and reads and
-    writes the state (24 B), every other axis pass reads and writes it (16 B)."""
-    return 16.0 * (d - rqp_fused_axes(d, np_)) + 24.0
+    """HBM bytes per lattice point and step: with two sets one pass reads f and reads and
+    writes the state (24 B), every further set reads and writes it (16 B); with one set the
+    state stays on chip for a run of 64 steps."""
+    g = rqp_sets(d, np_)
+    return 24.0 + 16.0 * (g - 2) if g > 1 else 8.0 + 16.0 / 64
+
+
+def rqp_flops_per_point(d, np_):
+    """FP64 operations per point and step: a real-times-complex matrix per line, for an odd
+    number of points in an even and an odd half."""
+    h = np_ // 2
+    fma = 2 * ((h + 1) ** 2 + h * h) if np_ % 2 else 2 * np_ * np_
+    return d * (2.0 * fma + (8.0 * h if np_ % 2 else 0.0)) / np_
 
 
 FP64_PEAK_TFLOPS = 78.6
@@ -228,14 +235,13 @@ def rqp_summary(secs, res, points, probs, nsteps, r):
     rate = gp / secs
     bpp = RQP_BYTES_PER_POINT_STEP(d, np_)
     achieved = rate * bpp / 1e9
-    flops = 8.0 * np_ * d  # every axis: np_ complex multiply-adds per point in FP64
-    k = rqp_fused_axes(d, np_)
+    flops = rqp_flops_per_point(d, np_)
     hb = measured_traffic("rqp_step")  # HBM bytes per lattice point and step (counters)
     step_points = float(points) * len(probs)
     return {"gp_steps_per_s": round(rate, 1), "grid_point_steps": gp,
             "roofline": {"bound": "hbm",
-                         "kernel": f"relaxed-QP step (axes 1-{k} fused in one LDS pass, {d - k} more axis "
-                                   f"passes, r+1={np_})",
+                         "kernel": f"relaxed-QP step ({rqp_sets(d, np_)} sets of axes swept up and down, "
+                                   f"r+1={np_})",
                          "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": round(achieved / HBM_PEAK_GBS, 4),
                          "traffic": round(hb * step_points, 1) if hb is not None else None,

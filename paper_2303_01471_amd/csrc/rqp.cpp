@@ -1,9 +1,8 @@
 // Relaxed QHD for box-constrained QP: the C ABI of include/qhd_rqp.h.
 //
 // Host side: validation, the eigen-decomposition of the relaxed chain adjacency A'
-// (FP64 cyclic Jacobi, once per handle), the schedule per step, and the launch
-// sequence of one symmetric step (d axis passes, the merged potential half steps
-// fused into the first).  Kernels in rqp_kernels.hip.
+// (FP64 cyclic Jacobi, once per handle), the split of the axes into sets, the schedule per
+// step, and the launch sequence of the symmetric steps.  Kernels in rqp_kernels.hip.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -33,7 +32,9 @@ struct qhd_rqp_s {
   double* Qb = nullptr;     // per instance [Q (d x d), b (d)]
   double* U = nullptr;      // eigenvectors of A' (columns), row-major NP x NP
   double* lam = nullptr;    // eigenvalues of A'
-  double2* M = nullptr;     // kinetic factor of one axis for the current step (NP x NP)
+  double* tab = nullptr;    // per step of a run: axis matrix and potential coefficient
+  float2* closed = nullptr; // readouts: the state with the owed set applied, `group` instances
+  double* part = nullptr;   // readouts: per-block sums and marginals
   double* amp = nullptr;    // discrete Gaussian amplitudes of one axis
   double* fmin = nullptr;
   long long* amin = nullptr;
@@ -44,7 +45,13 @@ struct qhd_rqp_s {
   std::vector<char> has_obj;
   long long steps_done = 0;
   bool pending = false;     // the trailing potential half step of the last step is owed
-  int fused_axes = 0;       // axes 1..K run as one LDS pass (0: every axis its own pass)
+  // The axes in sets, swept up and down in turn.  With several sets the last set of the last
+  // step is owed after a call (its matrix and the next step's are one pass); -1: nothing is.
+  std::vector<RqpSet> sets;
+  RqpSteps steps{};         // host copy of the run being formed
+  bool unfused = false;     // each axis of a set in passes of its own, the same values
+  int owed = -1;
+  int group = 0;
 };
 
 namespace {
@@ -141,14 +148,105 @@ void schedule(const qhd_rqp_s* h, long long j, double& a, double& b) {
   }
 }
 
+// theta and potential coefficient of steps j0 .. j0 + count - 1 (the first entry is only the
+// step before; with `before` false step j0 + 1 has no half step to merge with)
+void step_table(qhd_rqp h, long long j0, int count, bool before) {
+  const qhd_rqp_desc& d = h->desc;
+  const double r2 = (double)d.r * (double)d.r;
+  double prev = 0.0;
+  for (int q = 0; q < count; ++q) {
+    double a = 0.0, b = 0.0;
+    if (q > 0 || before) schedule(h, j0 + q, a, b);
+    // merged potential half steps: the trailing half of the step before and the leading half
+    const double beta = 0.5 * d.dt * b + (q > 1 || before ? 0.5 * d.dt * prev : 0.0);
+    h->steps.theta[q] = 0.5 * d.dt * a * r2;
+    h->steps.beta_turns[q] = beta * 0.15915494309189533577;
+    prev = b;
+  }
+}
+
 void release(qhd_rqp h) {
   if (!h) return;
   (void)hipSetDevice(h->device);
-  for (void* p : {(void*)h->psi, (void*)h->f, (void*)h->Qb, (void*)h->U, (void*)h->lam, (void*)h->M, (void*)h->amp,
-                  (void*)h->fmin, (void*)h->amin, (void*)h->sums})
+  for (void* p : {(void*)h->psi, (void*)h->f, (void*)h->Qb, (void*)h->U, (void*)h->lam, (void*)h->tab, (void*)h->amp,
+                  (void*)h->fmin, (void*)h->amin, (void*)h->sums, (void*)h->closed, (void*)h->part})
     if (p) (void)hipFree(p);
   if (h->host_sums) (void)hipHostFree(h->host_sums);
   delete h;
+}
+
+constexpr int kNarrow = 8;                       // inner points of a trailing tile at least (64 B)
+constexpr long long kClosedBytes = 256ll << 20;  // readout copy (or one instance, if that is larger)
+
+long long ipow(int b, int e) {
+  long long v = 1;
+  for (int k = 0; k < e; ++k) v *= b;
+  return v;
+}
+
+// Tiles of axes first + 1 .. first + count.  256 threads and their 256 lines where the set's
+// lattice fits (9^5: 729 leading points, 81 trailing rows by 27), else 1024.  Fewer whole
+// chunks or inner points per tile while that leaves the chip short of blocks.
+RqpSet make_set(int NP, int first, int count, long long total) {
+  RqpSet S{};
+  S.first = first;
+  S.count = count;
+  S.n = (int)ipow(NP, count);
+  S.s0 = (int)ipow(NP, first);
+  const int narrow = first == 0 ? 1 : std::min(kNarrow, S.s0);
+  S.threads = (long long)S.n * narrow <= 256 * NP ? 256 : 1024;
+  const int most = std::min(S.threads * NP, kRqpTilePoints) / S.n;  // chunks or inner points
+  const long long chunks = total / S.n;
+  int span = (int)std::max<long long>(std::min<long long>(most, chunks / 1024), std::min(narrow, most));
+  if (first == 0) {
+    S.span = span * S.n;
+  } else {
+    span = std::min(span, S.s0);
+    S.inner_tiles = (S.s0 + span - 1) / span;
+    S.span = (S.s0 + S.inner_tiles - 1) / S.inner_tiles;
+  }
+  auto magic = [](long long s) { return (unsigned)((((1ull << 32) + s - 1) / s) & 0xffffffffull); };
+  S.magic_span = magic(S.span);
+  long long s = first == 0 ? 1 : S.span;
+  for (int k = 0; k < count; ++k, s *= NP) S.magic[k] = magic(s);
+  return S;
+}
+
+// The fewest sets whose tiles fit, and among those the most even split: the passes then
+// share the matrix work (9^5 as 3 + 2 axes).
+std::vector<RqpSet> make_sets(int NP, int d, long long total) {
+  const long long most = std::min(1024ll * NP, (long long)kRqpTilePoints);
+  int lead = 1, trail = 0;
+  while (lead < d && ipow(NP, lead + 1) <= most) ++lead;
+  while (trail < d && ipow(NP, trail + 1) * kNarrow <= most) ++trail;
+  const int ntrail = (d - lead + trail - 1) / trail;
+  int first = std::min(lead, (d + ntrail) / (ntrail + 1));
+  while (d - first > ntrail * trail) ++first;
+  std::vector<RqpSet> sets{make_set(NP, 0, ntrail ? first : d, total)};
+  for (int k = 0, at = first; k < ntrail; ++k) {
+    const int c = (d - at + ntrail - k - 1) / (ntrail - k);
+    sets.push_back(make_set(NP, at, c, total));
+    at += c;
+  }
+  return sets;
+}
+
+// One pass of set i: mat0 (or NULL), then `rounds` steps from mat1 on.
+hipError_t set_pass(qhd_rqp h, int i, const float2* src, float2* dst, const double* f, long long total,
+                    const double* mat0, const double* mat1, int rounds, hipStream_t st) {
+  const RqpSet& S = h->sets[i];  // (total: whole instances)
+  if (!h->unfused) return rqp_pass(h->NP, src, dst, f, S, total, mat0, mat1, rounds, st);
+  // the reference form of the same arithmetic: one pass per axis and matrix
+  hipError_t e = hipSuccess;
+  for (int rd = mat0 ? -1 : 0; rd < rounds; ++rd)
+    for (int k = 0; k < S.count && e == hipSuccess; ++k) {
+      const double* m = rd < 0 ? mat0 : mat1 + (long long)rd * kRqpMatStride;
+      const RqpSet axis = make_set(h->NP, S.first + k, 1, total);
+      const bool pot = rd >= 0 && k == 0;  // the potential factor comes before the first axis
+      e = rqp_pass(h->NP, src, dst, f, axis, total, pot ? nullptr : m, m, pot ? 1 : 0, st);
+      src = dst;
+    }
+  return e;
 }
 
 qhd_status validate(const qhd_rqp_desc* d, int batch) {
@@ -203,13 +301,9 @@ qhd_status qhd_rqp_create(const qhd_rqp_desc* desc, int32_t batch, qhd_rqp* out)
   h->NP = desc->r + 1;
   h->N = 1;
   for (int k = 0; k < desc->dim; ++k) h->N *= h->NP;
-  // the most leading axes whose chunk fits the fused pass's LDS run (QHD_RQP_UNFUSED=1:
-  // one pass per axis, the reference form of the same arithmetic)
-  const char* unfused = std::getenv("QHD_RQP_UNFUSED");
-  if (!(unfused && std::strcmp(unfused, "1") == 0)) {
-    long long chunk = h->NP;
-    for (int k = 1; k <= desc->dim && chunk <= kFusedPoints; ++k, chunk *= h->NP) h->fused_axes = k;
-  }
+  const char* unfused = std::getenv("QHD_RQP_UNFUSED");  // 1: one pass per axis and matrix
+  h->unfused = unfused && std::strcmp(unfused, "1") == 0;
+  h->sets = make_sets(h->NP, desc->dim, h->N * batch);
   h->fmin_h.assign(batch, 0.0);
   h->amin_h.assign(batch, 0);
   h->has_obj.assign(batch, 0);
@@ -221,7 +315,18 @@ qhd_status qhd_rqp_create(const qhd_rqp_desc* desc, int32_t batch, qhd_rqp* out)
   if (e == hipSuccess) e = hipMalloc(&h->Qb, sizeof(double) * (size_t)batch * (d * d + d));
   if (e == hipSuccess) e = hipMalloc(&h->U, sizeof(double) * NP * NP);
   if (e == hipSuccess) e = hipMalloc(&h->lam, sizeof(double) * NP);
-  if (e == hipSuccess) e = hipMalloc(&h->M, sizeof(double2) * NP * NP);
+  if (e == hipSuccess) e = hipMalloc(&h->tab, sizeof(double) * kRqpStepRun * kRqpMatStride);
+  if (h->sets.size() > 1) {
+    h->group = (int)std::max<long long>(1, std::min<long long>(batch, kClosedBytes / (long long)(sizeof(float2) * h->N)));
+    if (e == hipSuccess) e = hipMalloc(&h->closed, sizeof(float2) * h->N * h->group);
+  }
+  const int most_group = h->group ? h->group : batch;
+  const int tail_group = batch % most_group;
+  size_t parts = 0;  // (a smaller last group takes more blocks per instance)
+  for (int n : {batch, most_group, tail_group})
+    if (n && rqp_observe_blocks(h->N, n) > 1)
+      parts = std::max(parts, (size_t)n * rqp_observe_blocks(h->N, n) * std::max(3, d * NP));
+  if (e == hipSuccess && parts) e = hipMalloc(&h->part, sizeof(double) * parts);
   if (e == hipSuccess) e = hipMalloc(&h->amp, sizeof(double) * NP);
   if (e == hipSuccess) e = hipMalloc(&h->fmin, sizeof(double) * batch);
   if (e == hipSuccess) e = hipMalloc(&h->amin, sizeof(long long) * batch);
@@ -289,31 +394,37 @@ qhd_status qhd_rqp_evolve(qhd_rqp h, int64_t max_steps, void* stream_v) {
   const long long rem = d.nsteps - h->steps_done;
   const long long n = (max_steps < 0 || max_steps > rem) ? rem : max_steps;
   const long long total = h->N * h->batch;
-  const double r2 = (double)d.r * (double)d.r;
-  for (long long s = 0; s < n; ++s) {
-    const long long j = h->steps_done + s;
-    double a, b;
-    schedule(h, j, a, b);
-    // merged potential half steps: the trailing half of step j-1 and the leading half of j
-    double beta = 0.5 * d.dt * b;
-    if (h->pending || s > 0) {
-      double ap, bp;
-      schedule(h, j - 1, ap, bp);
-      beta += 0.5 * d.dt * bp;
+  // A replay of a captured call starts where the last one ended: a call of an odd number of
+  // steps then ends on the set it began with, its last step's sets not merged with the next.
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  RQP_TRY(hipStreamIsCapturing(st, &cap));
+  const int last = (int)h->sets.size() - 1;
+  for (long long s0 = 0; s0 < n; s0 += kRqpStepRun - 1) {
+    const int run = (int)std::min<long long>(n - s0, kRqpStepRun - 1);
+    // entry q of the table: step j0 - 1 + q
+    const long long j0 = h->steps_done + s0;
+    const bool before = h->pending || s0 > 0;
+    step_table(h, j0 - 1, run + 1, before);
+    RQP_TRY(rqp_matrices(h->NP, h->U, h->lam, h->steps, run + 1, h->tab, st));
+    if (last == 0) {
+      // one set holds every axis: the run's steps in one pass
+      RQP_TRY(set_pass(h, 0, h->psi, h->psi, h->f, total, nullptr, h->tab + kRqpMatStride, run, st));
+      continue;
     }
-    const double theta = 0.5 * d.dt * a * r2;
-    long long stride = 1;
-    int k = 0;
-    RQP_TRY(rqp_matrix(h->NP, h->U, h->lam, theta, h->M, st));
-    if (h->fused_axes > 0) {
-      // axes 1..K in one pass through LDS, the rest one pass each
-      RQP_TRY(rqp_fused_pass(h->NP, h->psi, h->f, total, h->fused_axes, h->M, beta * 0.15915494309189533577, st));
-      for (; k < h->fused_axes; ++k) stride *= h->NP;
-    }
-    for (; k < d.dim; ++k) {
-      RQP_TRY(rqp_axis_pass(h->NP, h->psi, h->f, total, (int)stride, h->M, k == 0, beta * 0.15915494309189533577,
-                            st));
-      stride *= h->NP;
+    for (int s = 0; s < run; ++s) {
+      const double* now = h->tab + (long long)(s + 1) * kRqpMatStride;
+      const bool keep = cap != hipStreamCaptureStatusNone && (n & 1) && s0 + s == n - 1 && h->owed >= 0;
+      int from = h->owed < 0 ? 0 : h->owed;
+      if (keep) {
+        RQP_TRY(set_pass(h, from, h->psi, h->psi, h->f, total, now - kRqpMatStride, nullptr, 0, st));
+        from = last - from;
+      }
+      RQP_TRY(set_pass(h, from, h->psi, h->psi, h->f, total, keep || h->owed < 0 ? nullptr : now - kRqpMatStride, now, 1,
+                       st));
+      const int dir = from == 0 ? 1 : -1;
+      for (int k = from + dir; k > 0 && k < last; k += dir)
+        RQP_TRY(set_pass(h, k, h->psi, h->psi, h->f, total, now, nullptr, 0, st));
+      h->owed = last - from;
     }
   }
   if (n > 0) {
@@ -337,9 +448,27 @@ qhd_status qhd_rqp_observe(qhd_rqp h, void* stream_v, qhd_rqp_obs* out, float* m
     schedule(h, h->steps_done - 1, a, b);
     close_turns = 0.5 * h->desc.dt * b * 0.15915494309189533577;
   }
-  RQP_TRY(rqp_observe(h->psi, h->f, h->N, h->batch, h->fmin, h->desc.min_tol, h->sums, prob_dev,
-                      reinterpret_cast<float2*>(psi_dev), close_turns, st));
-  if (marginals_dev) RQP_TRY(rqp_marginals(h->NP, h->psi, h->N, h->desc.dim, h->batch, marginals_dev, st));
+  const int d = h->desc.dim, NP = h->NP;
+  // the owed set is applied on a copy, a group of instances at a time
+  if (h->owed >= 0) {
+    step_table(h, h->steps_done - 1, 1, true);
+    RQP_TRY(rqp_matrices(NP, h->U, h->lam, h->steps, 1, h->tab, st));
+  }
+  const int group = h->owed >= 0 ? h->group : h->batch;
+  for (int i = 0; i < h->batch; i += group) {
+    const int count = std::min(group, h->batch - i);
+    const size_t at = (size_t)i * h->N;
+    const float2* z = h->psi + at;
+    if (h->owed >= 0) {
+      RQP_TRY(set_pass(h, h->owed, z, h->closed, h->f + at, h->N * count, h->tab, nullptr, 0, st));
+      z = h->closed;
+    }
+    RQP_TRY(rqp_observe(z, h->f + at, h->N, count, h->fmin + i, h->desc.min_tol, h->part, h->sums + 3 * (size_t)i,
+                        prob_dev ? prob_dev + at : nullptr, psi_dev ? reinterpret_cast<float2*>(psi_dev) + at : nullptr,
+                        close_turns, st));
+    if (marginals_dev)
+      RQP_TRY(rqp_marginals(NP, z, h->N, d, count, h->part, marginals_dev + (size_t)i * d * NP, st));
+  }
   RQP_TRY(hipMemcpyAsync(h->host_sums, h->sums, sizeof(double) * 3 * h->batch, hipMemcpyDeviceToHost, st));
   RQP_TRY(hipStreamSynchronize(st));
   qhd_status status = QHD_OK;
@@ -366,6 +495,7 @@ qhd_status qhd_rqp_reset(qhd_rqp h, void* stream_v) {
   RQP_TRY(rqp_init(h->psi, h->amp, h->desc.dim, h->NP, h->N, h->batch, (hipStream_t)stream_v));
   h->steps_done = 0;
   h->pending = false;
+  h->owed = -1;
   return QHD_OK;
 }
 

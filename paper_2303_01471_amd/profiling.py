@@ -124,7 +124,7 @@ _FAMILY = [
 ]
 
 # relaxed-QP kernels of one step (psi read and written per axis pass, f read once)
-_RQP_STEP = re.compile(r"k_rqp_(?:fused|axis_staged|axis_direct)\b")
+_RQP_STEP = re.compile(r"k_rqp_(?:fused|axis_staged|axis_direct|pass)\b")
 
 
 def family_of(kernel: str):
@@ -171,11 +171,11 @@ def traffic(fetch_db: str, write_db: str, copy_bytes: float, points_per_dispatch
                                     "write_bytes_per_point": write / pts,
                                     "hbm_bytes_per_point": (fetch + write) / pts,
                                     "algorithmic_bytes_per_point": bpp}
-    # relaxed QP: all step kernels together (one fused pass per step, then one pass per
-    # remaining axis), bytes per lattice point and step
+    # relaxed QP: all step kernels together, bytes per lattice point and step (one k_rqp_pass
+    # per step with two sets of axes; k_rqp_fused, one per step, in older traces)
     rq = sorted(k for k in fe if _RQP_STEP.search(k))
     pts = points_per_dispatch.get("rqp_step")
-    steps = sum(nfe[k] for k in rq if "fused" in k)
+    steps = sum(nfe[k] for k in rq if "fused" in k or "k_rqp_pass" in k)
     if rq and pts and steps:
         fetch = sum(fe[k]["FETCH_SIZE"] * nfe[k] for k in rq) * 1024.0 * f_scale
         write = sum(wr.get(k, {}).get("WRITE_SIZE", 0.0) * nwr.get(k, 0) for k in rq) * 1024.0 * w_scale
