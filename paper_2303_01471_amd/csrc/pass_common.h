@@ -141,6 +141,13 @@ __device__ __forceinline__ long long step_limit(const InstDev& I, long long max_
   return (max_steps < 0 || cap > rem) ? rem : cap;
 }
 
+// The last kick of a step and the first one of the next are the same -dt/2 H(t_{n+1}) R added
+// to I: with both in one call the last kick adds it twice, rounded in between as by two
+// stages, and the first kick's stage is not launched (two stages a step instead of three).
+__device__ __forceinline__ bool lf_joins_next(const InstDev& I, int s, long long max_steps) {
+  return s % 3 == 2 && s + 1 < step_limit(I, max_steps);  // (a call starts on a whole step)
+}
+
 
 // offset of slot q of lane t on tiled row y (x = t + q*TPL); compile-time stride
 // between slots once a slot spans whole tiles

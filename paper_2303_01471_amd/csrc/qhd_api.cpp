@@ -391,6 +391,7 @@ qhd_status enqueue_chunk(qhd_plan p, long long ks, hipStream_t stream, bool timi
                                    st);
           }));
         } else if (c.ndim == 2 && c.leapfrog) {
+          if (s > 0 && s % 3 == 0) continue;  // joined to the kick before it (lf_joins_next)
           HIP_TRY(timed_on(st, c.fam_row, pts, [&] {
             return launch_lf_row_2d(c.nx, c.ny, c.dev, m, na, c.psi, c.f, c.scratch, s, ks, c.cap_row, st);
           }));
