@@ -208,21 +208,21 @@ int pass_blocks_col_2d(int nx, int ny, int ninst, int grid_cap, int variant);
 
 // spectrum kernels (qhd_spectrum_kernels.hip); v is a plain row-major (x fastest)
 // complex64 vector of one nx x ny instance
-hipError_t spec_lines(int axis, int sign, float2* v, int nx, int ny, const double2* tw, hipStream_t st);
-hipError_t spec_kinetic(float2* v, int nx, int ny, double cx, double cy, double s, hipStream_t st);
-hipError_t spec_finish(float2* out, const float2* w, const float2* v, const double* f, double b, int nx, int ny,
-                       hipStream_t st);
-hipError_t spec_multidot(const float2* V, long long n, int count, const float2* w, double* partials, int nblk,
+// out = H in: a F^{-1} diag(|k|^2 / 2) F in + b f in (cx, cy: the factors of n_x^2, n_y^2, a
+// included); scratch holds one vector, in and out are distinct
+hipError_t spec_matvec(const float2* in, float2* scratch, float2* out, int nx, int ny, const double2* tw_x,
+                       const double2* tw_y, double cx, double cy, const double* f, double b, hipStream_t st);
+constexpr int kSpecDotBlocks = 16;  // blocks per vector of a multidot (partials summed in order)
+hipError_t spec_multidot(const float2* V, long long n, int count, const float2* w, double* partials,
                          hipStream_t st);
-// (with `part`, groups x n FP64 pairs of scratch, long bases take the grouped two-kernel
-// form; scale_dev: the scale read from device memory)
-hipError_t spec_multiaxpy(float2* w, const float2* V, long long n, int count, const double* c, double scale,
-                          hipStream_t st, const double* scale_dev = nullptr, double2* part = nullptr,
-                          int groups = 1);
-// device-side reductions of the multidot partials (block order, FP64): coefficients
-// (optionally keeping the newest one), and a vector's norm with its reciprocal
-hipError_t spec_coef(const double* partials, int count, int nblk, double* coef, double* keep, hipStream_t st);
-hipError_t spec_norm(const double* partials, int nblk, double* keep, double* scale, hipStream_t st);
+// w <- scale (w - sum_i c_i V_i).  c: the coefficients in device memory, or (partials) what
+// spec_multidot wrote, summed in block order; keep (or NULL) gets the
+// real part of the last coefficient.  Long bases take the grouped two-kernel form (part:
+// groups x n FP64 pairs of scratch).
+hipError_t spec_multiaxpy(float2* w, const float2* V, long long n, int count, const double* c, bool partials, double scale,
+                          hipStream_t st, double2* part, int groups, double* keep = nullptr);
+// w <- w / |w| from the partials of <w, w>; keep[0] = |w|
+hipError_t spec_normalise(float2* w, long long n, const double* partials, double* keep, hipStream_t st);
 hipError_t spec_random(float2* v, long long n, unsigned long long seed, hipStream_t st);
 
 }  // namespace qhd

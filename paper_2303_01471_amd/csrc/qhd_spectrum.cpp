@@ -46,7 +46,6 @@ qhd_status sfail(qhd_status st, const char* fmt, ...) {
   } while (0)
 
 constexpr int kMaxKrylov = 400;
-constexpr int kDotBlocks = 16;  // blocks per vector of a multidot (partials summed in order)
 constexpr int kAxpyGroups = 8;  // groups of the grouped multiaxpy
 
 // a(t), b(t) of the instance's schedule at time t
@@ -189,7 +188,7 @@ struct Work {
   float2* r = nullptr;   // residual
   double* partials = nullptr;
   double* coef = nullptr;
-  double* hist = nullptr;  // Lanczos diagonal and off-diagonal entries, norm and scale
+  double* hist = nullptr;  // Lanczos diagonal and off-diagonal entries, norm of the start vector
   double2* part = nullptr;  // grouped multiaxpy sums
   ~Work() {
     (void)hipFree(hist);
@@ -215,27 +214,21 @@ struct Ctx {
   qhd_status matvec(const float2* in, float2* out) {
     const double L0 = v.length[0], L1 = v.length[1];
     const double cx = 0.5 * std::pow(2.0 * M_PI / L0, 2) * a, cy = 0.5 * std::pow(2.0 * M_PI / L1, 2) * a;
-    SP_TRY(hipMemcpyAsync(w.u, in, sizeof(float2) * n, hipMemcpyDeviceToDevice, st));
-    SP_TRY(spec_lines(0, -1, w.u, v.nx, v.ny, v.tw_x, st));
-    SP_TRY(spec_lines(1, -1, w.u, v.nx, v.ny, v.tw_y, st));
-    SP_TRY(spec_kinetic(w.u, v.nx, v.ny, cx, cy, 1.0 / (double)n, st));
-    SP_TRY(spec_lines(1, +1, w.u, v.nx, v.ny, v.tw_y, st));
-    SP_TRY(spec_lines(0, +1, w.u, v.nx, v.ny, v.tw_x, st));
-    SP_TRY(spec_finish(out, w.u, in, v.f, b, v.nx, v.ny, st));
+    SP_TRY(spec_matvec(in, w.u, out, v.nx, v.ny, v.tw_x, v.tw_y, cx, cy, v.f, b, st));
     return QHD_OK;
   }
 
   // c[i] = <V_i, y> for i < count (complex, FP64), synchronous
   qhd_status dots(const float2* Vb, int count, const float2* y, std::vector<double>& c) {
-    SP_TRY(spec_multidot(Vb, n, count, y, w.partials, kDotBlocks, st));
-    hp.resize((size_t)count * kDotBlocks * 2);
+    SP_TRY(spec_multidot(Vb, n, count, y, w.partials, st));
+    hp.resize((size_t)count * kSpecDotBlocks * 2);
     SP_TRY(hipMemcpyAsync(hp.data(), w.partials, sizeof(double) * hp.size(), hipMemcpyDeviceToHost, st));
     SP_TRY(hipStreamSynchronize(st));
     c.assign((size_t)2 * count, 0.0);
     for (int i = 0; i < count; ++i)
-      for (int k = 0; k < kDotBlocks; ++k) {
-        c[2 * i] += hp[((size_t)i * kDotBlocks + k) * 2];
-        c[2 * i + 1] += hp[((size_t)i * kDotBlocks + k) * 2 + 1];
+      for (int k = 0; k < kSpecDotBlocks; ++k) {
+        c[2 * i] += hp[((size_t)i * kSpecDotBlocks + k) * 2];
+        c[2 * i + 1] += hp[((size_t)i * kSpecDotBlocks + k) * 2 + 1];
       }
     return QHD_OK;
   }
@@ -247,7 +240,7 @@ struct Ctx {
       SP_TRY(hipMemcpyAsync(w.coef, c.data(), sizeof(double) * 2 * count, hipMemcpyHostToDevice, st));
       SP_TRY(hipStreamSynchronize(st));
     }
-    SP_TRY(spec_multiaxpy(y, Vb, n, count, w.coef, scale, st, nullptr, w.part, kAxpyGroups));
+    SP_TRY(spec_multiaxpy(y, Vb, n, count, w.coef, false, scale, st, w.part, kAxpyGroups));
     return QHD_OK;
   }
 
@@ -291,9 +284,9 @@ extern "C" qhd_status qhd_spectrum(qhd_plan plan, int32_t i, double t, int32_t n
   SP_TRY(hipMalloc(&c.w.u, sizeof(float2) * n));
   SP_TRY(hipMalloc(&c.w.x, sizeof(float2) * n));
   SP_TRY(hipMalloc(&c.w.r, sizeof(float2) * n));
-  SP_TRY(hipMalloc(&c.w.partials, sizeof(double) * 2 * kDotBlocks * (m + 1)));
+  SP_TRY(hipMalloc(&c.w.partials, sizeof(double) * 2 * kSpecDotBlocks * (m + 1)));
   SP_TRY(hipMalloc(&c.w.coef, sizeof(double) * 2 * (m + 1)));
-  SP_TRY(hipMalloc(&c.w.hist, sizeof(double) * (2 * m + 2)));
+  SP_TRY(hipMalloc(&c.w.hist, sizeof(double) * (2 * m + 1)));
   SP_TRY(hipMalloc(&c.w.part, sizeof(double2) * n * kAxpyGroups));
   float2* V = c.w.V;
   std::vector<double> alpha, beta, co;
@@ -307,23 +300,20 @@ extern "C" qhd_status qhd_spectrum(qhd_plan plan, int32_t i, double t, int32_t n
   double* d_alpha = c.w.hist;
   double* d_beta = c.w.hist + m;
   double* d_nrm = c.w.hist + 2 * m;
-  double* d_scale = c.w.hist + 2 * m + 1;
   // deterministic start vector, normalised
   SP_TRY(spec_random(V, n, 0x51ED5EEDull + (unsigned long long)i, st));
-  SP_TRY(spec_multidot(V, n, 1, V, c.w.partials, kDotBlocks, st));
-  SP_TRY(spec_norm(c.w.partials, kDotBlocks, d_nrm, d_scale, st));
-  SP_TRY(spec_multiaxpy(V, V, n, 0, c.w.coef, 0.0, st, d_scale));
+  SP_TRY(spec_multidot(V, n, 1, V, c.w.partials, st));
+  SP_TRY(spec_normalise(V, n, c.w.partials, d_nrm, st));
   for (int j = 0; j < m; ++j) {
     float2* w = V + (long long)(j + 1) * n;
     if ((s = c.matvec(V + (long long)j * n, w)) != QHD_OK) return s;
     for (int pass = 0; pass < 2; ++pass) {  // classical Gram-Schmidt, twice
-      SP_TRY(spec_multidot(V, n, j + 1, w, c.w.partials, kDotBlocks, st));
-      SP_TRY(spec_coef(c.w.partials, j + 1, kDotBlocks, c.w.coef, pass == 0 ? d_alpha + j : nullptr, st));
-      SP_TRY(spec_multiaxpy(w, V, n, j + 1, c.w.coef, 1.0, st, nullptr, c.w.part, kAxpyGroups));
+      SP_TRY(spec_multidot(V, n, j + 1, w, c.w.partials, st));
+      SP_TRY(spec_multiaxpy(w, V, n, j + 1, c.w.partials, true, 1.0, st, c.w.part, kAxpyGroups,
+                            pass == 0 ? d_alpha + j : nullptr));
     }
-    SP_TRY(spec_multidot(w, n, 1, w, c.w.partials, kDotBlocks, st));
-    SP_TRY(spec_norm(c.w.partials, kDotBlocks, d_beta + j, d_scale, st));
-    SP_TRY(spec_multiaxpy(w, V, n, 0, c.w.coef, 0.0, st, d_scale));
+    SP_TRY(spec_multidot(w, n, 1, w, c.w.partials, st));
+    SP_TRY(spec_normalise(w, n, c.w.partials, d_beta + j, st));
   }
   {
     std::vector<double> hab((size_t)2 * m);
