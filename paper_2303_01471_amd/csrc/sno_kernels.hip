@@ -19,11 +19,21 @@ __device__ __forceinline__ float gelu_grad(float z) {
   return 0.5f * (1.0f + erff(z * 0.70710678118654752f)) + z * 0.39894228040143268f * __expf(-0.5f * z * z);
 }
 
-// block-wide FP64 sum over 256 threads
+// Threads of the kernels that take a block per sample: with fewer samples than CUs a block of
+// 1024 covers its sample in a quarter of the rounds; from there on 256, so that several
+// samples' phases overlap on a CU.  One sample of 128^2, us with 256 and 1024 threads: features
+// and lift 86 and 11 (spread over 8 blocks, each with its own statistics), softmax 33 and 8;
+// the y-contractions, whose column tiles spread over 4 blocks, 19 and 6.6, 13 and 5.4.
+// (A batch's size picks the order of the FP64 sums.)
+constexpr int kFewSamples = 256;
+inline bool few_samples(int batch) { return batch < kFewSamples; }
+
+// block-wide FP64 sum over NT threads
+template <int NT>
 __device__ __forceinline__ double block_sum(double v, double* sh) {
   sh[threadIdx.x] = v;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
+  for (int o = NT / 2; o > 0; o >>= 1) {
     if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
     __syncthreads();
   }
@@ -32,10 +42,11 @@ __device__ __forceinline__ double block_sum(double v, double* sh) {
   return r;
 }
 
+template <int NT>
 __device__ __forceinline__ float block_max(float v, float* sh) {
   sh[threadIdx.x] = v;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
+  for (int o = NT / 2; o > 0; o >>= 1) {
     if ((int)threadIdx.x < o) sh[threadIdx.x] = fmaxf(sh[threadIdx.x], sh[threadIdx.x + o]);
     __syncthreads();
   }
@@ -45,21 +56,23 @@ __device__ __forceinline__ float block_max(float v, float* sh) {
 }
 
 // features per pixel: standardised f, x / S, y / S
-template <typename T>
-__global__ void __launch_bounds__(256) k_prep(const double* __restrict__ f, int S, T* __restrict__ in) {
-  __shared__ double sh[256];
+template <typename T, int NT>
+__global__ void __launch_bounds__(NT) k_prep(const double* __restrict__ f, int S, T* __restrict__ in) {
+  __shared__ double sh[NT];
   const int b = blockIdx.x, npix = S * S;
   const double* fb = f + (long long)b * npix;
   double s1 = 0.0, s2 = 0.0;
-  for (int p = threadIdx.x; p < npix; p += 256) {
+#pragma unroll 4
+  for (int p = threadIdx.x; p < npix; p += NT) {
     s1 += fb[p];
     s2 += fb[p] * fb[p];
   }
-  const double mean = block_sum(s1, sh) / npix;
-  const double var = block_sum(s2, sh) / npix - mean * mean;
+  const double mean = block_sum<NT>(s1, sh) / npix;
+  const double var = block_sum<NT>(s2, sh) / npix - mean * mean;
   const double inv = 1.0 / sqrt(var > 1e-24 ? var : 1e-24);
   T* ib = in + (long long)b * npix * 3;
-  for (int p = threadIdx.x; p < npix; p += 256) {
+#pragma unroll 4
+  for (int p = threadIdx.x; p < npix; p += NT) {
     ib[3 * p + 0] = (T)(float)((fb[p] - mean) * inv);
     ib[3 * p + 1] = (T)((float)(p % S) / (float)S);
     ib[3 * p + 2] = (T)((float)(p / S) / (float)S);
@@ -146,12 +159,12 @@ __global__ void __launch_bounds__(256) k_pointwise32(const __bf16* __restrict__ 
 }
 
 // one block per sample: logits q = h . wp + bp, then softmax over the grid
-template <typename T>
-__global__ void __launch_bounds__(256) k_project_softmax(const T* __restrict__ h, const float* __restrict__ wp,
+template <typename T, int NT>
+__global__ void __launch_bounds__(NT) k_project_softmax(const T* __restrict__ h, const float* __restrict__ wp,
                                                          const float* __restrict__ bp, int npix, int C,
                                                          float* __restrict__ rho) {
-  __shared__ double sh[256];
-  __shared__ float shf[256];
+  __shared__ double sh[NT];
+  __shared__ float shf[NT];
   const int b = blockIdx.x;
   const T* hb = h + (long long)b * npix * C;
   float* rb = rho + (long long)b * npix;
@@ -159,7 +172,7 @@ __global__ void __launch_bounds__(256) k_project_softmax(const T* __restrict__ h
   if (sizeof(T) == 2 && C == 32) {
     // width 32 in BF16: a pixel's 64-byte row in four 16-byte loads, the same FMA order
     typedef T t8 __attribute__((ext_vector_type(8)));
-    for (int p = threadIdx.x; p < npix; p += 256) {
+    for (int p = threadIdx.x; p < npix; p += NT) {
       const t8* row = reinterpret_cast<const t8*>(hb + (long long)p * 32);
       float q = bp[0];
 #pragma unroll
@@ -172,46 +185,51 @@ __global__ void __launch_bounds__(256) k_project_softmax(const T* __restrict__ h
       mx = fmaxf(mx, q);
     }
   } else {
-    for (int p = threadIdx.x; p < npix; p += 256) {
+    for (int p = threadIdx.x; p < npix; p += NT) {
       float q = bp[0];
       for (int c = 0; c < C; ++c) q = fmaf(ld(hb, (long long)p * C + c), wp[c], q);
       rb[p] = q;
       mx = fmaxf(mx, q);
     }
   }
-  mx = block_max(mx, shf);
+  mx = block_max<NT>(mx, shf);
   double s = 0.0;
-  for (int p = threadIdx.x; p < npix; p += 256) {
+#pragma unroll 4
+  for (int p = threadIdx.x; p < npix; p += NT) {
     const float e = __expf(rb[p] - mx);
     rb[p] = e;
     s += e;
   }
-  const double tot = block_sum(s, sh);
+  const double tot = block_sum<NT>(s, sh);
   const float inv = (float)(1.0 / tot);
-  for (int p = threadIdx.x; p < npix; p += 256) rb[p] *= inv;
+#pragma unroll 4
+  for (int p = threadIdx.x; p < npix; p += NT) rb[p] *= inv;
 }
 
 // one block per sample: loss_b = sum |rho_hat - rho|; dq = rho_hat (g - <rho_hat, g>), g = sign / B
-__global__ void __launch_bounds__(256) k_loss_grad(const float* __restrict__ rh, const float* __restrict__ r,
+template <int NT>
+__global__ void __launch_bounds__(NT) k_loss_grad(const float* __restrict__ rh, const float* __restrict__ r,
                                                    int batch, int npix, float* __restrict__ dq,
                                                    double* __restrict__ loss) {
-  __shared__ double sh[256];
+  __shared__ double sh[NT];
   const int b = blockIdx.x;
   const float* a = rh + (long long)b * npix;
   const float* t = r + (long long)b * npix;
   float* d = dq + (long long)b * npix;
   const float invb = 1.0f / (float)batch;
   double l = 0.0, s = 0.0;
-  for (int p = threadIdx.x; p < npix; p += 256) {
+#pragma unroll 4
+  for (int p = threadIdx.x; p < npix; p += NT) {
     const float diff = a[p] - t[p];
     const float g = diff > 0.0f ? invb : (diff < 0.0f ? -invb : 0.0f);
     l += fabs((double)diff);
     s += (double)a[p] * g;
     d[p] = g;
   }
-  const double lt = block_sum(l, sh);
-  const float st = (float)block_sum(s, sh);
-  for (int p = threadIdx.x; p < npix; p += 256) d[p] = a[p] * (d[p] - st);
+  const double lt = block_sum<NT>(l, sh);
+  const float st = (float)block_sum<NT>(s, sh);
+#pragma unroll 4
+  for (int p = threadIdx.x; p < npix; p += NT) d[p] = a[p] * (d[p] - st);
   if (threadIdx.x == 0) loss[b] = lt;
 }
 
@@ -349,8 +367,12 @@ inline dim3 grid1(long long n) { return dim3((unsigned)((n + 255) / 256)); }
 }  // namespace
 
 hipError_t sno_prep_input(const double* f, int batch, int S, void* in, bool bf16, hipStream_t st) {
-  if (bf16) hipLaunchKernelGGL(k_prep<__bf16>, dim3(batch), dim3(256), 0, st, f, S, (__bf16*)in);
-  else hipLaunchKernelGGL(k_prep<float>, dim3(batch), dim3(256), 0, st, f, S, (float*)in);
+  const bool few = few_samples(batch);
+  const dim3 nt(few ? 1024 : 256);
+  if (bf16)
+    hipLaunchKernelGGL((few ? k_prep<__bf16, 1024> : k_prep<__bf16, 256>), dim3(batch), nt, 0, st, f, S, (__bf16*)in);
+  else
+    hipLaunchKernelGGL((few ? k_prep<float, 1024> : k_prep<float, 256>), dim3(batch), nt, 0, st, f, S, (float*)in);
   return hipGetLastError();
 }
 
@@ -378,19 +400,21 @@ hipError_t sno_bias_act(float* z, const float* bias, long long rows, int C, void
 // inference form at width 32 in BF16: one sample's features, formed as k_prep forms them and
 // rounded to BF16 like the lift's operands, and the lift h0 = x0 Wl^T + bl in one pass; the
 // features are not stored. Thread t writes channels 8(t%4) .. 8(t%4)+7 of its pixels.
-__global__ void __launch_bounds__(256) k_prep_lift32(const double* __restrict__ f, int S,
+template <int NT>
+__global__ void __launch_bounds__(NT) k_prep_lift32(const double* __restrict__ f, int S,
                                                      const __bf16* __restrict__ Wl, const float* __restrict__ bl,
                                                      __bf16* __restrict__ h) {
-  __shared__ double sh[256];
+  __shared__ double sh[NT];
   const int b = blockIdx.x, npix = S * S;
   const double* fb = f + (long long)b * npix;
   double s1 = 0.0, s2 = 0.0;
-  for (int p = threadIdx.x; p < npix; p += 256) {
+#pragma unroll 4
+  for (int p = threadIdx.x; p < npix; p += NT) {
     s1 += fb[p];
     s2 += fb[p] * fb[p];
   }
-  const double mean = block_sum(s1, sh) / npix;
-  const double var = block_sum(s2, sh) / npix - mean * mean;
+  const double mean = block_sum<NT>(s1, sh) / npix;
+  const double var = block_sum<NT>(s2, sh) / npix - mean * mean;
   const double inv = 1.0 / sqrt(var > 1e-24 ? var : 1e-24);
   const int c = threadIdx.x & 3;
   float w0[8], w1[8], w2[8], bb[8];
@@ -406,7 +430,8 @@ __global__ void __launch_bounds__(256) k_prep_lift32(const double* __restrict__ 
   // S is a power of two: coordinates by mask and shift, scaled exactly by 1/S
   const int sl = 31 - __clz(S);
   const float rs = 1.0f / (float)S;
-  for (int e = threadIdx.x; e < npix * 4; e += 256) {
+  const int per = npix * 4 / gridDim.y;  // (both powers of two)
+  for (int e = per * blockIdx.y + threadIdx.x; e < per * (int)(blockIdx.y + 1); e += NT) {
     const int p = e >> 2;
     const float x0 = (float)(__bf16)(float)((fb[p] - mean) * inv);
     const float x1 = (float)(__bf16)((float)(p & (S - 1)) * rs);
@@ -420,7 +445,11 @@ __global__ void __launch_bounds__(256) k_prep_lift32(const double* __restrict__ 
 
 hipError_t sno_prep_lift32(const double* f, int batch, int S, const void* Wl, const float* bl, void* h,
                            hipStream_t st) {
-  hipLaunchKernelGGL(k_prep_lift32, dim3(batch), dim3(256), 0, st, f, S, (const __bf16*)Wl, bl, (__bf16*)h);
+  if (few_samples(batch))
+    hipLaunchKernelGGL(k_prep_lift32<1024>, dim3(batch, S >= 32 ? 8 : 1), dim3(1024), 0, st, f, S, (const __bf16*)Wl, bl,
+                       (__bf16*)h);
+  else
+    hipLaunchKernelGGL(k_prep_lift32<256>, dim3(batch), dim3(256), 0, st, f, S, (const __bf16*)Wl, bl, (__bf16*)h);
   return hipGetLastError();
 }
 
@@ -559,26 +588,33 @@ hipError_t sno_spectral_pointwise32(const void* gx, const void* U, const void* h
 
 // per sample, rho = softmax of its logits in place: the max, the FP64 sum of exp(q - max)
 // and the scaling exactly as k_project_softmax takes them (same threads, same order)
-__global__ void __launch_bounds__(256) k_softmax_rows(float* __restrict__ rho, int npix) {
-  __shared__ double sh[256];
-  __shared__ float shf[256];
+template <int NT>
+__global__ void __launch_bounds__(NT) k_softmax_rows(float* __restrict__ rho, int npix) {
+  __shared__ double sh[NT];
+  __shared__ float shf[NT];
   float* rb = rho + (long long)blockIdx.x * npix;
   float mx = -INFINITY;
-  for (int p = threadIdx.x; p < npix; p += 256) mx = fmaxf(mx, rb[p]);
-  mx = block_max(mx, shf);
+#pragma unroll 4
+  for (int p = threadIdx.x; p < npix; p += NT) mx = fmaxf(mx, rb[p]);
+  mx = block_max<NT>(mx, shf);
   double s = 0.0;
-  for (int p = threadIdx.x; p < npix; p += 256) {
+#pragma unroll 4
+  for (int p = threadIdx.x; p < npix; p += NT) {
     const float e = __expf(rb[p] - mx);
     rb[p] = e;
     s += e;
   }
-  const double tot = block_sum(s, sh);
+  const double tot = block_sum<NT>(s, sh);
   const float inv = (float)(1.0 / tot);
-  for (int p = threadIdx.x; p < npix; p += 256) rb[p] *= inv;
+#pragma unroll 4
+  for (int p = threadIdx.x; p < npix; p += NT) rb[p] *= inv;
 }
 
 hipError_t sno_softmax_rows(float* rho, int batch, int npix, hipStream_t st) {
-  hipLaunchKernelGGL(k_softmax_rows, dim3(batch), dim3(256), 0, st, rho, npix);
+  if (few_samples(batch))
+    hipLaunchKernelGGL(k_softmax_rows<1024>, dim3(batch), dim3(1024), 0, st, rho, npix);
+  else
+    hipLaunchKernelGGL(k_softmax_rows<256>, dim3(batch), dim3(256), 0, st, rho, npix);
   return hipGetLastError();
 }
 
@@ -624,10 +660,12 @@ __global__ void __launch_bounds__(256) k_inv_y32(const __bf16* __restrict__ Gy, 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = lane & 31, h = lane >> 5;
   const __bf16* Gb = G + (long long)blockIdx.x * gstride;
-  for (int e = tid; e < 64 * 64; e += 256) {  // 16-byte pieces: row k = e % 64, columns 8 (e / 64) ..
+  // column tiles [ct0, ct0 + nct) of this block
+  const int nct = 16 / gridDim.y, ct0 = nct * blockIdx.y;
+  for (int e = tid; e < 64 * 4 * nct; e += 256) {  // 16-byte pieces: row k = e % 64, columns 8 (e / 64) ..
     // (a wavefront's lanes take the 64 rows of one column group, so each of its transposed
     // 2-byte writes covers 64 consecutive entries of one LDS row)
-    const int k = e & 63, c0 = (e >> 6) * 8;
+    const int k = e & 63, c0 = (e >> 6) * 8 + 32 * ct0;
     const bf16x8_t v = *reinterpret_cast<const bf16x8_t*>(Gb + k * 512 + c0);
 #pragma unroll
     for (int i = 0; i < 8; ++i) gt[(c0 + i) * 72 + k] = v[i];
@@ -638,7 +676,7 @@ __global__ void __launch_bounds__(256) k_inv_y32(const __bf16* __restrict__ Gy, 
     bf16x8_t a[4];
 #pragma unroll
     for (int st = 0; st < 4; ++st) a[st] = *reinterpret_cast<const bf16x8_t*>(Gy + (32 * rt + c) * 64 + 16 * st + 8 * h);
-    for (int ct = 0; ct < 16; ++ct) {
+    for (int ct = ct0; ct < ct0 + nct; ++ct) {
       f32x16_t acc = {};
 #pragma unroll
       for (int st = 0; st < 4; ++st) {
@@ -653,7 +691,7 @@ __global__ void __launch_bounds__(256) k_inv_y32(const __bf16* __restrict__ Gy, 
 }
 
 hipError_t sno_inv_y32(const void* Gy, const void* G, long long gstride, int batch, int S, void* U, hipStream_t st) {
-  hipLaunchKernelGGL(k_inv_y32, dim3(batch), dim3(256), 0, st, (const __bf16*)Gy, (const __bf16*)G, gstride, S,
+  hipLaunchKernelGGL(k_inv_y32, dim3(batch, few_samples(batch) ? 4 : 1), dim3(256), 0, st, (const __bf16*)Gy, (const __bf16*)G, gstride, S,
                      (__bf16*)U);
   return hipGetLastError();
 }
@@ -678,7 +716,7 @@ __global__ void __launch_bounds__(256) k_fwd_y32(const __bf16* __restrict__ Fy1,
   __syncthreads();
   const __bf16* Tb = T + (long long)blockIdx.x * S * 1024;
   __bf16* Hb = H + (long long)blockIdx.x * hstride;
-  for (int ct = wave; ct < 16; ct += 4) {
+  for (int ct = 4 * blockIdx.y + wave; ct < 16; ct += 4 * gridDim.y) {
     f32x16_t acc0 = {}, acc1 = {};
     const __bf16* tc = Tb + 32 * ct + c;
     for (int k0 = 0; k0 < S; k0 += 16) {
@@ -715,7 +753,7 @@ hipError_t sno_fwd_y32(const void* Fy1, const void* Fy2, const void* T, int batc
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_fwd_y32, dim3(batch), dim3(256), lds, st, (const __bf16*)Fy1, (const __bf16*)Fy2,
+  hipLaunchKernelGGL(k_fwd_y32, dim3(batch, few_samples(batch) ? 4 : 1), dim3(256), lds, st, (const __bf16*)Fy1, (const __bf16*)Fy2,
                      (const __bf16*)T, S, (__bf16*)H, hstride);
   return hipGetLastError();
 }
@@ -793,21 +831,32 @@ hipError_t sno_pointwise32(const void* h, const void* W, const float* z, const f
   return hipGetLastError();
 }
 
+template <typename T>
+static void project_softmax(const T* h, const float* wp, const float* bp, int batch, int npix, int C, float* rho,
+                            hipStream_t st) {
+  if (few_samples(batch))
+    hipLaunchKernelGGL((k_project_softmax<T, 1024>), dim3(batch), dim3(1024), 0, st, h, wp, bp, npix, C, rho);
+  else
+    hipLaunchKernelGGL((k_project_softmax<T, 256>), dim3(batch), dim3(256), 0, st, h, wp, bp, npix, C, rho);
+}
+
 hipError_t sno_project_softmax(const void* h, const float* wp, const float* bp, int batch, int npix,
                                int C, bool bf16, float* rho, hipStream_t st) {
   if (bf16)
-    hipLaunchKernelGGL(k_project_softmax<__bf16>, dim3(batch), dim3(256), 0, st, (const __bf16*)h, wp, bp,
-                       npix, C, rho);
+    project_softmax((const __bf16*)h, wp, bp, batch, npix, C, rho, st);
   else
-    hipLaunchKernelGGL(k_project_softmax<float>, dim3(batch), dim3(256), 0, st, (const float*)h, wp, bp,
-                       npix, C, rho);
+    project_softmax((const float*)h, wp, bp, batch, npix, C, rho, st);
   return hipGetLastError();
 }
 
 hipError_t sno_loss_grad(const float* rho_hat, const float* rho, int batch, int npix, float* dq,
                          double* loss_per_sample, hipStream_t st) {
-  hipLaunchKernelGGL(k_loss_grad, dim3(batch), dim3(256), 0, st, rho_hat, rho, batch, npix, dq,
-                     loss_per_sample);
+  if (few_samples(batch))
+    hipLaunchKernelGGL(k_loss_grad<1024>, dim3(batch), dim3(1024), 0, st, rho_hat, rho, batch, npix, dq,
+                       loss_per_sample);
+  else
+    hipLaunchKernelGGL(k_loss_grad<256>, dim3(batch), dim3(256), 0, st, rho_hat, rho, batch, npix, dq,
+                       loss_per_sample);
   return hipGetLastError();
 }
 
