@@ -391,8 +391,15 @@ qhd_status splitk(qhd_sno_s* m, const void* dzp, int a, const void* x, int b, lo
                   hipStream_t st) {
   const int ns = m->nsplit;
   const long long chunk = rows / ns;
-  ST_TRY(gemm(m, a, b, (int)chunk, ns, dzp, a, chunk * a, true, x, b, chunk * b, false, m->partials, b,
-              (long long)a * b, false, 1.0f, 0.0f, st));
+  if (m->bf16 && a == 32 && b <= 32 && chunk % 64 == 0) {
+    ST_TRY(check(m, dzp, rows * a * m->es, "gradient input"));
+    ST_TRY(check(m, x, rows * b * m->es, "gradient features"));
+    ST_TRY(check(m, m->partials, (long long)ns * a * b * 4, "partials"));
+    ST_TRY(launch(m, DEV(m, sno_splitk32(dzp, x, b, (int)chunk, ns, m->partials, st)), "1x1 map gradient"));
+  } else {
+    ST_TRY(gemm(m, a, b, (int)chunk, ns, dzp, a, chunk * a, true, x, b, chunk * b, false, m->partials, b,
+                (long long)a * b, false, 1.0f, 0.0f, st));
+  }
   ST_TRY(check(m, out, (long long)a * b * 4, "split-K output"));
   return launch(m, DEV(m, sno_reduce_partials(m->partials, ns, a * b, out, false, st)), "split-K reduce");
 }

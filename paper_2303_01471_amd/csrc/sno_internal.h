@@ -53,6 +53,9 @@ hipError_t sno_spectral_pointwise32(const void* gx, const void* U, const void* h
                                     int S, long long nrows, void* out, int act, const void* fx, void* T,
                                     const float* wp, const float* bp, float* q, hipStream_t st);
 // per sample, softmax of npix logits in place (as sno_project_softmax forms it)
+// partial gradients of a 1x1 map at width 32, BF16: out[part] (32 x b) = sum over the part's
+// `rows` (a multiple of 64) rows of dz^T x, b <= 32
+hipError_t sno_splitk32(const void* dz, const void* x, int b, int rows, int parts, float* out, hipStream_t st);
 hipError_t sno_softmax_rows(float* rho, int batch, int npix, hipStream_t st);
 // width 32, 16 modes, BF16: per row of S pixels (nrows = batch x S), T_row (32 x 32) = fx (32 x S) X_row;
 // S % 16 == 0

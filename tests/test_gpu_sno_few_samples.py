@@ -7,6 +7,7 @@ value, as FP32 rounds them, and their sums within 1e-5 of one."""
 import numpy as np
 import pytest
 
+from oracle import sno_reference as ref
 from paper_2303_01471_amd import qhd as q
 
 pytestmark = pytest.mark.gpu
@@ -37,3 +38,36 @@ def test_one_sample_alone_and_in_batches(S, C, M, precision):
             assert float((out.double().sum(dim=(1, 2)) - 1.0).abs().max()) <= 1e-5
     finally:
         net.close()
+
+
+@pytest.mark.parametrize("B", [3, 16, 24, 32])
+def test_training_gradient_with_parts_of_either_form(B):
+    """32^2 pixels: parts of 4 B rows, the width-32 kernel from 64 on in steps of 64, else the
+    general product; against the FP64 gradient with the bounds of BF16 activations (cosine
+    0.99, each 1x1 map within 10 % with sharp parameters)."""
+    import torch
+    cfg = ref.Config(S=32, C=32, M=16, L=2)
+    d = ref.unpack(ref.random_params(cfg, 47, spectral_scale=4.0 / cfg.C), cfg)
+    d["Wp"] = 8.0 * d["Wp"]
+    p = ref.pack(d, cfg).astype(np.float32)
+    rng = np.random.default_rng(48)
+    f = rng.standard_normal((B, 32, 32)) * 2.0 + 1.0
+    rho = rng.dirichlet(np.ones(1024), size=B).reshape(B, 32, 32).astype(np.float32)
+    net = _net(32, 32, 16, B, "bf16", True)
+    try:
+        net.set_params(p)
+        ft, rt = torch.from_numpy(f).cuda().contiguous(), torch.from_numpy(rho).cuda().contiguous()
+        net.forward(ft)
+        loss, g = net.backward(ft, rt, want_grad=True)
+    finally:
+        net.close()
+    lref, gref = ref.backward(p.astype(np.float64), f, rho.astype(np.float64), cfg)
+    g64 = g.astype(np.float64)
+    assert abs(loss - lref) < 0.02 * lref
+    assert float(g64 @ gref / (np.linalg.norm(g64) * np.linalg.norm(gref))) > 0.99
+    o = 0
+    for name, shape in ref.param_layout(cfg):
+        n = int(np.prod(shape))
+        if name[0] == "W":
+            assert np.linalg.norm(g64[o:o + n] - gref[o:o + n]) < 0.1 * np.linalg.norm(gref[o:o + n]), name
+        o += n
