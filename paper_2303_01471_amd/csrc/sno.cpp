@@ -319,6 +319,10 @@ qhd_status build_dft(qhd_sno_s* m) {
   return st;
 }
 
+// training at width 32 with 16 modes in BF16: a layer's inverse x-contraction and 1x1 map are one
+// pass, in either direction (any other width or mode count takes the general products)
+bool train32(const qhd_sno_s* m) { return m->train && m->bf16 && m->C == 32 && m->M == 16 && m->S % 32 == 0; }
+
 qhd_status forward(qhd_sno_s* m, const double* f, int B, hipStream_t st) {
   const int C = m->C;
   const long long npix = m->npix, rows = (long long)B * npix;
@@ -363,8 +367,14 @@ qhd_status forward(qhd_sno_s* m, const double* f, int B, hipStream_t st) {
                     "inverse+1x1 map+GELU"));
       continue;
     }
-    ST_TRY(inv_dft(m, m->G, m->Gxw, zl, B, 0.0f, st));
     ST_TRY(check(m, zl, rows * C * 4, "layer pre-activation"));
+    if (train32(m)) {
+      ST_TRY(inv_dft_y(m, m->G, B, st));
+      ST_TRY(launch(m, DEV(m, sno_train_map32(m->Gxw, m->T1, hin, m->T(m->pt, m->o_w[l]), m->params + m->o_b[l], m->S,
+                                              (long long)B * m->S, zl, hout, st)), "inverse+1x1 map+GELU"));
+      continue;
+    }
+    ST_TRY(inv_dft(m, m->G, m->Gxw, zl, B, 0.0f, st));
     if (!m->train && m->bf16 && C == 32) {
       // inference: the 1x1 map, bias and GELU in one pass (the pre-activation is not kept)
       ST_TRY(launch(m, DEV(m, sno_pointwise32(hin, m->T(m->pt, m->o_w[l]), zl, m->params + m->o_b[l], rows, hout,
@@ -442,6 +452,12 @@ qhd_status backward(qhd_sno_s* m, const float* target, int B, hipStream_t st) {
     ST_TRY(gemm(m, B, C, C, nm, m->T(m->G, half), ld, C, false, Rr, C, (long long)C * C, false,
                 m->T(m->dH, half), ld, C, true, 1.0f, 0.0f, st, m->G, Ri, -1.0f));
     // dh = Re(F^H dH) + dz W
+    if (train32(m)) {
+      ST_TRY(inv_dft_y(m, m->dH, B, st));
+      ST_TRY(launch(m, DEV(m, sno_train_map32(m->Gx, m->T1, m->dz, m->T(m->pt, m->o_w[l]), nullptr, m->S,
+                                              (long long)B * m->S, m->dh, nullptr, st)), "inverse+1x1 map adjoint"));
+      continue;
+    }
     ST_TRY(inv_dft(m, m->dH, m->Gx, m->dh, B, 0.0f, st));
     ST_TRY(gemm(m, (int)npix, C, C, B, m->dz, C, npix * C, false, m->T(m->pt, m->o_w[l]), C, 0, false, m->dh, C,
                 npix * C, false, 1.0f, 1.0f, st));

@@ -56,6 +56,10 @@ hipError_t sno_spectral_pointwise32(const void* gx, const void* U, const void* h
 // partial gradients of a 1x1 map at width 32, BF16: out[part] (32 x b) = sum over the part's
 // `rows` (a multiple of 64) rows of dz^T x, b <= 32
 hipError_t sno_splitk32(const void* dz, const void* x, int b, int rows, int parts, float* out, hipStream_t st);
+// training form of a layer's spectral part and 1x1 map at width 32 with 16 modes, BF16: z = gx U_row
+// + h W^T + bias and out = GELU(z), or, without out, z = gx U_row + h W (S a power of two >= 32)
+hipError_t sno_train_map32(const void* gx, const void* U, const void* h, const void* W, const float* bias, int S,
+                           long long nrows, float* z, void* out, hipStream_t st);
 hipError_t sno_softmax_rows(float* rho, int batch, int npix, hipStream_t st);
 // width 32, 16 modes, BF16: per row of S pixels (nrows = batch x S), T_row (32 x 32) = fx (32 x S) X_row;
 // S % 16 == 0
