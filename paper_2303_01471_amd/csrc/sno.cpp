@@ -339,8 +339,8 @@ qhd_status forward(qhd_sno_s* m, const double* f, int B, hipStream_t st) {
     float* z0 = m->z[0];
     ST_TRY(gemm(m, (int)npix, C, 3, B, m->in, 3, npix * 3, false, m->T(m->pt, m->o_wl), 3, 0, true, z0, C,
                 npix * C, false, 1.0f, 0.0f, st));
-    // (the biased pre-activations are kept only for the backward pass of training)
-    ST_TRY(launch(m, DEV(m, sno_bias_act(z0, m->params + m->o_bl, rows, C, m->h[0], m->bf16, 0, st, m->train)),
+    // (the lift has no activation, so its biased values are not kept for the backward pass)
+    ST_TRY(launch(m, DEV(m, sno_bias_act(z0, m->params + m->o_bl, rows, C, m->h[0], m->bf16, 0, st, false)),
                   "lift bias"));
   }
   // inference at width 32 with 16 modes: a layer's inverse x-contraction, 1x1 map, bias and GELU

