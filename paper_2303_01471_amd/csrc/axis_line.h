@@ -14,41 +14,47 @@ __host__ __device__ constexpr int etab_len() {
   return MODEL == kModelQAA ? ilog2_c(N) + 1 : N / 2 + 1;
 }
 
-// Tables of instances i0 .. i0 + count - 1: per instance E(a_{j-1}) then E(a_j), j = the
-// stage of sub-step s, by the whole block (the caller synchronises around it).  The entry
-// of |frequency| N / 2 is the fourth power of that of N / 4 (its phase is four times as
-// large), so that a block of N threads or half as many has whole rounds.
-template <int N, int MODEL, bool Y4>
-__device__ __forceinline__ void fill_etab(double2* __restrict__ tab, const InstDev* __restrict__ inst, int i0, int count,
-                                          int axis, long long s) {
+// Tables E(a0) then E(a1) of one instance, by the whole block (the caller synchronises around
+// it).  The entry of |frequency| N / 2 is the fourth power of that of N / 4 (its phase is four
+// times as large), so that a block of N threads or half as many has whole rounds.
+template <int N, int MODEL>
+__device__ __forceinline__ void fill_etab_pair(double2* __restrict__ tab, const InstDev& I, int axis, double a0, double a1) {
   constexpr int H = etab_len<N, MODEL>();
   constexpr int R = MODEL == kModelQAA ? H : N / 2;  // entries evaluated per table
   constexpr double inv_n = 1.0 / N;
-  for (int d = 0; d < count; ++d, tab += 2 * H) {
+  const double unit = MODEL == kModelQAA ? I.dt * kInv2Pi : I.kin_turns[axis];
+  for (int e = threadIdx.x; e < 2 * R; e += blockDim.x) {
+    const int cur = e >= R ? 1 : 0, k = e - cur * R;
+    const double c = (cur ? a1 : a0) * unit;
+    const double turns = c * (double)(MODEL == kModelQAA ? 2 * k - ilog2_c(N) : k * k);
+    // 128-point axes by the exact angle: their rounding left no room for the error of the
+    // transcendental form (state error of 8 x 128^2 after 600 steps 4.6e-6 -> 3.4e-6, no time
+    // seen); at other lengths the errors stand below those of separate axis passes without it,
+    // and it costs registers (512-point columns 78 -> 104) or latency (one 64^2 instance +0.9 us)
+    double2 v;
+    if constexpr (N == 128) v = phase_turns_exact(turns);
+    else v = phase_turns_d(turns);
+    tab[cur * H + k] = make_double2(v.x * inv_n, v.y * inv_n);
+    if (MODEL != kModelQAA && k == N / 4) {
+      v = cmul_dd(v, v);
+      v = cmul_dd(v, v);
+      tab[cur * H + N / 2] = make_double2(v.x * inv_n, v.y * inv_n);
+    }
+  }
+}
+
+// Tables of instances i0 .. i0 + count - 1: per instance E(a_{j-1}) then E(a_j), j = the
+// stage of sub-step s
+template <int N, int MODEL, bool Y4>
+__device__ __forceinline__ void fill_etab(double2* __restrict__ tab, const InstDev* __restrict__ inst, int i0, int count,
+                                          int axis, long long s) {
+  for (int d = 0; d < count; ++d, tab += 2 * etab_len<N, MODEL>()) {
     const InstDev& I = inst[i0 + d];
     const long long j = I.steps_done + s;
     double a0, a1, b;
     sched_ab<Y4>(I, j - 1, a0, b);
     sched_ab<Y4>(I, j, a1, b);
-    const double unit = MODEL == kModelQAA ? I.dt * kInv2Pi : I.kin_turns[axis];
-    for (int e = threadIdx.x; e < 2 * R; e += blockDim.x) {
-      const int cur = e >= R ? 1 : 0, k = e - cur * R;
-      const double c = (cur ? a1 : a0) * unit;
-      const double turns = c * (double)(MODEL == kModelQAA ? 2 * k - ilog2_c(N) : k * k);
-      // 128-point axes by the exact angle: their rounding left no room for the error of the
-      // transcendental form (state error of 8 x 128^2 after 600 steps 4.6e-6 -> 3.4e-6, no time
-      // seen); at other lengths the errors stand below those of separate axis passes without it,
-      // and it costs registers (512-point columns 78 -> 104) or latency (one 64^2 instance +0.9 us)
-      double2 v;
-      if constexpr (N == 128) v = phase_turns_exact(turns);
-      else v = phase_turns_d(turns);
-      tab[cur * H + k] = make_double2(v.x * inv_n, v.y * inv_n);
-      if (MODEL != kModelQAA && k == N / 4) {
-        v = cmul_dd(v, v);
-        v = cmul_dd(v, v);
-        tab[cur * H + N / 2] = make_double2(v.x * inv_n, v.y * inv_n);
-      }
-    }
+    fill_etab_pair<N, MODEL>(tab, I, axis, a0, a1);
   }
 }
 

@@ -94,6 +94,15 @@ __device__ __forceinline__ double axis_turns(const InstDev& I, int axis, int idx
   }
 }
 
+// the merged potential factor of stage j from b of its step (b) and of the one before (bp)
+__device__ __forceinline__ double merged_turns(const InstDev& I, long long j, bool entry, double b, double bp) {
+  if (I.scheme == kSchemeLie) return I.dt * b * kInv2Pi;
+  double beta = 0.5 * I.dt * b;
+  if (!entry && j > 0) beta += 0.5 * I.dt * bp;
+  return beta * kInv2Pi;
+}
+
+
 // Potential phase of the pass that applies V in step j, in turns per unit f.
 // Symmetric scheme: the leading half step of j merged with the trailing half step of
 // j-1 (only the leading half on the entry step, where nothing is pending).

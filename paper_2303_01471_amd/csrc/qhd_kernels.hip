@@ -276,14 +276,11 @@ __global__ void __launch_bounds__(64) k_line_steps_1d(const InstDev* __restrict_
     }
     // b of the stage before, carried along (potential_turns evaluates the schedule twice)
     double a, b, b_prev = 0.0;
-    const bool lie = I.scheme == kSchemeLie;
     if (I.steps_done > 0 && lim > 0) sched_ab(I, I.steps_done - 1, a, b_prev);
     for (long long s = 0; s < lim; ++s) {
       const long long j = I.steps_done + s;
       sched_ab(I, j, a, b);
-      double beta = 0.5 * I.dt * b;
-      if (!(s == 0 && I.mode == kModeClean) && j > 0) beta += 0.5 * I.dt * b_prev;
-      const double cpot = (lie ? I.dt * b : beta) * kInv2Pi;
+      const double cpot = merged_turns(I, j, s == 0 && I.mode == kModeClean, b, b_prev);
       b_prev = b;
       const double ck = a * I.kin_turns[0];
 #pragma unroll

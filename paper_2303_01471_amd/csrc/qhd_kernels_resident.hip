@@ -25,29 +25,33 @@
 
 namespace qhd {
 
-template <int NX, int NY, int MODEL = kModelQHD>
+// MANY (128 x 32 and 32 x 128, more members than CUs): 256 threads, so that two instances fit a
+// CU beside each other (us per step, 512 and 256 threads: 2000 x 128 x 32 58 and 47, 2000 x 32 x
+// 128 45 and 38; one instance 7.4 and 8.4, 5.6 and 6.3)
+template <int NX, int NY, int MODEL, bool MANY>
 struct ResCfg {
   // 128-point lines take 16 points per lane (radices 16 and 8: one exchange per transform)
   static constexpr int PX = NX >= 128 ? 16 : 8, PY = NY >= 128 ? 16 : 8;
   static constexpr int TX = NX / PX, TY = NY / PY;             // lanes per row / column line
   static constexpr int LANES = NX * NY / PX > NX * NY / PY ? NX * NY / PX : NX * NY / PY;
-  // 1024 threads (four waves per SIMD) where the registers fit in 128 per lane
-  static constexpr int MAXT = MODEL == kModelQAA && (PX == 16 || PY == 16) ? 512 : 1024;
+  // 16 points need more than the 128 registers of a 1024-thread block (1024 and 512 threads, us
+  // per step: 1000 x 128 x 64 67 and 47, 1000 x 64 x 128 60 and 42, 512 x 128^2 55 and 50)
+  static constexpr int MAXT = MANY ? 256 : PX == 16 || PY == 16 ? 512 : 1024;
   static constexpr int NT = LANES < MAXT ? LANES : MAXT;
   static constexpr int RS = ((NX + NX / 8) | 1);               // row stride in slots (odd)
   static constexpr int ROWS_PER_IT = NT / TX, COLS_PER_IT = NT / TY;
   static_assert(NX >= 32 && NY >= 32 && NX <= 128 && NY <= 128, "resident sizes: 32..128 per axis");
 };
 
-template <int NX, int NY, int MODEL, bool Y4>
-__global__ void __launch_bounds__((ResCfg<NX, NY, MODEL>::NT)) k_resident_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p,
+template <int NX, int NY, int MODEL, bool Y4, bool MANY>
+__global__ void __launch_bounds__((ResCfg<NX, NY, MODEL, MANY>::NT)) k_resident_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p,
                                                                      float2* __restrict__ psi,
                                                                      const double* __restrict__ f,
                                                                      const double2* __restrict__ twx,
                                                                      const double2* __restrict__ twy,
                                                                      long long max_steps, int start_axis) {
   const int ninst = *nact_p;  // members active in this sub-step (device, set per chunk)
-  using C = ResCfg<NX, NY, MODEL>;
+  using C = ResCfg<NX, NY, MODEL, MANY>;
   constexpr int PX = C::PX, PY = C::PY, TX = C::TX, TY = C::TY, NT = C::NT, RS = C::RS;
   constexpr int HX = etab_len<NX, MODEL>(), HY = etab_len<NY, MODEL>();
   constexpr bool SHARE_TW = NX == NY;
@@ -80,13 +84,23 @@ __global__ void __launch_bounds__((ResCfg<NX, NY, MODEL>::NT)) k_resident_2d(con
       st[y * RS + lds_slot(x)] = make_float2(v.x, v.y);
       st[y * RS + lds_slot(x) + 1] = make_float2(v.z, v.w);
     }
-    if (start_axis == 0) fill_etab<NX, MODEL, Y4>(ex, inst, i, 1, 0, 0);
-    else fill_etab<NY, MODEL, Y4>(ey, inst, i, 1, 1, 0);
+    // a, b of the step before, this one and the next, carried along: one evaluation of the
+    // schedule per step (line_task and fill_etab take four: 39 x 32^2 and 44 fourth-order steps, 572 -> 551 us)
+    double ap, bp, ac, bc;
+    sched_ab<Y4>(I, I.steps_done - 1, ap, bp);
+    sched_ab<Y4>(I, I.steps_done, ac, bc);
+    if (start_axis == 0) fill_etab_pair<NX, MODEL>(ex, I, 0, ap, ac);
+    else fill_etab_pair<NY, MODEL>(ey, I, 1, ap, ac);
     __syncthreads();
     for (long long s = 0; s < lim; ++s) {
-      if (((start_axis + s) & 1) == 0) {
-        const LineTask k = line_task<Y4>(I, s, max_steps, kModeOweX, 0);
-        fill_etab<NY, MODEL, Y4>(ey, inst, i, 1, 1, s + 1);  // read after the barrier
+      double an, bn;
+      sched_ab<Y4>(I, I.steps_done + s + 1, an, bn);
+      const bool row = ((start_axis + s) & 1) == 0;
+      struct { bool prev; double cpot; } k;
+      k.prev = s > 0 || I.mode == (row ? kModeOweX : kModeOweY);
+      k.cpot = merged_turns(I, I.steps_done + s, s == 0 && I.mode == kModeClean, bc, bp);
+      if (row) {
+        fill_etab_pair<NY, MODEL>(ey, I, 1, ac, an);  // read after the barrier
 #pragma unroll 1
         for (int y = rl; y < NY; y += C::ROWS_PER_IT) {
           float2* my = st + y * RS;
@@ -113,8 +127,7 @@ __global__ void __launch_bounds__((ResCfg<NX, NY, MODEL>::NT)) k_resident_2d(con
           }
         }
       } else {
-        const LineTask k = line_task<Y4>(I, s, max_steps, kModeOweY, 0);
-        fill_etab<NX, MODEL, Y4>(ex, inst, i, 1, 0, s + 1);
+        fill_etab_pair<NX, MODEL>(ex, I, 0, ac, an);
 #pragma unroll 1
         for (int x = cl; x < NX; x += C::COLS_PER_IT) {
           float2* my = st + lds_slot(x);
@@ -141,6 +154,9 @@ __global__ void __launch_bounds__((ResCfg<NX, NY, MODEL>::NT)) k_resident_2d(con
           }
         }
       }
+      ac = an;
+      bp = bc;
+      bc = bn;
       __syncthreads();
     }
     // row-major LDS -> tiled HBM
@@ -165,29 +181,28 @@ hipError_t launch_resident_2d(int nx, int ny, const InstDev* inst, int ninst, co
                               bool y4, int start_axis, hipStream_t stream) {
   if (ninst <= 0) return hipSuccess;
   if (!resident_supported(nx, ny)) return hipErrorInvalidValue;
-#define QHD_RES_LAUNCH(NX_, NY_)                                                                              \
-  if (nx == NX_ && ny == NY_) {                                                                               \
-    constexpr int NT_ = ResCfg<NX_, NY_>::NT, NTQ_ = ResCfg<NX_, NY_, kModelQAA>::NT;                         \
-    if (model == kModelQAA)                                                                                   \
-      QHD_LAUNCH((k_resident_2d<NX_, NY_, kModelQAA, false>), dim3(ninst), dim3(NTQ_), 0, stream,     \
-                         inst, nact, psi, f, tw_nx, tw_ny, max_steps, start_axis);                                       \
-    else if (y4)                                                                                              \
-      QHD_LAUNCH((k_resident_2d<NX_, NY_, kModelQHD, true>), dim3(ninst), dim3(NT_), 0, stream,       \
-                         inst, nact, psi, f, tw_nx, tw_ny, max_steps, start_axis);                                       \
-    else                                                                                                      \
-      QHD_LAUNCH((k_resident_2d<NX_, NY_, kModelQHD, false>), dim3(ninst), dim3(NT_), 0, stream,      \
-                         inst, nact, psi, f, tw_nx, tw_ny, max_steps, start_axis);                                       \
-    return hipGetLastError();                                                                                 \
+  auto go = [&](auto kernel, int threads) {
+    QHD_LAUNCH(kernel, dim3(ninst), dim3(threads), 0, stream, inst, nact, psi, f, tw_nx, tw_ny, max_steps, start_axis);
+    return hipGetLastError();
+  };
+#define QHD_RES_LAUNCH(NX_, NY_, MANY_)                                                              \
+  if (nx == NX_ && ny == NY_ && (!MANY_ || ninst > 256)) {                                           \
+    if (model == kModelQAA)                                                                          \
+      return go(k_resident_2d<NX_, NY_, kModelQAA, false, MANY_>, ResCfg<NX_, NY_, kModelQAA, MANY_>::NT); \
+    if (y4) return go(k_resident_2d<NX_, NY_, kModelQHD, true, MANY_>, ResCfg<NX_, NY_, kModelQHD, MANY_>::NT); \
+    return go(k_resident_2d<NX_, NY_, kModelQHD, false, MANY_>, ResCfg<NX_, NY_, kModelQHD, MANY_>::NT); \
   }
-  QHD_RES_LAUNCH(32, 32)
-  QHD_RES_LAUNCH(32, 64)
-  QHD_RES_LAUNCH(32, 128)
-  QHD_RES_LAUNCH(64, 32)
-  QHD_RES_LAUNCH(64, 64)
-  QHD_RES_LAUNCH(64, 128)
-  QHD_RES_LAUNCH(128, 32)
-  QHD_RES_LAUNCH(128, 64)
-  QHD_RES_LAUNCH(128, 128)
+  QHD_RES_LAUNCH(32, 128, true)
+  QHD_RES_LAUNCH(128, 32, true)
+  QHD_RES_LAUNCH(32, 32, false)
+  QHD_RES_LAUNCH(32, 64, false)
+  QHD_RES_LAUNCH(32, 128, false)
+  QHD_RES_LAUNCH(64, 32, false)
+  QHD_RES_LAUNCH(64, 64, false)
+  QHD_RES_LAUNCH(64, 128, false)
+  QHD_RES_LAUNCH(128, 32, false)
+  QHD_RES_LAUNCH(128, 64, false)
+  QHD_RES_LAUNCH(128, 128, false)
 #undef QHD_RES_LAUNCH
   return hipErrorInvalidValue;
 }
