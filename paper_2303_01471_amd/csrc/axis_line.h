@@ -143,7 +143,7 @@ __device__ __forceinline__ LineTask line_task(const InstDev& I, long long s, lon
   LineTask k;
   k.prev = s > 0 || I.mode == owe;
   k.entry = s == 0 && I.mode == kModeClean;
-  k.active = fix ? I.mode == owe : s < step_limit(I, max_steps);
+  k.active = fix ? pays_owed(I, owe) : s < step_limit(I, max_steps);
   k.cpot = potential_turns<Y4>(I, I.steps_done + s, k.entry);
   return k;
 }

@@ -143,6 +143,12 @@ __device__ __forceinline__ void leapfrog_stage(const InstDev& I, long long j, do
   sched_at_time(I, ((double)step + 0.5 * k) * I.dt, a, b);
 }
 
+// A member whose owed operator (mode `owe`) a fix-up launch pays: only one that goes on.  A
+// finished one keeps its state and mode, as the host's mirror does.
+__device__ __forceinline__ bool pays_owed(const InstDev& I, int owe) {
+  return I.mode == owe && I.steps_done < I.nsteps;
+}
+
 // stages instance I takes in an evolve call capped at max_steps steps (< 0: no cap)
 __device__ __forceinline__ long long step_limit(const InstDev& I, long long max_steps) {
   const long long rem = I.nsteps - I.steps_done;

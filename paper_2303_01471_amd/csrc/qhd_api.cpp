@@ -1076,7 +1076,13 @@ qhd_status qhd_set_potential(qhd_plan p, int32_t i, const double* f, int32_t on_
   c.host[pos].f_min = v;
   c.host[pos].argmin = idx[0];
   p->potential_set[i] = 1;
-  return push_inst(p, i);
+  // of the device's record only what the potential decides: its clock and mode may have moved
+  // without the host (a captured evolve replayed)
+  InstDev* dev = c.dev + pos;
+  HIP_TRY(hipMemcpyAsync(&dev->f_min, &c.host[pos].f_min, sizeof dev->f_min, hipMemcpyHostToDevice, p->internal));
+  HIP_TRY(hipMemcpyAsync(&dev->argmin, &c.host[pos].argmin, sizeof dev->argmin, hipMemcpyHostToDevice, p->internal));
+  HIP_TRY(hipStreamSynchronize(p->internal));
+  return QHD_OK;
 }
 
 qhd_status qhd_set_state(qhd_plan p, int32_t i, const float* psi, int32_t on_device) {

@@ -115,7 +115,7 @@ hipError_t launch_col_pass_2d(int nx, int ny, const InstDev* inst, int ninst, co
                               const double* f, const double2* tw_ny, int s, long long max_steps, int grid_cap,
                               int variant, hipStream_t stream, int model = kModelQHD, bool y4 = true,
                               bool fix = false);
-// after a `fix` launch on the axis owed in mode `owe`: those members become kModeKDone
+// after a `fix` launch on the axis owed in mode `owe`: the members it paid become kModeKDone
 hipError_t launch_fix_mode(InstDev* inst, int ninst, int owe, hipStream_t stream);
 // 1-D: every sub-step of the chunk in one launch
 hipError_t launch_line_steps_1d(int n, const InstDev* inst, int ninst, const int* nact, float2* psi, const double* f,

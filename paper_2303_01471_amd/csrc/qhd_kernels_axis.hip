@@ -187,7 +187,7 @@ k_col_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
   long long begin, end;
   block_share(total, ITEMS, begin, end);
   int cached = -1, cached_n = 0;
-  auto live = [&](const InstDev& I) { return fix ? I.mode == kModeOweY : s < step_limit(I, max_steps); };
+  auto live = [&](const InstDev& I) { return fix ? pays_owed(I, kModeOweY) : s < step_limit(I, max_steps); };
   for (long long g0 = begin; g0 < end; g0 += ITEMS) {
     const long long glast = g0 + ITEMS <= end ? g0 + ITEMS - 1 : end - 1;
     const int i0 = (int)(g0 >> tc_log2), count = (int)(glast >> tc_log2) - i0 + 1;
@@ -578,10 +578,10 @@ __global__ void __launch_bounds__(256) k_observe_col_2d(const InstDev* __restric
   }
 }
 
-// FixUp: the members that owed the axis `owe` have had it applied
+// after a fix-up launch: the members that it paid owe only the potential half step
 __global__ void k_fix_mode(InstDev* __restrict__ inst, int ninst, int owe) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < ninst && inst[i].mode == owe) inst[i].mode = kModeKDone;
+  if (i < ninst && pays_owed(inst[i], owe)) inst[i].mode = kModeKDone;
 }
 
 // ------------------------------------------------------------------------------------

@@ -1,0 +1,82 @@
+"""A plan whose evolve or reset was captured by its caller: the device's state then moves, or
+stays, without the host, and members that have finished, readouts, uploads and a capture that
+is never replayed must not be told apart from a plan that was never captured.
+
+Tolerances: members that a call does not touch, and runs of the same arithmetic, bitwise; a
+member whose owed operator is paid in a launch of its own takes one more rounding each time,
+within 1e-6 of the plain run (as in the other tests of replays)."""
+import numpy as np
+import pytest
+
+import qhd_inputs
+from gpu_helpers import run_gpu
+from paper_2303_01471_amd import qhd as q
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+    q.load_library()
+
+
+def _plan(shape, steps, flags):
+    # a constant schedule: both factors of a step act from the first one on
+    specs = [q.InstanceSpec(shape=shape, nsteps=n, dt=1e-2, sched=q.QHD_SCHED_CONST, sched_p=(0.05, 20.0)) for n in steps]
+    fs = [qhd_inputs.landscape_grid(1400 + k, shape) for k in range(len(steps))]
+    plan = q.Plan(specs, flags=flags)
+    for i, f in enumerate(fs):
+        plan.set_potential(i, f)
+    return plan, specs, fs
+
+
+def _captured(fn):
+    import torch
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=side):
+        fn(side)
+    return g
+
+
+def _states(plan, n):
+    import torch
+    res, psi, _, st = plan.observe(want_psi=True)
+    torch.cuda.synchronize()
+    return res, [plan.psi_of(psi, i).cpu().numpy().copy() for i in range(n)], st
+
+
+@pytest.mark.parametrize("flags", [0, q.QHD_OPT_RESIDENT], ids=["streaming", "resident"])
+@pytest.mark.parametrize("shape", [(64, 64), (32, 128), (128, 32)], ids=str)
+def test_finished_member_keeps_its_state_and_its_potential_can_be_set_again(shape, flags):
+    """Members of 1 and 20 steps: evolve(3) captured and replayed once, two eager steps (which
+    start on either axis), then the finished member's potential again."""
+    want_res, want, _ = _plan_run(shape, (1, 5), flags)
+    plan, _, fs = _plan(shape, (1, 20), flags)
+    try:
+        g = _captured(lambda st: plan.evolve(3, stream=st))
+        g.replay()
+        plan.evolve(1)
+        plan.evolve(1)
+        plan.set_potential(0, fs[0])
+        res, psis, st = _states(plan, 2)
+        assert st == q.QHD_OK
+        assert np.array_equal(psis[0], want[0])
+        assert res[0]["e_f"] == want_res[0]["e_f"] and res[0]["norm"] == want_res[0]["norm"]
+        assert np.max(np.abs(psis[1] - want[1])) <= 1e-6
+        del g
+    finally:
+        plan.close()
+
+
+def _plan_run(shape, steps, flags):
+    plan, specs, fs = _plan(shape, steps, flags)
+    plan.close()
+    res, psis, _, st = run_gpu(specs, fs, flags=flags)
+    assert st == q.QHD_OK
+    return res, psis, st
