@@ -191,7 +191,7 @@ struct qhd_plan_s {
   // axis of the next sub-step of the alternating classes: every member of a class advances
   // by the same number of stages (mod 2) in a call, so one parity serves the plan
   int phase = 0;
-  // an evolve was captured by the caller: replays move the device's axes without the host,
+  // an evolve or a reset was captured by the caller: replays move the device's axes without the host,
   // so every later chunk first pays what a member owes along the other axis
   bool fix_up = false;
   // timing
@@ -1210,6 +1210,11 @@ qhd_status qhd_reset(qhd_plan p, void* stream_v) {
   if (!p) return fail(QHD_EINVAL, "plan is NULL");
   hipStream_t stream = (hipStream_t)stream_v;
   HIP_TRY(hipSetDevice(p->device));
+  // a captured reset may be replayed at any time or never: until then the device's axes are not
+  // the host's
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  HIP_TRY(hipStreamIsCapturing(stream, &cap));
+  if (cap != hipStreamCaptureStatusNone) p->fix_up = true;
   p->phase = 0;
   for (auto& c : p->classes) {
     const int m = (int)c.members.size();

@@ -80,3 +80,25 @@ def _plan_run(shape, steps, flags):
     res, psis, _, st = run_gpu(specs, fs, flags=flags)
     assert st == q.QHD_OK
     return res, psis, st
+
+
+@pytest.mark.parametrize("flags", [0, q.QHD_OPT_RESIDENT], ids=["streaming", "resident"])
+@pytest.mark.parametrize("replays", [0, 1])
+def test_captured_reset(replays, flags):
+    """One step, a captured reset that is not replayed (the state goes on) or is (it starts
+    again), then the rest of the run."""
+    _, want, _ = _plan_run((64, 64), (9, 6), flags)
+    plan, _, fs = _plan((64, 64), (9, 6), flags)
+    try:
+        plan.evolve(1)
+        g = _captured(lambda st: plan.reset(stream=st))
+        for _ in range(replays):
+            g.replay()
+        plan.evolve()
+        res, psis, st = _states(plan, 2)
+        assert st == q.QHD_OK
+        for a, b in zip(psis, want):
+            assert np.max(np.abs(a - b)) <= 1e-6
+        del g
+    finally:
+        plan.close()
