@@ -219,8 +219,10 @@ qhd_status qhd_set_steps_done(qhd_plan plan, int32_t i, int64_t j);
 /* Advance every instance by min(max_steps, remaining) steps (max_steps < 0:
  * to the end).  Asynchronous on `stream`; allocates nothing.  Between evolve
  * calls the state may carry a pending half step, and on 2-D meshes the kinetic
- * factor of the last step along one axis; the result does not depend on how the
- * steps are split into calls.
+ * factor of the last step along one axis; the result of an instance does not depend
+ * on how the steps are split into calls, nor on the other instances (a new state set
+ * after an odd number of steps starts as in a plan of its own; while members of a
+ * class then differ in parity, a sub-step takes a launch for each axis).
  * The steps run in chunks of at most K steps (K = 64 / the most stages per step of
  * any instance; qhd_plan_info reports it).  Inside a chunk every shape class runs
  * on a stream of its own, forked from `stream` and joined back before the chunk's

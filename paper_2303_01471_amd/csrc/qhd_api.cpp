@@ -185,12 +185,9 @@ struct qhd_plan_s {
   // evolve runs in chunks of at most chunk_k steps; a full chunk of every class (chunk
   // plan, passes, commit) is captured once as a graph and replayed (see qhd_evolve)
   int chunk_k = 64;
-  // one captured chunk per starting axis of the alternating classes
+  // one captured chunk per starting axis that the members of the alternating classes share
   hipGraph_t graph[2] = {nullptr, nullptr};
   hipGraphExec_t graph_exec[2] = {nullptr, nullptr};
-  // axis of the next sub-step of the alternating classes: every member of a class advances
-  // by the same number of stages (mod 2) in a call, so one parity serves the plan
-  int phase = 0;
   // an evolve or a reset was captured by the caller: replays move the device's axes without the host,
   // so every later chunk first pays what a member owes along the other axis
   bool fix_up = false;
@@ -295,6 +292,31 @@ int host_nact(const ShapeClass& c, long long ks, long long s) {
   return 0;
 }
 
+// Axes that the members of an alternating class take next (bit a: some member that goes on takes
+// axis a).  Every member advances by the same number of stages (mod 2) in a call and starts a
+// new state on x, so they differ only where some got a new state after an odd number of steps.
+int axes_next(const ShapeClass& c) {
+  int axes = 0;
+  for (auto& I : c.host)
+    if (I.steps_done < I.nsteps) axes |= 1 << I.axis;
+  return axes;
+}
+
+// the axis that all of the plan's alternating classes take next, or -1 where members differ
+int common_axis(qhd_plan p) {
+  int axes = 0;
+  for (auto& c : p->classes)
+    if (c.alt) axes |= axes_next(c);
+  return axes == 3 ? -1 : (axes == 2 ? 1 : 0);
+}
+
+// members of an alternating class that take `axis` in sub-step s of a chunk of at most ks steps
+int host_takes(const ShapeClass& c, long long ks, long long s, int axis) {
+  int n = 0;
+  for (auto& I : c.host) n += s < host_limit(I, ks) && ((I.axis + s) & 1) == axis;
+  return n;
+}
+
 // Launch one chunk of at most ks steps of every class: per class the chunk plan (the
 // members each sub-step visits, from the device step counters), then its sub-steps;
 // then the commit that advances every member by min(ks, remaining) steps.  full: every
@@ -302,9 +324,10 @@ int host_nact(const ShapeClass& c, long long ks, long long s) {
 // otherwise each class issues the sub-steps its members need (from the host mirror).
 // concurrent: each class on its own stream, forked from and joined back to `stream`.
 // timing: every pass launch is bracketed by HIP events (serialised on `stream`).
-// phase: the axis of the first sub-step of the alternating classes.
+// axis: the axis of the first sub-step of the alternating classes, or -1: as the host mirror
+// has it, a launch of each axis for a sub-step in which members differ.
 qhd_status enqueue_chunk(qhd_plan p, long long ks, hipStream_t stream, bool timing, bool concurrent, bool full,
-                         int phase) {
+                         int axis) {
   auto timed_on = [&](hipStream_t st, int fam, double points, auto&& fn) -> hipError_t {
     (void)st;
     hipEvent_t a = nullptr, b = nullptr;
@@ -342,15 +365,24 @@ qhd_status enqueue_chunk(qhd_plan p, long long ks, hipStream_t stream, bool timi
     if (S > kMaxSub) return fail(QHD_EINVAL, "internal: %lld sub-steps in one chunk", S);
     hipStream_t st = concurrent ? c.stream : stream;
     if (concurrent) HIP_TRY(hipStreamWaitEvent(st, p->fork, 0));
+    int axes = axis >= 0 ? 1 << axis : (c.alt ? axes_next(c) : 0);
     if (c.alt && p->fix_up) {
+      // whatever the device's members owe is paid, and all start on one axis
       const int* all = c.nact + kMaxSub;
-      if (phase == 0)
+      const int start = axes == 2 ? 1 : 0;
+      if (start == 0)
         HIP_TRY(launch_col_pass_2d(c.nx, c.ny, c.dev, m, all, c.psi, c.f, c.tw_y, 0, ks, c.cap_col, c.col_variant, st,
                                    c.model, c.y4, true));
       else
         HIP_TRY(launch_row_pass_2d(c.nx, c.ny, c.dev, m, all, c.psi, c.f, c.tw_x, 0, ks, c.cap_row, c.row_points, st,
                                    c.model, c.y4, true));
-      HIP_TRY(launch_fix_mode(c.dev, m, phase == 0 ? kModeOweY : kModeOweX, st));
+      HIP_TRY(launch_set_axis(c.dev, m, start, st));
+      for (auto& I : c.host)
+        if (I.steps_done < I.nsteps) {
+          if (I.mode == (start == 0 ? kModeOweY : kModeOweX)) I.mode = kModeKDone;
+          I.axis = start;
+        }
+      axes = 1 << start;
     }
     HIP_TRY(launch_chunk_plan(c.dev, m, ks, (int)S, c.nact, st));
     if (c.resident || c.ndim == 1) {
@@ -362,7 +394,7 @@ qhd_status enqueue_chunk(qhd_plan p, long long ks, hipStream_t stream, bool timi
       HIP_TRY(timed_on(st, c.ndim == 1 ? c.fam_line : c.fam_res, gps, [&] {
         if (c.ndim == 1)
           return launch_line_steps_1d(c.nx, c.dev, m, c.nact, c.psi, c.f, c.tw_x, ks, p->grid_cap, st);
-        return launch_resident_2d(c.nx, c.ny, c.dev, m, c.nact, c.psi, c.f, c.tw_x, c.tw_y, ks, c.model, c.y4, phase, st);
+        return launch_resident_2d(c.nx, c.ny, c.dev, m, c.nact, c.psi, c.f, c.tw_x, c.tw_y, ks, c.model, c.y4, st);
       }));
     } else {
       for (long long sub = 0; sub < S; ++sub) {
@@ -399,15 +431,18 @@ qhd_status enqueue_chunk(qhd_plan p, long long ks, hipStream_t stream, bool timi
             return launch_lf_col_2d(c.nx, c.ny, c.dev, m, na, c.psi, c.scratch, s, ks, c.cap_col, st);
           }));
         } else if (c.ndim == 2) {
-          if (((phase + sub) & 1) == 0)
-            HIP_TRY(timed_on(st, c.fam_row, pts, [&] {
+          // a member on axis a takes x in the sub-steps of a's parity
+          const int row = 1 << (s & 1), col = 3 - row;
+          auto points = [&](int ax) { return timing && axes == 3 ? (double)host_takes(c, ks, s, ax) * (double)c.points : pts; };
+          if (axes & row)
+            HIP_TRY(timed_on(st, c.fam_row, points(0), [&] {
               return launch_row_pass_2d(c.nx, c.ny, c.dev, m, na, c.psi, c.f, c.tw_x, s, ks, c.cap_row, c.row_points,
-                                        st, c.model, c.y4);
+                                        st, c.model, c.y4 || axes == 3);
             }));
-          else
-            HIP_TRY(timed_on(st, c.fam_col, pts, [&] {
+          if (axes & col)
+            HIP_TRY(timed_on(st, c.fam_col, points(1), [&] {
               return launch_col_pass_2d(c.nx, c.ny, c.dev, m, na, c.psi, c.f, c.tw_y, s, ks, c.cap_col, c.col_variant,
-                                        st, c.model, c.y4);
+                                        st, c.model, c.y4 || axes == 3);
             }));
         }
       }
@@ -419,22 +454,17 @@ qhd_status enqueue_chunk(qhd_plan p, long long ks, hipStream_t stream, bool timi
   }
   for (int ci : joined) HIP_TRY(hipStreamWaitEvent(stream, p->classes[ci].join, 0));
   for (auto& c : p->classes)
-    HIP_TRY(launch_commit(c.dev, (int)c.members.size(), ks, c.alt ? phase : -1, stream));
+    HIP_TRY(launch_commit(c.dev, (int)c.members.size(), ks, c.alt, stream));
   return QHD_OK;
 }
 
-// advance the host mirror as a chunk of ks steps does on the device (one stage or three per
-// step: the axis parity moves by ks either way)
+// advance the host mirror as a chunk of ks steps does on the device
 void mirror_chunk(qhd_plan p, long long ks) {
   for (auto& c : p->classes)
     for (auto& I : c.host) {
       const long long l = host_limit(I, ks);
-      if (l > 0) {
-        I.steps_done += l;
-        I.mode = mode_after(c.alt ? p->phase : -1, l);
-      }
+      if (l > 0) advance(I, l, c.alt);
     }
-  p->phase = (int)((p->phase + ks) & 1);
 }
 
 // ---- launch tuning ----------------------------------------------------------------
@@ -495,8 +525,8 @@ double time_launches(hipStream_t st, hipEvent_t a, hipEvent_t b, int reps, F&& f
 }
 
 // Time the row pass over grid caps and the column pass over variants x grid caps on
-// the class's own buffers (the second sub-step, in which a pass does its whole work, with
-// every member active), keep the fastest.  The state is overwritten; the caller restores it.
+// the class's own buffers (a sub-step in which a pass does its whole work, with every member
+// active), keep the fastest.  The state is overwritten; the caller restores it.
 qhd_status autotune_class(qhd_plan p, ShapeClass& c, double& us_row, double& us_col) {
   const int m = (int)c.members.size();
   static const int caps[] = {512, 1024, 2048, 4096, 8192};
@@ -516,7 +546,7 @@ qhd_status autotune_class(qhd_plan p, ShapeClass& c, double& us_row, double& us_
   for (int rp : row_pts)
     for (int cap : caps) {
       const double t = time_launches(p->internal, a, b, reps, [&] {
-        return launch_row_pass_2d(c.nx, c.ny, c.dev, m, c.nact + kMaxSub, c.psi, c.f, c.tw_x, 1, 2, cap, rp,
+        return launch_row_pass_2d(c.nx, c.ny, c.dev, m, c.nact + kMaxSub, c.psi, c.f, c.tw_x, 2, 3, cap, rp,
                                   p->internal, c.model, c.y4);
       });
       if (t < 0) ok = false;
@@ -591,7 +621,7 @@ qhd_status compare_resident(qhd_plan p, ShapeClass& c, double& us_res, double& u
     return fail(QHD_EDEVICE, "hipEventCreate failed");
   }
   us_res = time_launches(p->internal, a, b, 2, [&] {
-    return launch_resident_2d(c.nx, c.ny, c.dev, m, c.nact + kMaxSub, c.psi, c.f, c.tw_x, c.tw_y, k, c.model, c.y4, 0,
+    return launch_resident_2d(c.nx, c.ny, c.dev, m, c.nact + kMaxSub, c.psi, c.f, c.tw_x, c.tw_y, k, c.model, c.y4,
                               p->internal);
   });
   us_str = time_launches(p->internal, a, b, 2, [&] {
@@ -613,9 +643,9 @@ qhd_status compare_resident(qhd_plan p, ShapeClass& c, double& us_res, double& u
 // Capture one full chunk of chunk_k steps of every class (classes concurrent) on the
 // plan's internal stream; replayed by qhd_evolve for every chunk in which every class
 // still has a member with at least chunk_k steps to go.
-qhd_status build_chunk_graph(qhd_plan p, int phase) {
+qhd_status build_chunk_graph(qhd_plan p, int axis) {
   HIP_TRY(hipStreamBeginCapture(p->internal, hipStreamCaptureModeThreadLocal));
-  qhd_status st = enqueue_chunk(p, p->chunk_k, p->internal, false, true, true, phase);
+  qhd_status st = enqueue_chunk(p, p->chunk_k, p->internal, false, true, true, axis);
   hipGraph_t g = nullptr;
   hipError_t e = hipStreamEndCapture(p->internal, &g);
   if (st != QHD_OK) {
@@ -623,12 +653,12 @@ qhd_status build_chunk_graph(qhd_plan p, int phase) {
     return st;
   }
   if (e != hipSuccess) return fail(QHD_EDEVICE, "graph capture: %s", hipGetErrorString(e));
-  e = hipGraphInstantiate(&p->graph_exec[phase], g, nullptr, nullptr, 0);
+  e = hipGraphInstantiate(&p->graph_exec[axis], g, nullptr, nullptr, 0);
   if (e != hipSuccess) {
     (void)hipGraphDestroy(g);
     return fail(QHD_EDEVICE, "graph instantiate: %s", hipGetErrorString(e));
   }
-  p->graph[phase] = g;
+  p->graph[axis] = g;
   return QHD_OK;
 }
 
@@ -1103,6 +1133,7 @@ qhd_status qhd_set_state(qhd_plan p, int32_t i, const float* psi, int32_t on_dev
     HIP_TRY(launch_import_psi(c.ndim >= 2 ? 2 : 1, c.nx, c.ny * c.nz, p->staging_psi, c.psi + c.host[pos].psi_off,
                               p->internal));
   c.host[pos].mode = kModeClean;
+  c.host[pos].axis = 0;
   p->state_ready[i] = 1;
   return push_inst(p, i);
 }
@@ -1159,18 +1190,20 @@ qhd_status qhd_evolve(qhd_plan p, int64_t max_steps, void* stream_v) {
   const long long full = replay ? rmin / K : 0;
   long long done = 0;
   for (long long ch = 0; ch < full; ++ch, done += K) {
-    if (timing && ch % p->opts.timing_stride == 0) {
-      qhd_status st = enqueue_chunk(p, K, stream, true, false, true, p->phase);
+    const bool timed = timing && ch % p->opts.timing_stride == 0;
+    const int axis = common_axis(p);
+    if (timed || axis < 0) {
+      qhd_status st = enqueue_chunk(p, K, stream, timed, true, axis >= 0, axis);
       if (st != QHD_OK) return st;
     } else {
-      HIP_TRY(hipGraphLaunch(p->graph_exec[p->graph_exec[1] ? p->phase : 0], stream));
+      HIP_TRY(hipGraphLaunch(p->graph_exec[p->graph_exec[1] ? axis : 0], stream));
     }
     mirror_chunk(p, K);
   }
   for (long long ch = 0; done < S; ++ch) {
     const long long ks = std::min(K, S - done);
     qhd_status st = enqueue_chunk(p, ks, stream, timing && ch % p->opts.timing_stride == 0, true, false,
-                                  p->phase);
+                                  -1);
     if (st != QHD_OK) return st;
     mirror_chunk(p, ks);
     done += ks;
@@ -1215,7 +1248,6 @@ qhd_status qhd_reset(qhd_plan p, void* stream_v) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   HIP_TRY(hipStreamIsCapturing(stream, &cap));
   if (cap != hipStreamCaptureStatusNone) p->fix_up = true;
-  p->phase = 0;
   for (auto& c : p->classes) {
     const int m = (int)c.members.size();
     HIP_TRY(launch_fill_psi(c.psi, (long long)m * c.points, (float)(1.0 / std::sqrt((double)c.points)), stream));
@@ -1223,6 +1255,7 @@ qhd_status qhd_reset(qhd_plan p, void* stream_v) {
     for (int k = 0; k < m; ++k) {
       c.host[k].steps_done = 0;
       c.host[k].mode = kModeClean;
+      c.host[k].axis = 0;
       const int i = c.host[k].plan_index;
       p->state_ready[i] = p->inst[i].init_kind == QHD_INIT_UNIFORM;
     }

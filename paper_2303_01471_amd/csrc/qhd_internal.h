@@ -17,13 +17,6 @@ enum : int { kSchemeStrang = 0, kSchemeLie = 1, kSchemeYoshida4 = 2, kSchemeLeap
 enum : int { kModelQHD = 0, kModelQAA = 1 };
 enum : int { kSchedNesterov = 0, kSchedConst = 1, kSchedTable = 2, kSchedLinear = 3 };
 
-// Mode after `lim` > 0 sub-steps of a chunk whose first took axis `start_axis` (-1: not a
-// class of alternating passes): the pass of one axis leaves the other one owed.
-__host__ __device__ inline int mode_after(int start_axis, long long lim) {
-  if (start_axis < 0) return kModePending;
-  return ((start_axis + lim - 1) & 1) == 0 ? kModeOweY : kModeOweX;
-}
-
 // Per-instance parameters as the kernels see them.  One array per shape class.
 struct InstDev {
   double dt;
@@ -40,11 +33,24 @@ struct InstDev {
   long long argmin;      // flat index of x*
   int sched;
   int mode;              // kMode...
-  int plan_index;        // position in the user's batch
+  int axis;              // axis (0 = x, 1 = y) of the next sub-step in a class of alternating passes
   int scheme;            // kSchemeStrang / kSchemeLie / kSchemeYoshida4
-  int model;             // kModelQHD / kModelQAA
   int stages;            // stages per step: 3 for kSchemeYoshida4, else 1
+  int model;             // kModelQHD / kModelQAA
+  int plan_index;        // position in the user's batch
 };
+
+// Clock, mode and axis after `lim` > 0 sub-steps of a chunk (alt: in a class of alternating
+// passes, where the pass of one axis leaves the other one owed).
+__host__ __device__ inline void advance(InstDev& I, long long lim, bool alt) {
+  I.steps_done += lim;
+  if (!alt) {
+    I.mode = kModePending;
+  } else {
+    I.axis = (int)((I.axis + lim) & 1);
+    I.mode = I.axis == 1 ? kModeOweY : kModeOweX;
+  }
+}
 
 // What the spectrum entry point (qhd_spectrum.cpp) reads of one plan instance.
 struct InstanceView {
@@ -74,7 +80,7 @@ struct TimingSink {
 hipError_t launch_row_pass_2d(int nx, int ny, const InstDev* inst, int ninst, const int* nact, float2* psi,
                               const double* f, const double2* tw_nx, int s, long long max_steps,
                               int grid_cap, int points_per_lane, hipStream_t stream, int model = kModelQHD,
-                              bool y4 = true, bool fix = false);
+                              bool general = true, bool fix = false);
 // Sampled pass timing.  When armed, the next pass launch of this host thread records
 // the two events itself: hipExtLaunchKernelGGL stamps them with the dispatch's own start
 // and end (what a kernel trace reports), where events recorded around a launch would
@@ -113,16 +119,18 @@ hipError_t launch_lf_col_2d(int nx, int ny, const InstDev* inst, int ninst, cons
                             long long max_steps, int grid_cap, hipStream_t stream);
 hipError_t launch_col_pass_2d(int nx, int ny, const InstDev* inst, int ninst, const int* nact, float2* psi,
                               const double* f, const double2* tw_ny, int s, long long max_steps, int grid_cap,
-                              int variant, hipStream_t stream, int model = kModelQHD, bool y4 = true,
+                              int variant, hipStream_t stream, int model = kModelQHD, bool general = true,
                               bool fix = false);
-// after a `fix` launch on the axis owed in mode `owe`: the members it paid become kModeKDone
-hipError_t launch_fix_mode(InstDev* inst, int ninst, int owe, hipStream_t stream);
+// (general: members of the fourth-order scheme, or on either axis; fix: only what members that
+// go on owe along the axis)
+// the members that go on take `axis` next; after a `fix` launch along the other one: those it
+// paid become kModeKDone
+hipError_t launch_set_axis(InstDev* inst, int ninst, int axis, hipStream_t stream);
 // 1-D: every sub-step of the chunk in one launch
 hipError_t launch_line_steps_1d(int n, const InstDev* inst, int ninst, const int* nact, float2* psi, const double* f,
                                 const double2* tw, long long max_steps, int grid_cap, hipStream_t stream);
-// start_axis: the axis (0 = x, 1 = y) of the chunk's first sub-step in a class of
-// alternating passes, -1 for the others
-hipError_t launch_commit(InstDev* inst, int ninst, long long max_steps, int start_axis, hipStream_t stream);
+// alt: a class of alternating passes
+hipError_t launch_commit(InstDev* inst, int ninst, long long max_steps, bool alt, hipStream_t stream);
 // Active-member counts of the sub-steps s = 0..S-1 of an evolve chunk capped at
 // max_steps steps: nact[s] = 1 + the last member k with step_limit(inst[k]) > s (0 if
 // none).  Members are sorted by step count, so the prefix is tight for batches evolved
@@ -137,7 +145,7 @@ bool resident_supported(int nx, int ny);
 hipError_t launch_resident_2d(int nx, int ny, const InstDev* inst, int ninst, const int* nact, float2* psi,
                               const double* f,
                               const double2* tw_nx, const double2* tw_ny, long long max_steps, int model,
-                              bool y4, int start_axis, hipStream_t stream);
+                              bool y4, hipStream_t stream);
 
 // 3-D (qhd_kernels_3d.hip), plane layout: x slowest, every (y, z) plane contiguous in 8x8
 // tiles of (y, z).  The x-pass does F_x . V . F_x^{-1} (lines along x, f read), the plane

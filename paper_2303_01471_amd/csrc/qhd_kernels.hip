@@ -319,16 +319,14 @@ __global__ void k_reset_inst(InstDev* __restrict__ inst, int ninst) {
   if (i >= ninst) return;
   inst[i].steps_done = 0;
   inst[i].mode = kModeClean;
+  inst[i].axis = 0;
 }
 
-__global__ void k_commit(InstDev* __restrict__ inst, int ninst, long long max_steps, int start_axis) {
+__global__ void k_commit(InstDev* __restrict__ inst, int ninst, long long max_steps, bool alt) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= ninst) return;
   const long long lim = step_limit(inst[i], max_steps);
-  if (lim > 0) {
-    inst[i].steps_done += lim;
-    inst[i].mode = mode_after(start_axis, lim);
-  }
+  if (lim > 0) advance(inst[i], lim, alt);
 }
 
 // ------------------------------------------------------------------------------------
@@ -684,9 +682,9 @@ hipError_t launch_line_steps_1d(int n, const InstDev* inst, int ninst, const int
   });
 }
 
-hipError_t launch_commit(InstDev* inst, int ninst, long long max_steps, int start_axis, hipStream_t stream) {
+hipError_t launch_commit(InstDev* inst, int ninst, long long max_steps, bool alt, hipStream_t stream) {
   QHD_LAUNCH(k_commit, dim3((ninst + 255) / 256), dim3(256), 0, stream, inst, ninst,
-                     max_steps, start_axis);
+                     max_steps, alt);
   return hipGetLastError();
 }
 

@@ -74,7 +74,7 @@ struct IxShift<Slot16Ix> {
   static constexpr int value = 4;
 };
 
-template <int NX, int P, int MODEL = kModelQHD, bool Y4 = true>
+template <int NX, int P, int MODEL = kModelQHD, bool GEN = true>
 __global__ void __launch_bounds__((RowCfg<NX, P, MODEL>::NT)) __attribute__((amdgpu_waves_per_eu(RowCfg<NX, P, MODEL>::WAVES)))
 k_row_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, int ny_log2,
               float2* __restrict__ psi, const double* __restrict__ f, const double2* __restrict__ twtab, int s,
@@ -128,11 +128,11 @@ k_row_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
     };
     if (i0 != cached) {  // block-uniform
       if (cached >= 0) __syncthreads();  // the previous instance's readers
-      fill_etab<NX, MODEL, Y4>(etab, inst, i0, per_block < ninst - i0 ? per_block : ninst - i0, 0, s);
+      fill_etab<NX, MODEL, GEN>(etab, inst, i0, per_block < ninst - i0 ? per_block : ninst - i0, 0, s);
       __syncthreads();
       cached = i0;
     }
-    const LineTask k = line_task<Y4>(I, s, max_steps, kModeOweX, fix);
+    const LineTask k = line_task<GEN>(I, s, max_steps, 0, fix);
     const double2* tab = etab + (i - i0) * 2 * H;
     if constexpr (MODEL == kModelQAA) {
       double2 x[P];
@@ -166,7 +166,7 @@ k_row_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
 // layout (64-byte pieces).  The general form: short columns, QAA, and a choice of the
 // tuning cache at the other lengths.
 
-template <int NY, int P, int MODEL = kModelQHD, bool Y4 = true>
+template <int NY, int P, int MODEL = kModelQHD, bool GEN = true>
 __global__ void __launch_bounds__((ColCfg<NY, P>::NT)) __attribute__((amdgpu_waves_per_eu(ColCfg<NY, P>::MIN_WAVES)))
 k_col_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, int nx_log2,
               float2* __restrict__ psi, const double* __restrict__ f, const double2* __restrict__ twtab, int s,
@@ -187,13 +187,13 @@ k_col_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
   long long begin, end;
   block_share(total, ITEMS, begin, end);
   int cached = -1, cached_n = 0;
-  auto live = [&](const InstDev& I) { return fix ? pays_owed(I, kModeOweY) : s < step_limit(I, max_steps); };
+  auto live = [&](const InstDev& I) { return line_active<GEN>(I, s, max_steps, 1, fix); };
   for (long long g0 = begin; g0 < end; g0 += ITEMS) {
     const long long glast = g0 + ITEMS <= end ? g0 + ITEMS - 1 : end - 1;
     const int i0 = (int)(g0 >> tc_log2), count = (int)(glast >> tc_log2) - i0 + 1;
     if (i0 != cached || count > cached_n) {
       // the previous items' readers passed the barrier that ends their store
-      fill_etab<NY, MODEL, Y4>(etab, inst, i0, count, 1, s);
+      fill_etab<NY, MODEL, GEN>(etab, inst, i0, count, 1, s);
       cached = i0;
       cached_n = count;
     }
@@ -231,7 +231,7 @@ k_col_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
       const int i = (int)(gc >> tc_log2), tc = (int)(gc & (tcols - 1));
       const InstDev& I = inst[i];
       const int x = tc * 8 + (line & 7);
-      const LineTask k = line_task<Y4>(I, s, max_steps, kModeOweY, fix);
+      const LineTask k = line_task<GEN>(I, s, max_steps, 1, fix);
       const double2* tab = etab + (i - i0) * 2 * H;
       const double* __restrict__ fl = f + I.psi_off;
       float2 reg[P];
@@ -300,7 +300,7 @@ struct ColSplitCfg {
   static constexpr int STRIDE = ColCfg<NY, P>::STRIDE;  // line stride in LDS slots
 };
 
-template <int NY, bool Y4>
+template <int NY, bool GEN>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6)))
 k_col_axis_split(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, int nx_log2,
                  float2* __restrict__ psi, const double* __restrict__ f, const double2* __restrict__ twtab, int s,
@@ -353,7 +353,7 @@ k_col_axis_split(const InstDev* __restrict__ inst, const int* __restrict__ nact_
   for (long long g0 = begin; g0 < end; ++g0) {
     const int i = (int)(g0 >> tc_log2), tc = (int)(g0 & (tcols - 1));
     const InstDev& I = inst[i];
-    const LineTask k = line_task<Y4>(I, s, max_steps, kModeOweY, fix);
+    const LineTask k = line_task<GEN>(I, s, max_steps, 1, fix);
     if (!k.active) continue;  // block-uniform
     const LaneView<float2> pv(psi + I.psi_off + tc * 64, lane);
     const LaneView<double> fv(f + I.psi_off + tc * 64, lane);
@@ -363,7 +363,7 @@ k_col_axis_split(const InstDev* __restrict__ inst, const int* __restrict__ nact_
     if (i != cached) {
       // the previous item's readers passed its last barrier; this item's readers wait for
       // the barrier after the first stage
-      fill_etab<NY, kModelQHD, Y4>(etab, inst, i, 1, 1, s);
+      fill_etab<NY, kModelQHD, GEN>(etab, inst, i, 1, 1, s);
       cached = i;
     }
     typename LinePrec<NY, 1>::V v[P];
@@ -408,7 +408,7 @@ struct ColTwCfg {
   static_assert(TPL % 8 == 0, "tile-wave column pass needs TPL multiple of 8");
 };
 
-template <int NY, int P, int MODEL, bool Y4>
+template <int NY, int P, int MODEL, bool GEN>
 __global__ void __launch_bounds__((ColTwCfg<NY, P>::NT)) __attribute__((amdgpu_waves_per_eu(ColTwCfg<NY, P>::MIN_WAVES)))
 k_col_axis_tw(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, int nx_log2,
               float2* __restrict__ psi, const double* __restrict__ f, const double2* __restrict__ twtab, int s,
@@ -452,12 +452,12 @@ k_col_axis_tw(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
     for (int q = 0; q < P; ++q) in[q] = pv.load(q * W * tcols * 64);
     if (i0 != cached || count > cached_n) {  // block-uniform
       if (cached >= 0) __syncthreads();  // the previous items' readers are done
-      fill_etab<NY, MODEL, Y4>(etab, inst, i0, count, 1, s);
+      fill_etab<NY, MODEL, GEN>(etab, inst, i0, count, 1, s);
       __syncthreads();
       cached = i0;
       cached_n = count;
     }
-    const LineTask k = line_task<Y4>(I, s, max_steps, kModeOweY, fix);
+    const LineTask k = line_task<GEN>(I, s, max_steps, 1, fix);
     const bool active = valid && k.active;
     const double2* tab = etab + (i - i0) * 2 * H;
     if constexpr (MODEL == kModelQAA) {
@@ -578,10 +578,13 @@ __global__ void __launch_bounds__(256) k_observe_col_2d(const InstDev* __restric
   }
 }
 
-// after a fix-up launch: the members that it paid owe only the potential half step
-__global__ void k_fix_mode(InstDev* __restrict__ inst, int ninst, int owe) {
+// the members that go on take `axis` next; those that a fix-up launch paid for the other axis
+// owe only the potential half step
+__global__ void k_set_axis(InstDev* __restrict__ inst, int ninst, int axis) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < ninst && pays_owed(inst[i], owe)) inst[i].mode = kModeKDone;
+  if (i >= ninst || inst[i].steps_done >= inst[i].nsteps) return;
+  if (pays_owed(inst[i], axis == 0 ? kModeOweY : kModeOweX)) inst[i].mode = kModeKDone;
+  inst[i].axis = axis;
 }
 
 // ------------------------------------------------------------------------------------
@@ -641,36 +644,36 @@ struct PassArgs {
   hipStream_t stream;
 };
 
-template <int N, int P, int MODEL, bool Y4>
+template <int N, int P, int MODEL, bool GEN>
 hipError_t go_row(int blocks, int ny, const PassArgs& a) {
   const int lpw = RowCfg<N, P, MODEL>::LPW;
   const int per_block = lpw > ny ? lpw / ny : 1;
   const size_t dyn = (size_t)per_block * 2 * etab_len<N, MODEL>() * sizeof(double2);
-  QHD_LAUNCH((k_row_axis_2d<N, P, MODEL, Y4>), dim3(blocks), dim3(RowCfg<N, P, MODEL>::NT), dyn, a.stream, a.inst, a.nact, ilog2(ny), a.psi,
+  QHD_LAUNCH((k_row_axis_2d<N, P, MODEL, GEN>), dim3(blocks), dim3(RowCfg<N, P, MODEL>::NT), dyn, a.stream, a.inst, a.nact, ilog2(ny), a.psi,
              a.f, a.tw, a.s, a.max_steps, a.fix);
   return hipGetLastError();
 }
 
-template <bool Y4>
+template <bool GEN>
 hipError_t row_pass_qhd(int nx, int ny, int blocks, int points, const PassArgs& a) {
-  if (points == 16 && nx == 128) return go_row<128, 16, kModelQHD, Y4>(blocks, ny, a);
-  if (points == 16 && nx == 256) return go_row<256, 16, kModelQHD, Y4>(blocks, ny, a);
-  if (points == 16 && nx == 512) return go_row<512, 16, kModelQHD, Y4>(blocks, ny, a);
-  QHD_SWITCH_N(nx, { return (go_row<N_, pts_per_lane<N_>(), kModelQHD, Y4>)(blocks, ny, a); });
+  if (points == 16 && nx == 128) return go_row<128, 16, kModelQHD, GEN>(blocks, ny, a);
+  if (points == 16 && nx == 256) return go_row<256, 16, kModelQHD, GEN>(blocks, ny, a);
+  if (points == 16 && nx == 512) return go_row<512, 16, kModelQHD, GEN>(blocks, ny, a);
+  QHD_SWITCH_N(nx, { return (go_row<N_, pts_per_lane<N_>(), kModelQHD, GEN>)(blocks, ny, a); });
 }
 
-template <int N, int P, int MODEL, bool Y4>
+template <int N, int P, int MODEL, bool GEN>
 hipError_t go_col_staged(int blocks, int nx, const PassArgs& a) {
-  QHD_LAUNCH((k_col_axis_2d<N, P, MODEL, Y4>), dim3(blocks), dim3(ColCfg<N, P>::NT), 0, a.stream, a.inst, a.nact,
+  QHD_LAUNCH((k_col_axis_2d<N, P, MODEL, GEN>), dim3(blocks), dim3(ColCfg<N, P>::NT), 0, a.stream, a.inst, a.nact,
              ilog2(nx), a.psi, a.f, a.tw, a.s, a.max_steps, a.fix);
   return hipGetLastError();
 }
 
-template <int N, int MODEL, bool Y4>
+template <int N, int MODEL, bool GEN>
 hipError_t go_col_tw(int blocks, int nx, const PassArgs& a) {
   if constexpr (N >= 64 && (MODEL == kModelQHD || N <= 128)) {
     constexpr int P_ = col_tw_p<N>();
-    QHD_LAUNCH((k_col_axis_tw<N, P_, MODEL, Y4>), dim3(blocks), dim3(ColTwCfg<N, P_>::NT), 0, a.stream, a.inst, a.nact,
+    QHD_LAUNCH((k_col_axis_tw<N, P_, MODEL, GEN>), dim3(blocks), dim3(ColTwCfg<N, P_>::NT), 0, a.stream, a.inst, a.nact,
                ilog2(nx), a.psi, a.f, a.tw, a.s, a.max_steps, a.fix);
     return hipGetLastError();
   } else {
@@ -678,51 +681,59 @@ hipError_t go_col_tw(int blocks, int nx, const PassArgs& a) {
   }
 }
 
-template <bool Y4>
+template <bool GEN>
 hipError_t col_pass_qhd(int nx, int ny, int blocks, int v, const PassArgs& a) {
-  if (v == kColTileWave) QHD_SWITCH_N(ny, { return (go_col_tw<N_, kModelQHD, Y4>)(blocks, nx, a); });
+  if (v == kColTileWave) QHD_SWITCH_N(ny, { return (go_col_tw<N_, kModelQHD, GEN>)(blocks, nx, a); });
   if (v == kColSplit) {
-    QHD_LAUNCH((k_col_axis_split<512, Y4>), dim3(blocks), dim3(ColSplitCfg<512>::NT), 0, a.stream, a.inst, a.nact,
+    QHD_LAUNCH((k_col_axis_split<512, GEN>), dim3(blocks), dim3(ColSplitCfg<512>::NT), 0, a.stream, a.inst, a.nact,
                ilog2(nx), a.psi, a.f, a.tw, a.s, a.max_steps, a.fix);
     return hipGetLastError();
   }
   if (v == kColStaged16)
-    return ny == 256 ? go_col_staged<256, 16, kModelQHD, Y4>(blocks, nx, a)
-                     : go_col_staged<512, 16, kModelQHD, Y4>(blocks, nx, a);
-  QHD_SWITCH_N(ny, { return (go_col_staged<N_, pts_per_lane<N_>(), kModelQHD, Y4>)(blocks, nx, a); });
+    return ny == 256 ? go_col_staged<256, 16, kModelQHD, GEN>(blocks, nx, a)
+                     : go_col_staged<512, 16, kModelQHD, GEN>(blocks, nx, a);
+  QHD_SWITCH_N(ny, { return (go_col_staged<N_, pts_per_lane<N_>(), kModelQHD, GEN>)(blocks, nx, a); });
+}
+
+template <bool GEN>
+hipError_t col_pass_qaa(int nx, int ny, int blocks, const PassArgs& a) {
+  if (ny == 64) return go_col_tw<64, kModelQAA, GEN>(blocks, nx, a);
+  if (ny == 128) return go_col_tw<128, kModelQAA, GEN>(blocks, nx, a);
+  QHD_SWITCH_N(ny, { return (go_col_staged<N_, pts_per_lane<N_>(), kModelQAA, GEN>)(blocks, nx, a); });
 }
 
 }  // namespace
 
 hipError_t launch_row_pass_2d(int nx, int ny, const InstDev* inst, int ninst, const int* nact, float2* psi,
                               const double* f, const double2* tw, int s, long long max_steps, int grid_cap,
-                              int points_per_lane, hipStream_t stream, int model, bool y4, bool fix) {
+                              int points_per_lane, hipStream_t stream, int model, bool general, bool fix) {
   const PassArgs a{inst, nact, psi, f, tw, s, max_steps, fix ? 1 : 0, stream};
+  general = general || fix;
   if (model == kModelQAA) {  // the QAA model runs the symmetric scheme or leapfrog
     const int blocks = pass_blocks_row_2d(nx, ny, ninst, grid_cap, 8);
+    if (general) QHD_SWITCH_N(nx, { return (go_row<N_, pts_per_lane<N_>(), kModelQAA, true>)(blocks, ny, a); });
     QHD_SWITCH_N(nx, { return (go_row<N_, pts_per_lane<N_>(), kModelQAA, false>)(blocks, ny, a); });
   }
   const int blocks = pass_blocks_row_2d(nx, ny, ninst, grid_cap, points_per_lane);
   const int points = row_points_resolve(nx, points_per_lane);
-  return y4 ? row_pass_qhd<true>(nx, ny, blocks, points, a) : row_pass_qhd<false>(nx, ny, blocks, points, a);
+  return general ? row_pass_qhd<true>(nx, ny, blocks, points, a) : row_pass_qhd<false>(nx, ny, blocks, points, a);
 }
 
 hipError_t launch_col_pass_2d(int nx, int ny, const InstDev* inst, int ninst, const int* nact, float2* psi,
                               const double* f, const double2* tw, int s, long long max_steps, int grid_cap,
-                              int variant, hipStream_t stream, int model, bool y4, bool fix) {
+                              int variant, hipStream_t stream, int model, bool general, bool fix) {
   const PassArgs a{inst, nact, psi, f, tw, s, max_steps, fix ? 1 : 0, stream};
+  general = general || fix;
   if (model == kModelQAA) {
     // 64- and 128-point Walsh-Hadamard columns lie in one wavefront of the tile-wave form;
     // the others are staged (in-wave shuffles along a line)
     const int v = ny == 64 || ny == 128 ? kColTileWave : kColStaged;
     const int blocks = pass_blocks_col_2d(nx, ny, ninst, grid_cap, v);
-    if (ny == 64) return go_col_tw<64, kModelQAA, false>(blocks, nx, a);
-    if (ny == 128) return go_col_tw<128, kModelQAA, false>(blocks, nx, a);
-    QHD_SWITCH_N(ny, { return (go_col_staged<N_, pts_per_lane<N_>(), kModelQAA, false>)(blocks, nx, a); });
+    return general ? col_pass_qaa<true>(nx, ny, blocks, a) : col_pass_qaa<false>(nx, ny, blocks, a);
   }
   const int blocks = pass_blocks_col_2d(nx, ny, ninst, grid_cap, variant);
   const int v = col_variant_resolve(ny, variant);
-  return y4 ? col_pass_qhd<true>(nx, ny, blocks, v, a) : col_pass_qhd<false>(nx, ny, blocks, v, a);
+  return general ? col_pass_qhd<true>(nx, ny, blocks, v, a) : col_pass_qhd<false>(nx, ny, blocks, v, a);
 }
 
 hipError_t launch_observe_col_2d(int nx, int ny, const InstDev* inst, int ninst, const float2* psi, const double* f,
@@ -741,8 +752,8 @@ hipError_t launch_observe_col_2d(int nx, int ny, const InstDev* inst, int ninst,
   });
 }
 
-hipError_t launch_fix_mode(InstDev* inst, int ninst, int owe, hipStream_t stream) {
-  QHD_LAUNCH(k_fix_mode, dim3((ninst + 255) / 256), dim3(256), 0, stream, inst, ninst, owe);
+hipError_t launch_set_axis(InstDev* inst, int ninst, int axis, hipStream_t stream) {
+  QHD_LAUNCH(k_set_axis, dim3((ninst + 255) / 256), dim3(256), 0, stream, inst, ninst, axis);
   return hipGetLastError();
 }
 

@@ -49,7 +49,7 @@ __global__ void __launch_bounds__((ResCfg<NX, NY, MODEL, MANY>::NT)) k_resident_
                                                                      const double* __restrict__ f,
                                                                      const double2* __restrict__ twx,
                                                                      const double2* __restrict__ twy,
-                                                                     long long max_steps, int start_axis) {
+                                                                     long long max_steps) {
   const int ninst = *nact_p;  // members active in this sub-step (device, set per chunk)
   using C = ResCfg<NX, NY, MODEL, MANY>;
   constexpr int PX = C::PX, PY = C::PY, TX = C::TX, TY = C::TY, NT = C::NT, RS = C::RS;
@@ -74,6 +74,7 @@ __global__ void __launch_bounds__((ResCfg<NX, NY, MODEL, MANY>::NT)) k_resident_
     const InstDev& I = inst[i];
     const long long lim = step_limit(I, max_steps);
     if (lim <= 0) continue;  // block-uniform
+    const int start_axis = I.axis;
     float2* __restrict__ pg = psi + I.psi_off;
     const double* __restrict__ fg = f + I.psi_off;
     // tiled HBM -> row-major LDS: element 2e and 2e+1 are (x, y) and (x + 1, y), x even
@@ -178,11 +179,11 @@ bool resident_supported(int nx, int ny) {
 hipError_t launch_resident_2d(int nx, int ny, const InstDev* inst, int ninst, const int* nact, float2* psi,
                               const double* f,
                               const double2* tw_nx, const double2* tw_ny, long long max_steps, int model,
-                              bool y4, int start_axis, hipStream_t stream) {
+                              bool y4, hipStream_t stream) {
   if (ninst <= 0) return hipSuccess;
   if (!resident_supported(nx, ny)) return hipErrorInvalidValue;
   auto go = [&](auto kernel, int threads) {
-    QHD_LAUNCH(kernel, dim3(ninst), dim3(threads), 0, stream, inst, nact, psi, f, tw_nx, tw_ny, max_steps, start_axis);
+    QHD_LAUNCH(kernel, dim3(ninst), dim3(threads), 0, stream, inst, nact, psi, f, tw_nx, tw_ny, max_steps);
     return hipGetLastError();
   };
 #define QHD_RES_LAUNCH(NX_, NY_, MANY_)                                                              \
