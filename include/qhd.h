@@ -234,8 +234,12 @@ qhd_status qhd_set_steps_done(qhd_plan plan, int32_t i, int64_t j);
  * bitwise identical to direct launches.  Not with QHD_OPT_NO_GRAPH, and not while
  * `stream` is itself being captured (the passes are then launched directly into
  * the caller's capture; a capture of an odd number of steps may be replayed any
- * number of times, later evolves then pay what is owed along the other axis first).  With QHD_OPT_TIME_PASSES one chunk in timing_stride is
- * launched directly with its classes serialised and every pass timed. */
+ * number of times).  From the first evolve or reset that a caller captured on, replays
+ * may have moved the state unseen: each later evolve begins with three more launches
+ * per 2-D class, which pay what the state owes along the axis it does not start on
+ * (usually nothing), and runs as on any other plan from there.
+ * With QHD_OPT_TIME_PASSES one chunk in timing_stride is launched directly with its
+ * classes serialised and every pass timed. */
 qhd_status qhd_evolve(qhd_plan plan, int64_t max_steps, void *stream);
 
 /* Lowest eigenpairs of the discrete Hamiltonian of 2-D instance i at time t,

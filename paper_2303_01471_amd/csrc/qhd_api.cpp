@@ -189,8 +189,8 @@ struct qhd_plan_s {
   hipGraph_t graph[2] = {nullptr, nullptr};
   hipGraphExec_t graph_exec[2] = {nullptr, nullptr};
   // an evolve or a reset was captured by the caller: replays move the device's axes without the host,
-  // so every later chunk first pays what a member owes along the other axis
-  bool fix_up = false;
+  // so every later call first settles them (settle_axes)
+  bool captured = false;
   // timing
   std::vector<Family> families;
   std::vector<Pending> pending;
@@ -365,25 +365,7 @@ qhd_status enqueue_chunk(qhd_plan p, long long ks, hipStream_t stream, bool timi
     if (S > kMaxSub) return fail(QHD_EINVAL, "internal: %lld sub-steps in one chunk", S);
     hipStream_t st = concurrent ? c.stream : stream;
     if (concurrent) HIP_TRY(hipStreamWaitEvent(st, p->fork, 0));
-    int axes = axis >= 0 ? 1 << axis : (c.alt ? axes_next(c) : 0);
-    if (c.alt && p->fix_up) {
-      // whatever the device's members owe is paid, and all start on one axis
-      const int* all = c.nact + kMaxSub;
-      const int start = axes == 2 ? 1 : 0;
-      if (start == 0)
-        HIP_TRY(launch_col_pass_2d(c.nx, c.ny, c.dev, m, all, c.psi, c.f, c.tw_y, 0, ks, c.cap_col, c.col_variant, st,
-                                   c.model, c.y4, true));
-      else
-        HIP_TRY(launch_row_pass_2d(c.nx, c.ny, c.dev, m, all, c.psi, c.f, c.tw_x, 0, ks, c.cap_row, c.row_points, st,
-                                   c.model, c.y4, true));
-      HIP_TRY(launch_set_axis(c.dev, m, start, st));
-      for (auto& I : c.host)
-        if (I.steps_done < I.nsteps) {
-          if (I.mode == (start == 0 ? kModeOweY : kModeOweX)) I.mode = kModeKDone;
-          I.axis = start;
-        }
-      axes = 1 << start;
-    }
+    const int axes = axis >= 0 ? 1 << axis : (c.alt ? axes_next(c) : 0);
     HIP_TRY(launch_chunk_plan(c.dev, m, ks, (int)S, c.nact, st));
     if (c.resident || c.ndim == 1) {
       // every sub-step of the chunk in one launch, psi in LDS or (1-D) registers (timed as a
@@ -455,6 +437,33 @@ qhd_status enqueue_chunk(qhd_plan p, long long ks, hipStream_t stream, bool timi
   for (int ci : joined) HIP_TRY(hipStreamWaitEvent(stream, p->classes[ci].join, 0));
   for (auto& c : p->classes)
     HIP_TRY(launch_commit(c.dev, (int)c.members.size(), ks, c.alt, stream));
+  return QHD_OK;
+}
+
+// At the start of a call on a plan that was captured: in every alternating class that goes on,
+// what the device's members owe along the other axis is paid, and all take the axis that the
+// mirror has (x where it has both), so that the call's chunks run as on any other plan.  The
+// pass visits the members up to the last that owes, usually none.
+qhd_status settle_axes(qhd_plan p, hipStream_t st) {
+  for (auto& c : p->classes) {
+    const int axes = c.alt ? axes_next(c) : 0, m = (int)c.members.size();
+    if (!axes) continue;
+    const int start = axes == 2 ? 1 : 0, owe = start == 0 ? kModeOweY : kModeOweX;
+    int* owing = c.nact + kMaxSub + 1;
+    HIP_TRY(launch_count_owing(c.dev, m, owe, owing, st));
+    if (start == 0)
+      HIP_TRY(launch_col_pass_2d(c.nx, c.ny, c.dev, m, owing, c.psi, c.f, c.tw_y, 0, 1, c.cap_col, c.col_variant, st,
+                                 c.model, true, true));
+    else
+      HIP_TRY(launch_row_pass_2d(c.nx, c.ny, c.dev, m, owing, c.psi, c.f, c.tw_x, 0, 1, c.cap_row, c.row_points, st,
+                                 c.model, true, true));
+    HIP_TRY(launch_set_axis(c.dev, m, start, st));
+    for (auto& I : c.host)
+      if (I.steps_done < I.nsteps) {
+        if (I.mode == owe) I.mode = kModeKDone;
+        I.axis = start;
+      }
+  }
   return QHD_OK;
 }
 
@@ -876,9 +885,9 @@ qhd_status qhd_plan_create(const qhd_instance* inst, int32_t batch, const qhd_pl
     if (e == hipSuccess) e = hipMalloc(&c.f, sizeof(double) * pts);
     if (e == hipSuccess) e = hipMalloc(&c.partials, sizeof(double) * 3 * (size_t)m * c.stride);
     if (e == hipSuccess) e = hipMalloc(&c.results, sizeof(double) * 3 * (size_t)m);
-    if (e == hipSuccess) e = hipMalloc(&c.nact, sizeof(int) * (kMaxSub + 1));
+    if (e == hipSuccess) e = hipMalloc(&c.nact, sizeof(int) * (kMaxSub + 2));
     if (e == hipSuccess) {
-      std::vector<int> counts(kMaxSub + 1, m);
+      std::vector<int> counts(kMaxSub + 2, m);
       e = hipMemcpy(c.nact, counts.data(), sizeof(int) * counts.size(), hipMemcpyHostToDevice);
     }
     if (e == hipSuccess) e = hipMemcpy(c.dev, c.host.data(), sizeof(InstDev) * m, hipMemcpyHostToDevice);
@@ -1185,8 +1194,12 @@ qhd_status qhd_evolve(qhd_plan p, int64_t max_steps, void* stream_v) {
   // the captured chunk (with pass timing, one in timing_stride of them is launched directly
   // with every pass timed instead); then the rest in direct chunks of at most K steps,
   // each issuing only the sub-steps its members need
-  if (cap != hipStreamCaptureStatusNone) p->fix_up = true;
-  const bool replay = p->graph_exec[0] && cap == hipStreamCaptureStatusNone && !p->fix_up;
+  if (cap != hipStreamCaptureStatusNone) p->captured = true;
+  if (p->captured && S > 0) {
+    qhd_status st = settle_axes(p, stream);
+    if (st != QHD_OK) return st;
+  }
+  const bool replay = p->graph_exec[0] && cap == hipStreamCaptureStatusNone;
   const long long full = replay ? rmin / K : 0;
   long long done = 0;
   for (long long ch = 0; ch < full; ++ch, done += K) {
@@ -1247,7 +1260,7 @@ qhd_status qhd_reset(qhd_plan p, void* stream_v) {
   // the host's
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   HIP_TRY(hipStreamIsCapturing(stream, &cap));
-  if (cap != hipStreamCaptureStatusNone) p->fix_up = true;
+  if (cap != hipStreamCaptureStatusNone) p->captured = true;
   for (auto& c : p->classes) {
     const int m = (int)c.members.size();
     HIP_TRY(launch_fill_psi(c.psi, (long long)m * c.points, (float)(1.0 / std::sqrt((double)c.points)), stream));

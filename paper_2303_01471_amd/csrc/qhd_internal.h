@@ -123,6 +123,8 @@ hipError_t launch_col_pass_2d(int nx, int ny, const InstDev* inst, int ninst, co
                               bool fix = false);
 // (general: members of the fourth-order scheme, or on either axis; fix: only what members that
 // go on owe along the axis)
+// *owing = 1 + the last member that a `fix` launch would pay in mode `owe` (0: none)
+hipError_t launch_count_owing(const InstDev* inst, int ninst, int owe, int* owing, hipStream_t stream);
 // the members that go on take `axis` next; after a `fix` launch along the other one: those it
 // paid become kModeKDone
 hipError_t launch_set_axis(InstDev* inst, int ninst, int axis, hipStream_t stream);

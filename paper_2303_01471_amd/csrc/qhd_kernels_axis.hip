@@ -578,6 +578,21 @@ __global__ void __launch_bounds__(256) k_observe_col_2d(const InstDev* __restric
   }
 }
 
+__global__ void __launch_bounds__(256) k_count_owing(const InstDev* __restrict__ inst, int ninst, int owe,
+                                                     int* __restrict__ owing) {
+  __shared__ int last[256];
+  int n = 0;
+  for (int i = threadIdx.x; i < ninst; i += 256)
+    if (pays_owed(inst[i], owe)) n = i + 1;
+  last[threadIdx.x] = n;
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if ((int)threadIdx.x < o) last[threadIdx.x] = max(last[threadIdx.x], last[threadIdx.x + o]);
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *owing = last[0];
+}
+
 // the members that go on take `axis` next; those that a fix-up launch paid for the other axis
 // owe only the potential half step
 __global__ void k_set_axis(InstDev* __restrict__ inst, int ninst, int axis) {
@@ -750,6 +765,11 @@ hipError_t launch_observe_col_2d(int nx, int ny, const InstDev* inst, int ninst,
                  f, tw_ny, out_psi, out_rho, partials, stride);
     return hipGetLastError();
   });
+}
+
+hipError_t launch_count_owing(const InstDev* inst, int ninst, int owe, int* owing, hipStream_t stream) {
+  QHD_LAUNCH(k_count_owing, dim3(1), dim3(256), 0, stream, inst, ninst, owe, owing);
+  return hipGetLastError();
 }
 
 hipError_t launch_set_axis(InstDev* inst, int ninst, int axis, hipStream_t stream) {
