@@ -78,10 +78,13 @@ qhd_status qhd_rqp_set_objective(qhd_rqp h, int32_t i, const double *Q, const do
 
 /* Advance every instance by min(max_steps, remaining) steps (max_steps < 0: to the
  * end).  Asynchronous on `stream`; allocates nothing.  QHD_ESTATE if an objective is
- * missing.  The leading axes whose (r+1)^K points fit 6561 run as one pass through
- * LDS (the 9^5 lattice: axes 1-4 fused, axis 5 alone), with the values of K separate
- * passes; the environment variable QHD_RQP_UNFUSED=1, read at creation, keeps one pass
- * per axis. */
+ * missing.  The axes are split into sets whose lattice fits LDS, each one pass (the 9^5
+ * lattice: axes 1-3 and 4-5), with the values of one pass per axis; the environment
+ * variable QHD_RQP_UNFUSED=1, read at creation, keeps one pass per axis.
+ * A call may be captured by the caller; the schedule coefficients of its steps are then
+ * part of the capture.  It leaves every kinetic factor applied, so it may be replayed
+ * after a reset or after other calls, any number of times; steps_done counts the calls
+ * made, not the replays. */
 qhd_status qhd_rqp_evolve(qhd_rqp h, int64_t max_steps, void *stream);
 
 /* Readouts of every instance into host `out` (batch entries); optional device outputs:

@@ -33,7 +33,6 @@ struct qhd_rqp_s {
   double* U = nullptr;      // eigenvectors of A' (columns), row-major NP x NP
   double* lam = nullptr;    // eigenvalues of A'
   double* tab = nullptr;    // per step of a run: axis matrix and potential coefficient
-  float2* closed = nullptr; // readouts: the state with the owed set applied, `group` instances
   double* part = nullptr;   // readouts: per-block sums and marginals
   double* amp = nullptr;    // discrete Gaussian amplitudes of one axis
   double* fmin = nullptr;
@@ -45,13 +44,13 @@ struct qhd_rqp_s {
   std::vector<char> has_obj;
   long long steps_done = 0;
   bool pending = false;     // the trailing potential half step of the last step is owed
-  // The axes in sets, swept up and down in turn.  With several sets the last set of the last
-  // step is owed after a call (its matrix and the next step's are one pass); -1: nothing is.
+  // The axes in sets, swept up and down in turn: inside a call the last set of a step is one pass
+  // with the first of the next.  A call ends with its last set applied: what the device holds
+  // is then the same whether calls are eager, captured, replayed or reset in between.
   std::vector<RqpSet> sets;
+  int next = 0;             // the set that the next step begins with
   RqpSteps steps{};         // host copy of the run being formed
   bool unfused = false;     // each axis of a set in passes of its own, the same values
-  int owed = -1;
-  int group = 0;
 };
 
 namespace {
@@ -169,14 +168,13 @@ void release(qhd_rqp h) {
   if (!h) return;
   (void)hipSetDevice(h->device);
   for (void* p : {(void*)h->psi, (void*)h->f, (void*)h->Qb, (void*)h->U, (void*)h->lam, (void*)h->tab, (void*)h->amp,
-                  (void*)h->fmin, (void*)h->amin, (void*)h->sums, (void*)h->closed, (void*)h->part})
+                  (void*)h->fmin, (void*)h->amin, (void*)h->sums, (void*)h->part})
     if (p) (void)hipFree(p);
   if (h->host_sums) (void)hipHostFree(h->host_sums);
   delete h;
 }
 
 constexpr int kNarrow = 8;                       // inner points of a trailing tile at least (64 B)
-constexpr long long kClosedBytes = 256ll << 20;  // readout copy (or one instance, if that is larger)
 
 long long ipow(int b, int e) {
   long long v = 1;
@@ -232,10 +230,10 @@ std::vector<RqpSet> make_sets(int NP, int d, long long total) {
 }
 
 // One pass of set i: mat0 (or NULL), then `rounds` steps from mat1 on.
-hipError_t set_pass(qhd_rqp h, int i, const float2* src, float2* dst, const double* f, long long total,
-                    const double* mat0, const double* mat1, int rounds, hipStream_t st) {
+hipError_t set_pass(qhd_rqp h, int i, long long total, const double* mat0, const double* mat1, int rounds,
+                    hipStream_t st) {
   const RqpSet& S = h->sets[i];  // (total: whole instances)
-  if (!h->unfused) return rqp_pass(h->NP, src, dst, f, S, total, mat0, mat1, rounds, st);
+  if (!h->unfused) return rqp_pass(h->NP, h->psi, h->f, S, total, mat0, mat1, rounds, st);
   // the reference form of the same arithmetic: one pass per axis and matrix
   hipError_t e = hipSuccess;
   for (int rd = mat0 ? -1 : 0; rd < rounds; ++rd)
@@ -243,8 +241,7 @@ hipError_t set_pass(qhd_rqp h, int i, const float2* src, float2* dst, const doub
       const double* m = rd < 0 ? mat0 : mat1 + (long long)rd * kRqpMatStride;
       const RqpSet axis = make_set(h->NP, S.first + k, 1, total);
       const bool pot = rd >= 0 && k == 0;  // the potential factor comes before the first axis
-      e = rqp_pass(h->NP, src, dst, f, axis, total, pot ? nullptr : m, m, pot ? 1 : 0, st);
-      src = dst;
+      e = rqp_pass(h->NP, h->psi, h->f, axis, total, pot ? nullptr : m, m, pot ? 1 : 0, st);
     }
   return e;
 }
@@ -316,17 +313,9 @@ qhd_status qhd_rqp_create(const qhd_rqp_desc* desc, int32_t batch, qhd_rqp* out)
   if (e == hipSuccess) e = hipMalloc(&h->U, sizeof(double) * NP * NP);
   if (e == hipSuccess) e = hipMalloc(&h->lam, sizeof(double) * NP);
   if (e == hipSuccess) e = hipMalloc(&h->tab, sizeof(double) * kRqpStepRun * kRqpMatStride);
-  if (h->sets.size() > 1) {
-    h->group = (int)std::max<long long>(1, std::min<long long>(batch, kClosedBytes / (long long)(sizeof(float2) * h->N)));
-    if (e == hipSuccess) e = hipMalloc(&h->closed, sizeof(float2) * h->N * h->group);
-  }
-  const int most_group = h->group ? h->group : batch;
-  const int tail_group = batch % most_group;
-  size_t parts = 0;  // (a smaller last group takes more blocks per instance)
-  for (int n : {batch, most_group, tail_group})
-    if (n && rqp_observe_blocks(h->N, n) > 1)
-      parts = std::max(parts, (size_t)n * rqp_observe_blocks(h->N, n) * std::max(3, d * NP));
-  if (e == hipSuccess && parts) e = hipMalloc(&h->part, sizeof(double) * parts);
+  const int blocks = rqp_observe_blocks(h->N, batch);
+  if (e == hipSuccess && blocks > 1)
+    e = hipMalloc(&h->part, sizeof(double) * batch * (size_t)blocks * std::max(3, d * NP));
   if (e == hipSuccess) e = hipMalloc(&h->amp, sizeof(double) * NP);
   if (e == hipSuccess) e = hipMalloc(&h->fmin, sizeof(double) * batch);
   if (e == hipSuccess) e = hipMalloc(&h->amin, sizeof(long long) * batch);
@@ -394,10 +383,6 @@ qhd_status qhd_rqp_evolve(qhd_rqp h, int64_t max_steps, void* stream_v) {
   const long long rem = d.nsteps - h->steps_done;
   const long long n = (max_steps < 0 || max_steps > rem) ? rem : max_steps;
   const long long total = h->N * h->batch;
-  // A replay of a captured call starts where the last one ended: a call of an odd number of
-  // steps then ends on the set it began with, its last step's sets not merged with the next.
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  RQP_TRY(hipStreamIsCapturing(st, &cap));
   const int last = (int)h->sets.size() - 1;
   for (long long s0 = 0; s0 < n; s0 += kRqpStepRun - 1) {
     const int run = (int)std::min<long long>(n - s0, kRqpStepRun - 1);
@@ -408,24 +393,18 @@ qhd_status qhd_rqp_evolve(qhd_rqp h, int64_t max_steps, void* stream_v) {
     RQP_TRY(rqp_matrices(h->NP, h->U, h->lam, h->steps, run + 1, h->tab, st));
     if (last == 0) {
       // one set holds every axis: the run's steps in one pass
-      RQP_TRY(set_pass(h, 0, h->psi, h->psi, h->f, total, nullptr, h->tab + kRqpMatStride, run, st));
+      RQP_TRY(set_pass(h, 0, total, nullptr, h->tab + kRqpMatStride, run, st));
       continue;
     }
     for (int s = 0; s < run; ++s) {
       const double* now = h->tab + (long long)(s + 1) * kRqpMatStride;
-      const bool keep = cap != hipStreamCaptureStatusNone && (n & 1) && s0 + s == n - 1 && h->owed >= 0;
-      int from = h->owed < 0 ? 0 : h->owed;
-      if (keep) {
-        RQP_TRY(set_pass(h, from, h->psi, h->psi, h->f, total, now - kRqpMatStride, nullptr, 0, st));
-        from = last - from;
-      }
-      RQP_TRY(set_pass(h, from, h->psi, h->psi, h->f, total, keep || h->owed < 0 ? nullptr : now - kRqpMatStride, now, 1,
-                       st));
+      const int from = h->next;
+      RQP_TRY(set_pass(h, from, total, s0 + s > 0 ? now - kRqpMatStride : nullptr, now, 1, st));
       const int dir = from == 0 ? 1 : -1;
-      for (int k = from + dir; k > 0 && k < last; k += dir)
-        RQP_TRY(set_pass(h, k, h->psi, h->psi, h->f, total, now, nullptr, 0, st));
-      h->owed = last - from;
+      for (int k = from + dir; k > 0 && k < last; k += dir) RQP_TRY(set_pass(h, k, total, now, nullptr, 0, st));
+      h->next = last - from;
     }
+    if (s0 + run == n) RQP_TRY(set_pass(h, h->next, total, h->tab + (long long)run * kRqpMatStride, nullptr, 0, st));
   }
   if (n > 0) {
     h->steps_done += n;
@@ -449,26 +428,9 @@ qhd_status qhd_rqp_observe(qhd_rqp h, void* stream_v, qhd_rqp_obs* out, float* m
     close_turns = 0.5 * h->desc.dt * b * 0.15915494309189533577;
   }
   const int d = h->desc.dim, NP = h->NP;
-  // the owed set is applied on a copy, a group of instances at a time
-  if (h->owed >= 0) {
-    step_table(h, h->steps_done - 1, 1, true);
-    RQP_TRY(rqp_matrices(NP, h->U, h->lam, h->steps, 1, h->tab, st));
-  }
-  const int group = h->owed >= 0 ? h->group : h->batch;
-  for (int i = 0; i < h->batch; i += group) {
-    const int count = std::min(group, h->batch - i);
-    const size_t at = (size_t)i * h->N;
-    const float2* z = h->psi + at;
-    if (h->owed >= 0) {
-      RQP_TRY(set_pass(h, h->owed, z, h->closed, h->f + at, h->N * count, h->tab, nullptr, 0, st));
-      z = h->closed;
-    }
-    RQP_TRY(rqp_observe(z, h->f + at, h->N, count, h->fmin + i, h->desc.min_tol, h->part, h->sums + 3 * (size_t)i,
-                        prob_dev ? prob_dev + at : nullptr, psi_dev ? reinterpret_cast<float2*>(psi_dev) + at : nullptr,
-                        close_turns, st));
-    if (marginals_dev)
-      RQP_TRY(rqp_marginals(NP, z, h->N, d, count, h->part, marginals_dev + (size_t)i * d * NP, st));
-  }
+  RQP_TRY(rqp_observe(h->psi, h->f, h->N, h->batch, h->fmin, h->desc.min_tol, h->part, h->sums, prob_dev,
+                      reinterpret_cast<float2*>(psi_dev), close_turns, st));
+  if (marginals_dev) RQP_TRY(rqp_marginals(NP, h->psi, h->N, d, h->batch, h->part, marginals_dev, st));
   RQP_TRY(hipMemcpyAsync(h->host_sums, h->sums, sizeof(double) * 3 * h->batch, hipMemcpyDeviceToHost, st));
   RQP_TRY(hipStreamSynchronize(st));
   qhd_status status = QHD_OK;
@@ -495,7 +457,7 @@ qhd_status qhd_rqp_reset(qhd_rqp h, void* stream_v) {
   RQP_TRY(rqp_init(h->psi, h->amp, h->desc.dim, h->NP, h->N, h->batch, (hipStream_t)stream_v));
   h->steps_done = 0;
   h->pending = false;
-  h->owed = -1;
+  h->next = 0;
   return QHD_OK;
 }
 

@@ -31,9 +31,9 @@ struct RqpSet {
 // matrices and potential coefficients of `count` steps into tab[count][kRqpMatStride]
 hipError_t rqp_matrices(int NP, const double* U, const double* lam, const RqpSteps& steps, int count, double* tab,
                         hipStream_t st);
-// One pass over whole instances (src may be dst): mat0 (or NULL) along the set's axes, then
+// One pass over whole instances: mat0 (or NULL) along the set's axes, then
 // `rounds` times the potential factor and the matrix of the next entry of mat1.
-hipError_t rqp_pass(int NP, const float2* src, float2* dst, const double* f, const RqpSet& S, long long total_points,
+hipError_t rqp_pass(int NP, float2* psi, const double* f, const RqpSet& S, long long total_points,
                     const double* mat0, const double* mat1, int rounds, hipStream_t st);
 // blocks per instance of the readouts: about 2048 blocks over the batch, 1024 points or more each
 inline int rqp_observe_blocks(long long N, int batch) {

@@ -172,7 +172,7 @@ __device__ __forceinline__ void line_apply(const double* __restrict__ Mg, float2
 // against 87 us a step with three; with five the line spills: 193); for NP = 16 the bound
 // spills (16^3: 14.8 against 12.8).
 template <int NP, int NT, bool LEAD>
-__global__ void __launch_bounds__(NT, NT == 256 && NP <= 9 ? 4 : 1) k_rqp_pass(const float2* src, float2* dst,
+__global__ void __launch_bounds__(NT, NT == 256 && NP <= 9 ? 4 : 1) k_rqp_pass(float2* __restrict__ psi,
                                                 const double* __restrict__ f, RqpSet S, long long total_points,
                                                 long long tiles, const double* __restrict__ mat0, const double* __restrict__ mat1,
                                                 int rounds) {
@@ -200,11 +200,11 @@ __global__ void __launch_bounds__(NT, NT == 256 && NP <= 9 ? 4 : 1) k_rqp_pass(c
     double fv[PTS];
     // Offset of element e of the tile from its base (false: none there).  The base is the
     // same for the whole block and a byte offset fits 32 bits, so an address is one register.
-    const float2* srct = src + base;
+    float2* __restrict__ zt = psi + base;
     const double* __restrict__ ft = f + base;
-    float2* dstt = dst + base;
-    auto at = [](const auto* p, unsigned off) {
-      return reinterpret_cast<decltype(p)>(reinterpret_cast<const char*>(p) + off * (unsigned)sizeof(*p));
+    auto at = [](auto* p, unsigned off) {
+      using B = typename std::conditional<std::is_const<typename std::remove_pointer<decltype(p)>::type>::value, const char, char>::type;
+      return reinterpret_cast<decltype(p)>(reinterpret_cast<B*>(p) + off * (unsigned)sizeof(*p));
     };
     auto point = [&](int e, unsigned& off) {
       if constexpr (LEAD) {
@@ -221,7 +221,7 @@ __global__ void __launch_bounds__(NT, NT == 256 && NP <= 9 ? 4 : 1) k_rqp_pass(c
     for (int i = 0; i < PTS; ++i) {
       unsigned off;
       const bool in = point(tid + i * NT, off);
-      v[i] = in ? *at(srct, off) : make_float2(0.0f, 0.0f);
+      v[i] = in ? *at(zt, off) : make_float2(0.0f, 0.0f);
       fv[i] = rounds > 0 && in ? *at(ft, off) : 0.0;
     }
     auto axes = [&](const double* __restrict__ M) {
@@ -268,7 +268,7 @@ __global__ void __launch_bounds__(NT, NT == 256 && NP <= 9 ? 4 : 1) k_rqp_pass(c
 #pragma unroll
     for (int i = 0; i < PTS; ++i) {
       unsigned off;
-      if (point(again + i * NT, off)) *const_cast<float2*>(at(dstt, off)) = v[i];
+      if (point(again + i * NT, off)) *at(zt, off) = v[i];
     }
     __syncthreads();  // the next tile reuses the LDS
   }
@@ -460,7 +460,7 @@ hipError_t matrices_np(const double* U, const double* lam, const RqpSteps& steps
 }
 
 template <int NP, int NT, bool LEAD>
-hipError_t pass_np(const float2* src, float2* dst, const double* f, const RqpSet& S, long long total_points,
+hipError_t pass_np(float2* psi, const double* f, const RqpSet& S, long long total_points,
                    const double* mat0, const double* mat1, int rounds, hipStream_t st) {
   const int points = LEAD ? S.span : S.n * S.span;
   if (points < NP || points > NT * NP || points % NP != 0 || points > kRqpTilePoints ||
@@ -470,18 +470,18 @@ hipError_t pass_np(const float2* src, float2* dst, const double* f, const RqpSet
   long long blocks = (tiles + 7) / 8;
   if (blocks > 8192) blocks = 8192;
   hipLaunchKernelGGL((k_rqp_pass<NP, NT, LEAD>), dim3((unsigned)(8 * blocks)), dim3(NT), sizeof(float2) * points, st,
-                     src, dst, f, S, total_points, tiles, mat0, mat1, rounds);
+                     psi, f, S, total_points, tiles, mat0, mat1, rounds);
   return hipGetLastError();
 }
 
 template <int NP>
-hipError_t pass_any(const float2* src, float2* dst, const double* f, const RqpSet& S, long long total_points,
+hipError_t pass_any(float2* psi, const double* f, const RqpSet& S, long long total_points,
                     const double* mat0, const double* mat1, int rounds, hipStream_t st) {
   if (S.threads == kThreads)
-    return S.first == 0 ? pass_np<NP, kThreads, true>(src, dst, f, S, total_points, mat0, mat1, rounds, st)
-                        : pass_np<NP, kThreads, false>(src, dst, f, S, total_points, mat0, mat1, rounds, st);
-  return S.first == 0 ? pass_np<NP, 1024, true>(src, dst, f, S, total_points, mat0, mat1, rounds, st)
-                      : pass_np<NP, 1024, false>(src, dst, f, S, total_points, mat0, mat1, rounds, st);
+    return S.first == 0 ? pass_np<NP, kThreads, true>(psi, f, S, total_points, mat0, mat1, rounds, st)
+                        : pass_np<NP, kThreads, false>(psi, f, S, total_points, mat0, mat1, rounds, st);
+  return S.first == 0 ? pass_np<NP, 1024, true>(psi, f, S, total_points, mat0, mat1, rounds, st)
+                      : pass_np<NP, 1024, false>(psi, f, S, total_points, mat0, mat1, rounds, st);
 }
 
 template <int NP>
@@ -529,9 +529,9 @@ hipError_t rqp_matrices(int NP, const double* U, const double* lam, const RqpSte
   QHD_RQP_SWITCH(NP, matrices_np<NP_>(U, lam, steps, count, tab, st))
 }
 
-hipError_t rqp_pass(int NP, const float2* src, float2* dst, const double* f, const RqpSet& S, long long total_points,
+hipError_t rqp_pass(int NP, float2* psi, const double* f, const RqpSet& S, long long total_points,
                     const double* mat0, const double* mat1, int rounds, hipStream_t st) {
-  QHD_RQP_SWITCH(NP, pass_any<NP_>(src, dst, f, S, total_points, mat0, mat1, rounds, st))
+  QHD_RQP_SWITCH(NP, pass_any<NP_>(psi, f, S, total_points, mat0, mat1, rounds, st))
 }
 
 hipError_t rqp_marginals(int NP, const float2* psi, long long N, int d, int batch, double* part, float* marg,
