@@ -75,45 +75,68 @@ __device__ __forceinline__ void mul_field(double2 (&reg)[P], int t, const double
   for (int q = 0; q < P; ++q) reg[q] = cmul_fd(reg[q], b[__builtin_popcount(q)]);
 }
 
-// Where a line works in FP64 beside its twiddle and factor products: at the position-space
-// ends of the line operators (V: the last inverse and the first forward stage and the
-// potential factor between them) or at the frequency-space ends (K: the last forward and the
-// first inverse stage and the kinetic factor).  Early in a run every line of a near-uniform
-// state concentrates into one coefficient and is rounded alike, late the state is localised;
-// FP32 rounding of such values moves the norm.  K for all lines but those of 128 points and the
-// columns of 256, where the late phase decides: largest norm drift of the 128^2 members of the 768-instance batch
-// 1.3e-5 per 1e4 steps with K, 6.6e-6 with V.  (256^2: 9.3e-6 with neither, 5.1e-6 with K; with V
-// the near-uniform phase of 32^2 and 256^2 instances drifts up to 1.5 times as far in its first
-// 200 steps as with K.)  Either costs 2 % at 512 points, nothing that is seen below.
-template <int N, int AXIS>
+// Where a line works in FP64 beside its twiddle and factor products.  K, the frequency-space ends
+// of the line operators (the last forward and the first inverse stage and the kinetic factor):
+// always.  V, the position-space ends (the last inverse and the first forward stage and the
+// potential factor): lines of 128 and 256 points.  XI, the stages and exchanges between on the
+// way back to position space: 128 points.
+// Early in a run every line of a near-uniform state concentrates into one coefficient and is
+// rounded alike, late the state is localised; FP32 rounding of such values moves the norm, and
+// alike-rounded values move it all one way.  Where all four ends are FP64 the two exchanges are
+// what is left: a value that comes back through both is rounded twice and walks by a unit in the
+// last place per pass, through one it comes back to itself.
+// Largest norm drift of the 768-instance batch per 1e4 steps, and state error of 8 x 128^2 after
+// 600 steps (4 x 256^2 after 400): separate axis passes (K for columns, all four ends for
+// 128-point rows) 128^2 5.5e-6, 4.3e-6; 256^2 5.2e-6, 3.4e-6.  128^2 with K alone 1.3e-5; V
+// alone 6.9e-6, 3.4e-6; both ends 1.5e-5, 2.1e-6; and XI 4.9e-6, 1.9e-6 (the exchange towards
+// frequency space instead 4.0e-6, 1.4e-6 but 8 % longer; both 3.7e-6, 1.1e-6 and 11 %).  256^2
+// with K 8.9e-6, 3.2e-6, with both ends 4.0e-6, 2.7e-6 (3 % longer).  512^2 with K 4.1e-6 (5.4e-6
+// separate; both ends 2.6e-6, 3 % longer).
+template <int N>
 struct LinePrec {
-  static constexpr bool LATE = N == 128 || (N == 256 && AXIS == 1);
-  using V = typename std::conditional<LATE, double2, float2>::type;
-  using K = typename std::conditional<LATE, float2, double2>::type;
+  using V = typename std::conditional<N == 128 || N == 256, double2, float2>::type;
+  using K = double2;
+  using XI = typename std::conditional<N == 128, double2, float2>::type;
+};
+
+// Twiddles of a line.  128 points with 16 per lane: radices 8 and 16 in this order: the first
+// stage's scatter then puts neighbouring lanes on other banks where a line is a column of an
+// array of odd stride (512 resident 128^2, us per step, radices 16 and 8: 56, so 46; rows and
+// streamed columns 1 % longer).
+template <int N, int P>
+using LineTwiddles = typename std::conditional<N == 128 && P == 16, TwiddlesLds<N, P, TwPow<N, P>::value, 8>,
+                                               TwiddlesFor<N, P>>::type;
+template <int N, int P>
+struct LineTwSize {
+  static constexpr int value = TwLdsSize<N, P>::value;
+};
+template <>
+struct LineTwSize<128, 16> {
+  static constexpr int value = LineTwiddles<128, 16>::kEntries;
 };
 
 // F^{-1} E F of one line, from `in` to `out` (float2 or double2: the type of the first and
 // of the last stage; they may be the same array)
-template <int N, int P, int AXIS, bool BLOCK_SYNC, typename IX, typename TIN, typename TOUT, typename TW>
+template <int N, int P, bool BLOCK_SYNC, typename IX, typename TIN, typename TOUT, typename TW>
 __device__ __forceinline__ void line_kinetic(TIN (&in)[P], TOUT (&out)[P], int t, const TW& tw,
                                              float2* __restrict__ lds, const double2* __restrict__ tab) {
-  typename LinePrec<N, AXIS>::K k[P];
+  typename LinePrec<N>::K k[P];
   line_fft_io<N, P, -1, BLOCK_SYNC, IX>(in, k, t, tw, lds);
   mul_kinetic<N, P>(k, t, tab);
-  line_fft_io<N, P, +1, BLOCK_SYNC, IX>(k, out, t, tw, lds);
+  line_fft_io<N, P, +1, BLOCK_SYNC, IX, typename LinePrec<N>::XI>(k, out, t, tw, lds);
 }
 
 // A line's whole pass: the owed operator, the potential factor (fget(q): f of slot q) and
 // this step's operator; fix: the owed operator alone.  (fix is set only in general launches, but
 // tested in all: the branch keeps the loads of f behind the owed operator.  Without it 128-point
 // rows take 174 registers instead of 148, and 1024 x 128^2 ran 9 % longer.)
-template <int N, int P, int AXIS, bool BLOCK_SYNC, typename IX, typename TW, typename F>
+template <int N, int P, bool BLOCK_SYNC, typename IX, typename TW, typename F>
 __device__ __forceinline__ void line_pass(float2 (&reg)[P], int t, const TW& tw, float2* __restrict__ lds,
                                           const double2* __restrict__ tab, bool prev, double cpot, int fix, F&& fget) {
   constexpr int H = etab_len<N, kModelQHD>();
-  typename LinePrec<N, AXIS>::V x[P];
+  typename LinePrec<N>::V x[P];
   if (prev) {
-    line_kinetic<N, P, AXIS, BLOCK_SYNC, IX>(reg, x, t, tw, lds, tab);
+    line_kinetic<N, P, BLOCK_SYNC, IX>(reg, x, t, tw, lds, tab);
   } else {
 #pragma unroll
     for (int q = 0; q < P; ++q) assign(x[q], reg[q]);
@@ -121,7 +144,7 @@ __device__ __forceinline__ void line_pass(float2 (&reg)[P], int t, const TW& tw,
   if (!fix) {
 #pragma unroll
     for (int q = 0; q < P; ++q) x[q] = cmul_fd(x[q], phase_turns_d(cpot * fget(q)));
-    line_kinetic<N, P, AXIS, BLOCK_SYNC, IX>(x, x, t, tw, lds, tab + H);
+    line_kinetic<N, P, BLOCK_SYNC, IX>(x, x, t, tw, lds, tab + H);
   }
 #pragma unroll
   for (int q = 0; q < P; ++q) assign(reg[q], x[q]);

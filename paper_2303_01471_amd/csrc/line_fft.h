@@ -61,6 +61,7 @@ __device__ __forceinline__ void assign(float2& d, float2 v) { d = v; }
 __device__ __forceinline__ void assign(double2& d, float2 v) { d = make_double2(v.x, v.y); }
 __device__ __forceinline__ void assign(float2& d, double2 v) { d = make_float2((float)v.x, (float)v.y); }
 __device__ __forceinline__ void assign(double2& d, double2 v) { d = v; }
+__device__ __forceinline__ void assign(double& d, double v) { d = v; }
 
 // multiply by S*i (S = -1: -i z, S = +1: +i z), exact
 template <int S, typename W>
@@ -187,23 +188,25 @@ __device__ __forceinline__ void dft(W (&u)[R]) {
 }
 
 // ---------------------------------------------------------------------------------
-// stage plan: stage s has radix R_s = min(P, N / Ns_s), Ns_0 = 1, Ns_{s+1} = Ns_s R_s
+// stage plan: stage s has radix R_s = min(P, N / Ns_s), Ns_0 = 1, Ns_{s+1} = Ns_s R_s; FIRST:
+// the radix of stage 0 instead.  The twiddles carry their plan (SP) to the stages.
 
 __host__ __device__ constexpr int cmin(int a, int b) { return a < b ? a : b; }
 
-template <int N, int P>
+template <int N, int P, int FIRST = cmin(P, N)>
 struct StagePlan {
+  static constexpr int at(int ns) { return ns == 1 ? FIRST : cmin(P, N / ns); }
   static constexpr int count() {
     int c = 0;
-    for (int ns = 1; ns < N; ns *= cmin(P, N / ns)) ++c;
+    for (int ns = 1; ns < N; ns *= at(ns)) ++c;
     return c;
   }
   static constexpr int ns(int s) {
     int v = 1;
-    for (int i = 0; i < s; ++i) v *= cmin(P, N / v);
+    for (int i = 0; i < s; ++i) v *= at(v);
     return v;
   }
-  static constexpr int radix(int s) { return cmin(P, N / ns(s)); }
+  static constexpr int radix(int s) { return at(ns(s)); }
 };
 
 // LDS slot of line position i: one pad entry after every 8
@@ -323,9 +326,9 @@ struct Twiddles {
 //                faster for 128-, 512- (8 points per lane) and 1024-point lines, slower
 //                for 256-point lines and where the register budget is tight (512 points
 //                with 16 per lane spill the chain of powers).
-template <int N, int P, bool POW>
+template <int N, int P, bool POW, int FIRST = cmin(P, N)>
 struct TwiddlesLds {
-  using SP = StagePlan<N, P>;
+  using SP = StagePlan<N, P, FIRST>;
   static constexpr int kStages = SP::count();
   static constexpr int kTPL = N / P;
   static constexpr bool kPow = POW;
@@ -380,8 +383,8 @@ __device__ __forceinline__ double2 cmul_dd(double2 w, double2 v) {
 // (TwiddlesLds with POW): applied to u[1..R-1] while the next power is formed.
 template <typename TW>
 struct TwPowers : std::false_type {};
-template <int N, int P>
-struct TwPowers<TwiddlesLds<N, P, true>> : std::true_type {};
+template <int N, int P, int FIRST>
+struct TwPowers<TwiddlesLds<N, P, true, FIRST>> : std::true_type {};
 
 template <int S, int STAGE, int R, typename W, typename TW>
 __device__ __forceinline__ void apply_twiddle_powers(W (&u)[R], const TW& tw, int m) {
@@ -406,7 +409,7 @@ __device__ __forceinline__ void line_lds_sync() {
 
 template <int N, int P, int S, int STAGE, bool BLOCK_SYNC = false, typename IX = SlotIx, typename TW>
 __device__ __forceinline__ void fft_stage(float2 (&reg)[P], int t, const TW& tw, float2* __restrict__ lds) {
-  using SP = StagePlan<N, P>;
+  using SP = typename TW::SP;
   constexpr int NS = SP::ns(STAGE);
   constexpr int R = SP::radix(STAGE);
   constexpr int NB = P / R;
@@ -447,7 +450,7 @@ __device__ __forceinline__ void fft_stage(float2 (&reg)[P], int t, const TW& tw,
 
 template <int N, int P, int S, bool BLOCK_SYNC, int STAGE = 0, typename IX = SlotIx, typename TW>
 __device__ __forceinline__ void line_fft_from(float2 (&reg)[P], int t, const TW& tw, float2* __restrict__ lds) {
-  if constexpr (STAGE < StagePlan<N, P>::count()) {
+  if constexpr (STAGE < TW::SP::count()) {
     fft_stage<N, P, S, STAGE, BLOCK_SYNC, IX>(reg, t, tw, lds);
     line_fft_from<N, P, S, BLOCK_SYNC, STAGE + 1, IX>(reg, t, tw, lds);
   }
@@ -474,47 +477,90 @@ __device__ __forceinline__ void line_fft(float2 (&reg)[P], int t, const TW& tw, 
 // twiddle products moved to FP32 hi+lo pairs were measured to gain nothing at 512^2
 // and 1-2 % at 128^2 / 256^2.)
 
+// inputs of butterfly m of a stage: the lane's values in the stage's working type, times their
+// twiddles
+template <int S, int STAGE, int NB, int P, int R, typename W, typename A, typename TW>
+__device__ __forceinline__ void stage_butterfly(W (&u)[R], const A (&src)[P], const TW& tw, int m) {
+#pragma unroll
+  for (int r = 0; r < R; ++r) assign(u[r], src[m + r * NB]);
+  if constexpr (STAGE > 0) {
+    if constexpr (TwPowers<TW>::value) {
+      apply_twiddle_powers<S, STAGE>(u, tw, m);
+    } else {
+#pragma unroll
+      for (int r = 1; r < R; ++r) {
+        const double2 w = tw.template get<STAGE>(m * (R - 1) + (r - 1));
+        u[r] = S < 0 ? cmul_fd(u[r], w) : cmul_fd_conj(u[r], w);
+      }
+    }
+  }
+  dft<R, S>(u);
+}
+
+// An FP64 exchange through a line's FP32 complex slots: the real parts, then the imaginary
+// parts, eight bytes each (a buffer of complex FP64 would cost a workgroup per CU).
+typedef double lds_double __attribute__((may_alias));
+template <int N, int P, int R, int NS, bool BLOCK_SYNC, typename IX, bool IM>
+__device__ __forceinline__ void exchange_part(const double2 (&u)[P / R][R], double2 (&dst)[P], int t,
+                                              lds_double* __restrict__ lds) {
+  constexpr int NB = P / R, TPL = N / P;
+#pragma unroll
+  for (int m = 0; m < NB; ++m) {
+    const int v = t + m * TPL;
+    double part[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) part[r] = IM ? u[m][r].y : u[m][r].x;
+    lds_write_outputs<R, NS, IX>(lds, (v / NS) * NS * R + (v % NS), part);
+  }
+  line_lds_sync<BLOCK_SYNC>();
+  double part[P];
+  lds_read_slots<N, P, IX>(part, t, lds);
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    if (IM) dst[q].y = part[q];
+    else dst[q].x = part[q];
+  }
+  line_lds_sync<BLOCK_SYNC>();
+}
+
 template <int N, int P, int S, int STAGE, bool BLOCK_SYNC, typename W, typename IX, typename A, typename B,
           typename TW>
 __device__ __forceinline__ void fft_stage_io(const A (&src)[P], B (&dst)[P], int t, const TW& tw,
                                              float2* __restrict__ lds) {
-  using SP = StagePlan<N, P>;
+  using SP = typename TW::SP;
   constexpr int NS = SP::ns(STAGE);
   constexpr int R = SP::radix(STAGE);
   constexpr int NB = P / R;
   constexpr int TPL = N / P;
   constexpr bool LAST = (STAGE == SP::count() - 1);
-  static_assert(LAST || std::is_same<B, float2>::value, "an exchanged stage writes FP32");
+  if constexpr (!LAST && std::is_same<B, double2>::value) {
+    static_assert(std::is_same<W, double2>::value, "an FP64 exchange follows an FP64 stage");
+    double2 u[NB][R];
 #pragma unroll
-  for (int m = 0; m < NB; ++m) {
-    W u[R];
+    for (int m = 0; m < NB; ++m) stage_butterfly<S, STAGE, NB>(u[m], src, tw, m);
+    lds_double* __restrict__ ld = reinterpret_cast<lds_double*>(lds);
+    exchange_part<N, P, R, NS, BLOCK_SYNC, IX, false>(u, dst, t, ld);
+    exchange_part<N, P, R, NS, BLOCK_SYNC, IX, true>(u, dst, t, ld);
+    return;
+  } else {
 #pragma unroll
-    for (int r = 0; r < R; ++r) assign(u[r], src[m + r * NB]);
-    if constexpr (STAGE > 0) {
-      if constexpr (TwPowers<TW>::value) {
-        apply_twiddle_powers<S, STAGE>(u, tw, m);
+    for (int m = 0; m < NB; ++m) {
+      W u[R];
+      stage_butterfly<S, STAGE, NB>(u, src, tw, m);
+      if constexpr (LAST) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) assign(dst[m + r * NB], u[r]);
       } else {
-#pragma unroll
-        for (int r = 1; r < R; ++r) {
-          const double2 w = tw.template get<STAGE>(m * (R - 1) + (r - 1));
-          u[r] = S < 0 ? cmul_fd(u[r], w) : cmul_fd_conj(u[r], w);
-        }
+        const int v = t + m * TPL;
+        const int base = (v / NS) * NS * R + (v % NS);
+        lds_write_outputs<R, NS, IX>(lds, base, u);
       }
     }
-    dft<R, S>(u);
-    if constexpr (LAST) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) assign(dst[m + r * NB], u[r]);
-    } else {
-      const int v = t + m * TPL;
-      const int base = (v / NS) * NS * R + (v % NS);
-      lds_write_outputs<R, NS, IX>(lds, base, u);
+    if constexpr (!LAST) {
+      line_lds_sync<BLOCK_SYNC>();
+      lds_read_slots<N, P, IX>(dst, t, lds);
+      line_lds_sync<BLOCK_SYNC>();
     }
-  }
-  if constexpr (!LAST) {
-    line_lds_sync<BLOCK_SYNC>();
-    lds_read_slots<N, P, IX>(dst, t, lds);
-    line_lds_sync<BLOCK_SYNC>();
   }
 }
 
@@ -525,7 +571,7 @@ __device__ __forceinline__ void fft_stage_io(const A (&src)[P], B (&dst)[P], int
 // stage_inputs(); fft_stage_io is these two halves with wavefront-local syncs.
 template <int N, int P, int S, int STAGE, typename W, typename IX, typename A, typename TW>
 __device__ __forceinline__ void stage_outputs_to_lds(const A (&src)[P], int t, const TW& tw, float2* __restrict__ lds) {
-  using SP = StagePlan<N, P>;
+  using SP = typename TW::SP;
   constexpr int NS = SP::ns(STAGE);
   constexpr int R = SP::radix(STAGE);
   constexpr int NB = P / R;
@@ -534,20 +580,7 @@ __device__ __forceinline__ void stage_outputs_to_lds(const A (&src)[P], int t, c
 #pragma unroll
   for (int m = 0; m < NB; ++m) {
     W u[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) assign(u[r], src[m + r * NB]);
-    if constexpr (STAGE > 0) {
-      if constexpr (TwPowers<TW>::value) {
-        apply_twiddle_powers<S, STAGE>(u, tw, m);
-      } else {
-#pragma unroll
-        for (int r = 1; r < R; ++r) {
-          const double2 w = tw.template get<STAGE>(m * (R - 1) + (r - 1));
-          u[r] = S < 0 ? cmul_fd(u[r], w) : cmul_fd_conj(u[r], w);
-        }
-      }
-    }
-    dft<R, S>(u);
+    stage_butterfly<S, STAGE, NB>(u, src, tw, m);
     const int v = t + m * TPL;
     const int base = (v / NS) * NS * R + (v % NS);
     lds_write_outputs<R, NS, IX>(lds, base, u);
@@ -560,27 +593,28 @@ __device__ __forceinline__ void stage_inputs(float2 (&dst)[P], int t, const floa
   lds_read_slots<N, P, IX>(dst, t, lds);
 }
 
-template <int N, int P, int S, bool BLOCK_SYNC, int STAGE, typename IX, typename TW>
-__device__ __forceinline__ void fft_mid_stages(float2 (&reg)[P], int t, const TW& tw, float2* __restrict__ lds) {
-  if constexpr (STAGE < StagePlan<N, P>::count() - 1) {
-    fft_stage_io<N, P, S, STAGE, BLOCK_SYNC, float2, IX>(reg, reg, t, tw, lds);
+template <int N, int P, int S, bool BLOCK_SYNC, int STAGE, typename IX, typename MID, typename TW>
+__device__ __forceinline__ void fft_mid_stages(MID (&reg)[P], int t, const TW& tw, float2* __restrict__ lds) {
+  if constexpr (STAGE < TW::SP::count() - 1) {
+    fft_stage_io<N, P, S, STAGE, BLOCK_SYNC, MID, IX>(reg, reg, t, tw, lds);
     fft_mid_stages<N, P, S, BLOCK_SYNC, STAGE + 1, IX>(reg, t, tw, lds);
   }
 }
 
 // Full unnormalised transform of one line from `in` (float2 or double2) to `out`
-// (float2 or double2), same layout as line_fft.
-template <int N, int P, int S, bool BLOCK_SYNC = false, typename IX = SlotIx, typename TIN, typename TOUT,
-          typename TW>
+// (float2 or double2), same layout as line_fft.  MID: the type of the stages between and of the
+// exchanges (double2 only with an FP64 `in`).
+template <int N, int P, int S, bool BLOCK_SYNC = false, typename IX = SlotIx, typename MID = float2, typename TIN,
+          typename TOUT, typename TW>
 __device__ __forceinline__ void line_fft_io(TIN (&in)[P], TOUT (&out)[P], int t, const TW& tw,
                                             float2* __restrict__ lds) {
-  constexpr int C = StagePlan<N, P>::count();
+  constexpr int C = TW::SP::count();
   if constexpr (C == 1) {
     using W = typename std::conditional<std::is_same<TIN, double2>::value || std::is_same<TOUT, double2>::value,
                                         double2, float2>::type;
     fft_stage_io<N, P, S, 0, BLOCK_SYNC, W, IX>(in, out, t, tw, lds);
   } else {
-    float2 mid[P];
+    MID mid[P];
     fft_stage_io<N, P, S, 0, BLOCK_SYNC, TIN, IX>(in, mid, t, tw, lds);
     fft_mid_stages<N, P, S, BLOCK_SYNC, 1, IX>(mid, t, tw, lds);
     fft_stage_io<N, P, S, C - 1, BLOCK_SYNC, TOUT, IX>(mid, out, t, tw, lds);
@@ -607,8 +641,8 @@ template <int N, int P>
 __device__ __forceinline__ void load_twiddles(Twiddles<N, P>& tw, const double2* __restrict__ g, double2*, int t) {
   tw.load(g, t);
 }
-template <int N, int P, bool POW>
-__device__ __forceinline__ void load_twiddles(TwiddlesLds<N, P, POW>& tw, const double2* __restrict__ g, double2* l,
+template <int N, int P, bool POW, int FIRST>
+__device__ __forceinline__ void load_twiddles(TwiddlesLds<N, P, POW, FIRST>& tw, const double2* __restrict__ g, double2* l,
                                               int t) {
   tw.load(g, l, t);
 }

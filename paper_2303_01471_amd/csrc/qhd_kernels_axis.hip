@@ -86,8 +86,8 @@ k_row_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
   extern __shared__ double2 etab[];  // tables of the block's instances, sized at launch
   const int ll = threadIdx.x / TPL, t = threadIdx.x % TPL;
   float2* my = lds + (MODEL == kModelQAA ? 0 : ll * SLOTS);
-  using TW = typename std::conditional<RC::R4, TwiddlesLds<NX, P, true>, TwiddlesFor<NX, P>>::type;
-  __shared__ double2 twl[MODEL == kModelQAA ? 1 : (RC::R4 ? TwiddlesLds<NX, P, true>::kEntries : TwLdsSize<NX, P>::value)];
+  using TW = typename std::conditional<RC::R4, TwiddlesLds<NX, P, true>, LineTwiddles<NX, P>>::type;
+  __shared__ double2 twl[MODEL == kModelQAA ? 1 : (RC::R4 ? TwiddlesLds<NX, P, true>::kEntries : LineTwSize<NX, P>::value)];
   TW tw;
   if constexpr (MODEL != kModelQAA) load_twiddles(tw, twtab, twl, t);
   // instances of the block's lines: one, or LPW / ny whole ones
@@ -148,7 +148,7 @@ k_row_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
       for (int q = 0; q < P; ++q) assign(reg[q], x[q]);
     } else {
       using IX = typename std::conditional<RC::R4, Slot16Ix, SlotIx>::type;
-      line_pass<NX, P, 0, false, IX>(reg, t, tw, my, tab, k.prev, k.cpot, fix, fget);
+      line_pass<NX, P, false, IX>(reg, t, tw, my, tab, k.prev, k.cpot, fix, fget);
     }
     if (valid && k.active) {
 #pragma unroll
@@ -179,8 +179,8 @@ k_col_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
   __shared__ double2 etab[ITEMS * 2 * H];
   const int tid = threadIdx.x;
   const int line0 = tid / TPL, t = tid % TPL;  // first column of this lane group
-  __shared__ double2 twl[MODEL == kModelQAA ? 1 : TwLdsSize<NY, P>::value];
-  TwiddlesFor<NY, P> tw;
+  __shared__ double2 twl[MODEL == kModelQAA ? 1 : LineTwSize<NY, P>::value];
+  LineTwiddles<NY, P> tw;
   if constexpr (MODEL != kModelQAA) load_twiddles(tw, twtab, twl, t);
   const int tc_log2 = nx_log2 - 3, tcols = 1 << tc_log2, nx = 1 << nx_log2;
   const long long total = (long long)ninst << tc_log2;
@@ -251,7 +251,7 @@ k_col_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
 #pragma unroll
         for (int q = 0; q < P; ++q) assign(reg[q], kd[q]);
       } else {
-        line_pass<NY, P, 1, false, SlotIx>(reg, t, tw, my, tab, k.prev, k.cpot, fix,
+        line_pass<NY, P, false, SlotIx>(reg, t, tw, my, tab, k.prev, k.cpot, fix,
                                         [&](int q) { return fl[tile_index(x, t + q * TPL, nx)]; });
       }
 #pragma unroll
@@ -311,15 +311,15 @@ k_col_axis_split(const InstDev* __restrict__ inst, const int* __restrict__ nact_
   static_assert(TPL == 64 && StagePlan<NY, P>::count() == 3, "split form: 512-point lines, radices 8, 8, 8");
   __shared__ float2 lds[8 * STRIDE];
   __shared__ double2 etab[2 * H];
-  __shared__ double2 twl[TwLdsSize<NY, P>::value];
+  __shared__ double2 twl[LineTwSize<NY, P>::value];
   // the wavefront index is uniform: tile offsets are then scalar and not held per lane
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c_tv = lane & 7, t_tv = (lane >> 3) + 8 * wave;  // tile view: column, line position
   float2* my = lds + wave * STRIDE;                           // line view: this wavefront's column
   float2* mc = lds + c_tv * STRIDE;                           // tile view: this lane's column
-  TwiddlesFor<NY, P> tw;
+  LineTwiddles<NY, P> tw;
   load_twiddles(tw, twtab, twl, lane);
-  TwiddlesFor<NY, P> twt = tw;  // the same table seen from the tile view's line positions
+  LineTwiddles<NY, P> twt = tw;  // the same table seen from the tile view's line positions
   twt.tab = twl + t_tv;
   const int tc_log2 = nx_log2 - 3, tcols = 1 << tc_log2;
   const long long total = (long long)ninst << tc_log2;
@@ -330,7 +330,7 @@ k_col_axis_split(const InstDev* __restrict__ inst, const int* __restrict__ nact_
   auto kinetic = [&](auto& in, auto& out, const double2* __restrict__ tab) {
     using TIN = typename std::remove_reference<decltype(in[0])>::type;
     using TOUT = typename std::remove_reference<decltype(out[0])>::type;
-    using K = typename LinePrec<NY, 1>::K;
+    using K = typename LinePrec<NY>::K;
     stage_outputs_to_lds<NY, P, -1, 0, TIN, SlotIx>(in, t_tv, twt, mc);
     __syncthreads();
     {
@@ -366,7 +366,7 @@ k_col_axis_split(const InstDev* __restrict__ inst, const int* __restrict__ nact_
       fill_etab<NY, kModelQHD, GEN>(etab, inst, i, 1, 1, s);
       cached = i;
     }
-    typename LinePrec<NY, 1>::V v[P];
+    typename LinePrec<NY>::V v[P];
     if (k.prev) {
       kinetic(x, v, etab);
     } else {
@@ -426,8 +426,8 @@ k_col_axis_tw(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
   const int c = lane & 7;
   const int t = (lane >> 3) + 8 * wv;
   float2* my = lds + (MODEL == kModelQAA ? 0 : (item * 8 + c) * STRIDE);
-  __shared__ double2 twl[MODEL == kModelQAA ? 1 : TwLdsSize<NY, P>::value];
-  TwiddlesFor<NY, P> tw;
+  __shared__ double2 twl[MODEL == kModelQAA ? 1 : LineTwSize<NY, P>::value];
+  LineTwiddles<NY, P> tw;
   if constexpr (MODEL != kModelQAA) load_twiddles(tw, twtab, twl, t);
   const int tc_log2 = nx_log2 - 3, tcols = 1 << tc_log2;
   const long long total = (long long)ninst << tc_log2;
@@ -479,7 +479,7 @@ k_col_axis_tw(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
         }
       }
     } else {
-      line_pass<NY, P, 1, (W > 1), SlotIx>(in, t, tw, my, tab, k.prev, k.cpot, fix,
+      line_pass<NY, P, (W > 1), SlotIx>(in, t, tw, my, tab, k.prev, k.cpot, fix,
                                         [&](int q) { return fv.load(q * W * tcols * 64); });
       if (active) {
 #pragma unroll
@@ -504,10 +504,10 @@ __global__ void __launch_bounds__(256) k_observe_col_2d(const InstDev* __restric
   constexpr int STRIDE = ColCfg<NY, P>::STRIDE, TILES = NY / 8, H = etab_len<NY, MODEL>();
   __shared__ float2 lds[8 * STRIDE];
   __shared__ double2 etab[2 * H];
-  __shared__ double2 twl[MODEL == kModelQAA ? 1 : TwLdsSize<NY, P>::value];
+  __shared__ double2 twl[MODEL == kModelQAA ? 1 : LineTwSize<NY, P>::value];
   __shared__ double red[3][NT];
   const int tid = threadIdx.x, line0 = tid / TPL, t = tid % TPL;
-  TwiddlesFor<NY, P> tw;
+  LineTwiddles<NY, P> tw;
   if constexpr (MODEL != kModelQAA) load_twiddles(tw, twtab, twl, t);
   const int tc_log2 = nx_log2 - 3, tcols = 1 << tc_log2, nx = 1 << nx_log2;
   const long long total = (long long)ninst << tc_log2;
@@ -539,7 +539,7 @@ __global__ void __launch_bounds__(256) k_observe_col_2d(const InstDev* __restric
 #pragma unroll
         for (int q = 0; q < P; ++q) assign(reg[q], kd[q]);
       } else {
-        line_kinetic<NY, P, 1, false, SlotIx>(reg, reg, t, tw, my, etab);
+        line_kinetic<NY, P, false, SlotIx>(reg, reg, t, tw, my, etab);
       }
 #pragma unroll
       for (int q = 0; q < P; ++q) my[lds_slot(t + q * TPL)] = reg[q];

@@ -16,8 +16,8 @@
 // (contiguous, padded) and a column (stride RS) are exchanged in place: a line loads
 // its points into registers, and its own storage then serves as the exchange buffer
 // of its transforms.  The QAA model (App. E.2's baseline) runs the same steps with FP64
-// Walsh-Hadamard lines, which need no LDS exchange.  Lines of 32 and 64 points, and every
-// QAA line, give the values of the streaming passes bit for bit.
+// Walsh-Hadamard lines, which need no LDS exchange.  Every line gives the values of the
+// streaming passes bit for bit (of the forms with 16 points per lane where it has 128).
 #include "axis_line.h"
 #include "line_fft.h"
 #include "pass_common.h"
@@ -30,7 +30,7 @@ namespace qhd {
 // 128 45 and 38; one instance 7.4 and 8.4, 5.6 and 6.3)
 template <int NX, int NY, int MODEL, bool MANY>
 struct ResCfg {
-  // 128-point lines take 16 points per lane (radices 16 and 8: one exchange per transform)
+  // 128-point lines take 16 points per lane (radices 8 and 16: one exchange per transform)
   static constexpr int PX = NX >= 128 ? 16 : 8, PY = NY >= 128 ? 16 : 8;
   static constexpr int TX = NX / PX, TY = NY / PY;             // lanes per row / column line
   static constexpr int LANES = NX * NY / PX > NX * NY / PY ? NX * NY / PX : NX * NY / PY;
@@ -56,16 +56,16 @@ __global__ void __launch_bounds__((ResCfg<NX, NY, MODEL, MANY>::NT)) k_resident_
   constexpr int HX = etab_len<NX, MODEL>(), HY = etab_len<NY, MODEL>();
   constexpr bool SHARE_TW = NX == NY;
   __shared__ float2 st[NY * RS];
-  __shared__ double2 twlx[MODEL == kModelQAA ? 1 : TwLdsSize<NX, PX>::value];
-  __shared__ double2 twly[MODEL == kModelQAA || SHARE_TW ? 1 : TwLdsSize<NY, PY>::value];
+  __shared__ double2 twlx[MODEL == kModelQAA ? 1 : LineTwSize<NX, PX>::value];
+  __shared__ double2 twly[MODEL == kModelQAA || SHARE_TW ? 1 : LineTwSize<NY, PY>::value];
   // E(a_{j-1}) and E(a_j) of the axis of the current step; the other axis's are filled for
   // the next step meanwhile
   __shared__ double2 ex[2 * HX], ey[2 * HY];
   const int tid = threadIdx.x;
   const int rl = tid / TX, rt = tid % TX;  // row step: line of this lane group, lane in the line
   const int cl = tid / TY, ct = tid % TY;  // column step
-  TwiddlesFor<NX, PX> tx;
-  TwiddlesFor<NY, PY> ty;
+  LineTwiddles<NX, PX> tx;
+  LineTwiddles<NY, PY> ty;
   if constexpr (MODEL != kModelQAA) {
     load_twiddles(tx, twx, twlx, rt);
     load_twiddles(ty, twy, SHARE_TW ? twlx : twly, ct);  // equal sizes share one table
@@ -121,7 +121,7 @@ __global__ void __launch_bounds__((ResCfg<NX, NY, MODEL, MANY>::NT)) k_resident_
 #pragma unroll
             for (int q = 0; q < PX; ++q) reg[q] = my[lds_slot(rt + q * TX)];
             wave_lds_sync();
-            line_pass<NX, PX, 0, false, SlotIx>(reg, rt, tx, my, ex, k.prev, k.cpot, 0,
+            line_pass<NX, PX, false, SlotIx>(reg, rt, tx, my, ex, k.prev, k.cpot, 0,
                                              [&](int q) { return fg[tile_index(rt + q * TX, y, NX)]; });
 #pragma unroll
             for (int q = 0; q < PX; ++q) my[lds_slot(rt + q * TX)] = reg[q];
@@ -148,7 +148,7 @@ __global__ void __launch_bounds__((ResCfg<NX, NY, MODEL, MANY>::NT)) k_resident_
 #pragma unroll
             for (int q = 0; q < PY; ++q) reg[q] = my[(ct + q * TY) * RS];
             wave_lds_sync();
-            line_pass<NY, PY, 1, false, StrideIx<RS>>(reg, ct, ty, my, ey, k.prev, k.cpot, 0,
+            line_pass<NY, PY, false, StrideIx<RS>>(reg, ct, ty, my, ey, k.prev, k.cpot, 0,
                                                    [&](int q) { return fg[tile_index(x, ct + q * TY, NX)]; });
 #pragma unroll
             for (int q = 0; q < PY; ++q) my[(ct + q * TY) * RS] = reg[q];
