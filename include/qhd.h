@@ -120,8 +120,9 @@ typedef struct {
                               chunk in this many (<= 0 selects 16)                     */
   const char *tune_cache;  /* path of a text tuning cache, or NULL.  Entries found for
                               a shape class are used; with QHD_OPT_AUTOTUNE, classes
-                              without an entry are tuned and appended.  A missing or
-                              unreadable file is treated as empty                      */
+                              without an entry are tuned and appended.  Entries that
+                              the tuner timed on other kernels are passed over.  A
+                              missing or unreadable file is treated as empty           */
 } qhd_plan_opts;
 
 #define QHD_OPT_TIME_PASSES 0x1u /* record HIP events around sampled pass launches   */

@@ -479,7 +479,16 @@ void mirror_chunk(qhd_plan p, long long ks) {
 // ---- launch tuning ----------------------------------------------------------------
 
 // Tuning-cache lines: "qhd-tune 1 <arch> <nx> <ny> <members_pow2> <col_variant> <cap_row> <cap_col>
-// [<row points per lane>]" (the last field is optional, 8 when absent)
+// [<row points per lane>]" (the last field is optional, 8 when absent).  A line that the tuner
+// wrote ends in a comment with its timings, which begins with the passes it timed: lines timed on
+// other passes (the separate ones of each axis named none) are not used.  A line without a
+// comment is a caller's own choice.
+constexpr char kTimedPasses[] = "# alternating passes:";
+bool timed_elsewhere(const char* line) {
+  const char* c = strchr(line, '#');
+  return c && strncmp(c, kTimedPasses, sizeof kTimedPasses - 1) != 0;
+}
+
 std::string tune_key(const std::string& arch, const ShapeClass& c) {
   int m = 1;
   while (m < (int)c.members.size()) m <<= 1;
@@ -495,7 +504,7 @@ bool tune_lookup(const std::string& path, const std::string& key, ShapeClass& c)
   bool found = false;
   while (fgets(line, sizeof line, fh)) {
     const size_t k = key.size();
-    if (strncmp(line, key.c_str(), k) != 0 || line[k] != ' ') continue;
+    if (strncmp(line, key.c_str(), k) != 0 || line[k] != ' ' || timed_elsewhere(line)) continue;
     int v = 0, cr = 0, cc = 0, rp = 8;
     const int got = sscanf(line + k, "%d %d %d %d", &v, &cr, &cc, &rp);
     if (got >= 3 && v >= kColAuto && v <= kColSplit && cr >= 0 && cc >= 0 && (rp == 8 || rp == 16)) {
@@ -514,8 +523,8 @@ void tune_append(const std::string& path, const std::string& key, const ShapeCla
                  double us_col) {
   FILE* fh = fopen(path.c_str(), "a");
   if (!fh) return;
-  fprintf(fh, "%s %d %d %d %d  # row %.2f us, col %.2f us\n", key.c_str(), c.col_variant, c.cap_row, c.cap_col,
-          c.row_points, us_row, us_col);
+  fprintf(fh, "%s %d %d %d %d  %s row %.2f us, col %.2f us\n", key.c_str(), c.col_variant, c.cap_row, c.cap_col,
+          c.row_points, kTimedPasses, us_row, us_col);
   fclose(fh);
 }
 
@@ -602,7 +611,7 @@ int resident_lookup(const std::string& path, const std::string& key) {
   int dec = -1;
   while (fgets(line, sizeof line, fh)) {
     const size_t k = key.size();
-    if (strncmp(line, key.c_str(), k) != 0 || line[k] != ' ') continue;
+    if (strncmp(line, key.c_str(), k) != 0 || line[k] != ' ' || timed_elsewhere(line)) continue;
     int v = -1;
     if (sscanf(line + k, "%d", &v) == 1 && (v == 0 || v == 1)) dec = v;  // the last matching line wins
   }
@@ -613,7 +622,8 @@ int resident_lookup(const std::string& path, const std::string& key) {
 void resident_append(const std::string& path, const std::string& key, int dec, double us_res, double us_str) {
   FILE* fh = fopen(path.c_str(), "a");
   if (!fh) return;
-  fprintf(fh, "%s %d  # 16 steps: resident %.2f us, streaming %.2f us\n", key.c_str(), dec, us_res, us_str);
+  fprintf(fh, "%s %d  %s 16 steps, resident %.2f us, streaming %.2f us\n", key.c_str(), dec, kTimedPasses, us_res,
+          us_str);
   fclose(fh);
 }
 
