@@ -543,10 +543,14 @@ double time_launches(hipStream_t st, hipEvent_t a, hipEvent_t b, int reps, F&& f
 }
 
 // Time the row pass over grid caps and the column pass over variants x grid caps on
-// the class's own buffers (a sub-step in which a pass does its whole work, with every member
-// active), keep the fastest.  The state is overwritten; the caller restores it.
+// the class's own buffers, keep the fastest; in the third sub-step, in which a pass does its whole
+// work, or in the first (without the operator owed by the step before) where not every member
+// gets that far.  Nothing to time where no member has a step.  The state is overwritten; the
+// caller restores it.
 qhd_status autotune_class(qhd_plan p, ShapeClass& c, double& us_row, double& us_col) {
   const int m = (int)c.members.size();
+  if (c.host[0].nsteps == 0) return QHD_OK;  // (members are sorted by steps)
+  const int s = c.host[m - 1].nsteps > 2 ? 2 : 0;
   static const int caps[] = {512, 1024, 2048, 4096, 8192};
   hipEvent_t a = nullptr, b = nullptr;
   HIP_TRY(hipEventCreate(&a));
@@ -564,7 +568,7 @@ qhd_status autotune_class(qhd_plan p, ShapeClass& c, double& us_row, double& us_
   for (int rp : row_pts)
     for (int cap : caps) {
       const double t = time_launches(p->internal, a, b, reps, [&] {
-        return launch_row_pass_2d(c.nx, c.ny, c.dev, m, c.nact + kMaxSub, c.psi, c.f, c.tw_x, 2, 3, cap, rp,
+        return launch_row_pass_2d(c.nx, c.ny, c.dev, m, c.nact + kMaxSub, c.psi, c.f, c.tw_x, s, s + 1, cap, rp,
                                   p->internal, c.model, c.y4);
       });
       if (t < 0) ok = false;
@@ -574,10 +578,11 @@ qhd_status autotune_class(qhd_plan p, ShapeClass& c, double& us_row, double& us_
   if (col_variant_resolve(c.ny, kColTileWave) == kColTileWave) variants.push_back(kColTileWave);
   if (col_variant_resolve(c.ny, kColStaged16) == kColStaged16) variants.push_back(kColStaged16);
   if (c.model == kModelQHD && col_variant_resolve(c.ny, kColSplit) == kColSplit) variants.push_back(kColSplit);
+  HIP_TRY(launch_set_axis(c.dev, m, 1, p->internal));  // the column pass takes the even sub-steps
   for (int v : variants)
     for (int cap : caps) {
       const double t = time_launches(p->internal, a, b, reps, [&] {
-        return launch_col_pass_2d(c.nx, c.ny, c.dev, m, c.nact + kMaxSub, c.psi, c.f, c.tw_y, 1, 2, cap, v,
+        return launch_col_pass_2d(c.nx, c.ny, c.dev, m, c.nact + kMaxSub, c.psi, c.f, c.tw_y, s, s + 1, cap, v,
                                   p->internal, c.model, c.y4);
       });
       if (t < 0) ok = false;
@@ -585,6 +590,7 @@ qhd_status autotune_class(qhd_plan p, ShapeClass& c, double& us_row, double& us_
     }
   (void)hipEventDestroy(a);
   (void)hipEventDestroy(b);
+  HIP_TRY(launch_set_axis(c.dev, m, 0, p->internal));
   if (!ok) return fail(QHD_EDEVICE, "autotune launch failed: %s", hipGetErrorString(hipGetLastError()));
   c.cap_row = best_row;
   c.cap_col = best_col;
@@ -627,12 +633,12 @@ void resident_append(const std::string& path, const std::string& key, int dec, d
   fclose(fh);
 }
 
-// Time 16 steps of the class (every member) as one resident launch and as streaming
+// Time 16 steps of the class (all of its steps, if it has fewer) as one resident launch and as streaming
 // passes with the class's launch configuration.  The state is overwritten; the caller
 // restores it.
 qhd_status compare_resident(qhd_plan p, ShapeClass& c, double& us_res, double& us_str) {
   const int m = (int)c.members.size();
-  const int k = 16;
+  const int k = (int)std::min<long long>(16, c.host[0].nsteps);
   hipEvent_t a = nullptr, b = nullptr;
   HIP_TRY(hipEventCreate(&a));
   if (hipEventCreate(&b) != hipSuccess) {
@@ -1011,10 +1017,10 @@ qhd_status qhd_plan_create(const qhd_instance* inst, int32_t batch, const qhd_pl
           qhd_status st = autotune_class(p, c, us_row, us_col);
           if (st != QHD_OK) return bail(st);
           refill = true;
-          if (!p->tune_cache.empty()) tune_append(p->tune_cache, key, c, us_row, us_col);
+          if (c.tuned && !p->tune_cache.empty()) tune_append(p->tune_cache, key, c, us_row, us_col);
         }
       }
-      if (c.resident && autotune) {
+      if (c.resident && autotune && c.host[0].nsteps > 0) {
         // resident or streaming, whichever runs this class faster (or the cached choice)
         const std::string rkey = resident_key(arch, c);
         int dec = p->tune_cache.empty() ? -1 : resident_lookup(p->tune_cache, rkey);

@@ -61,3 +61,21 @@ def test_a_resident_choice_timed_on_other_kernels_is_not_used(tmp_path):
     assert len([ln for ln in cache.read_text().splitlines() if ln.startswith("qhd-resident")]) == 2
     cache.write_text(old + "\n")
     assert _info(specs, flags, str(cache))["resident"] is False
+
+
+def test_members_of_one_step_are_timed_at_work(tmp_path):
+    """64 x 512^2 of one step each: a pass in which they are active reads and writes 24 bytes of
+    each of 16.8 M points, which no memory of the card does in 20 us (20 TB/s)."""
+    specs = [q.InstanceSpec(shape=(512, 512), nsteps=1, dt=1e-3)] * 64
+    cache = tmp_path / "tune.txt"
+    assert _info(specs, q.QHD_OPT_AUTOTUNE, str(cache))["tuned"]
+    line = cache.read_text().splitlines()[-1]
+    row, col = float(line.split("row ")[1].split()[0]), float(line.split("col ")[1].split()[0])
+    assert row > 20.0 and col > 20.0, line
+
+
+def test_members_without_steps_are_not_timed(tmp_path):
+    specs = [q.InstanceSpec(shape=(64, 64), nsteps=0, dt=1e-3)] * 3
+    cache = tmp_path / "tune.txt"
+    assert not _info(specs, q.QHD_OPT_AUTOTUNE | q.QHD_OPT_RESIDENT, str(cache))["tuned"]
+    assert not cache.exists() or cache.read_text() == ""
