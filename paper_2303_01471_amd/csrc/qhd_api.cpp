@@ -574,7 +574,10 @@ qhd_status autotune_class(qhd_plan p, ShapeClass& c, double& us_row, double& us_
       if (t < 0) ok = false;
       else if (t < us_row) us_row = t, best_row = cap, best_pts = rp;
     }
-  std::vector<int> variants = {kColStaged};
+  // (128-point columns: the staged form, two FP32 exchanges towards frequency space, drifts more:
+  // 262 x 128^2 6.7e-6 per 1e4 steps, tile-wave 4.9e-6; it is slower too, 38 and 33 us a step)
+  std::vector<int> variants;
+  if (c.ny != 128) variants.push_back(kColStaged);
   if (col_variant_resolve(c.ny, kColTileWave) == kColTileWave) variants.push_back(kColTileWave);
   if (col_variant_resolve(c.ny, kColStaged16) == kColStaged16) variants.push_back(kColStaged16);
   if (c.model == kModelQHD && col_variant_resolve(c.ny, kColSplit) == kColSplit) variants.push_back(kColSplit);
@@ -996,9 +999,9 @@ qhd_status qhd_plan_create(const qhd_instance* inst, int32_t batch, const qhd_pl
       c.cap_row = c.cap_col = p->grid_cap;
       if (c.ndim != 2) continue;
       if (c.model != kModelQAA) {  // QAA passes have one fixed launch form
-        // 128-point rows: 16 points per lane (radices 16 and 8: the FP32 exchange next to the
-        // FP64 position-space stage rounds values that each carry an eighth of a localised
-        // line's mass, with 8 points per lane and radices 8, 8, 2 half of it; no time seen)
+        // 128-point rows: 16 points per lane for any number of members, so that a member's bits do
+        // not depend on the batch and are those of resident steps (262 / 1024 members 33 / 96 us
+        // per step, 34 / 101 with 8; a lone one 10.4 and 9.3; largest norm drift 4.9e-6 and 4.6e-6)
         c.row_points = c.nx == 128 ? 16 : 8;
         if (!env_cap) {
           // measured defaults (uniform batches of 256 instances per size on MI355X): a block

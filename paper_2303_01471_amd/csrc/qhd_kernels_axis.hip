@@ -628,6 +628,10 @@ int col_variant_resolve(int ny, int variant) {
   if (variant == kColStaged16 && (ny == 256 || ny == 512)) return kColStaged16;
   if (variant == kColSplit && ny == 512) return kColSplit;
   if (variant == kColStaged) return kColStaged;
+  // 512 points: by whole steps the split form is the better one but for mid-sized batches (us per
+  // step, split and tile-wave: 1 member 10.2 and 10.6, 4: 14.7 and 14.9, 16: 33.9 and 32.1, 64: 112
+  // and 113, 263: 464 and 470), although a tile-wave pass launched alone over and over may time
+  // faster
   return (ny >= 64 && ny <= 256) || ny == 1024 ? kColTileWave : (ny == 512 ? kColSplit : kColStaged);
 }
 
