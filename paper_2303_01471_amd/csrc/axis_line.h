@@ -15,31 +15,28 @@ __host__ __device__ constexpr int etab_len() {
 }
 
 // Tables E(a0) then E(a1) of one instance, by the whole block (the caller synchronises around
-// it).  The entry of |frequency| N / 2 is the fourth power of that of N / 4 (its phase is four
-// times as large), so that a block of N threads or half as many has whole rounds.
+// it).  The two entries of |frequency| N / 2 come last: a block of N threads or half as many has
+// whole rounds before them.  (As fourth powers of the entries of N / 4 they cost no round, but
+// carried four times those entries' error: 3.6e-7 rad a step, 1.1e-7 by their own angle.)
 template <int N, int MODEL>
 __device__ __forceinline__ void fill_etab_pair(double2* __restrict__ tab, const InstDev& I, int axis, double a0, double a1) {
   constexpr int H = etab_len<N, MODEL>();
-  constexpr int R = MODEL == kModelQAA ? H : N / 2;  // entries evaluated per table
+  constexpr int R = MODEL == kModelQAA ? H : N / 2;  // entries per table before the last ones
   constexpr double inv_n = 1.0 / N;
   const double unit = MODEL == kModelQAA ? I.dt * kInv2Pi : I.kin_turns[axis];
-  for (int e = threadIdx.x; e < 2 * R; e += blockDim.x) {
-    const int cur = e >= R ? 1 : 0, k = e - cur * R;
+  for (int e = threadIdx.x; e < 2 * H; e += blockDim.x) {
+    const bool last = e >= 2 * R;
+    const int cur = last ? e - 2 * R : (e >= R ? 1 : 0), k = last ? R : e - cur * R;
     const double c = (cur ? a1 : a0) * unit;
     const double turns = c * (double)(MODEL == kModelQAA ? 2 * k - ilog2_c(N) : k * k);
-    // 128-point axes by the exact angle: their rounding left no room for the error of the
-    // transcendental form (state error of 8 x 128^2 after 600 steps 4.6e-6 -> 3.4e-6, no time
-    // seen); at other lengths the errors stand below those of separate axis passes without it,
-    // and it costs registers (512-point columns 78 -> 104) or latency (one 64^2 instance +0.9 us)
+    // 128-point axes by the exact angle (state error of 8 x 128^2 after 600 steps 3.5e-6 -> 1.8e-6,
+    // with a constant schedule 5.8e-6 -> 1.5e-6; 262 x 128^2 32.9 -> 33.2 us per step); at other
+    // lengths the errors stand below those of separate axis passes without it, and it costs
+    // registers (512-point columns 78 -> 104) or latency (one 64^2 instance +0.9 us)
     double2 v;
     if constexpr (N == 128) v = phase_turns_exact(turns);
     else v = phase_turns_d(turns);
     tab[cur * H + k] = make_double2(v.x * inv_n, v.y * inv_n);
-    if (MODEL != kModelQAA && k == N / 4) {
-      v = cmul_dd(v, v);
-      v = cmul_dd(v, v);
-      tab[cur * H + N / 2] = make_double2(v.x * inv_n, v.y * inv_n);
-    }
   }
 }
 
@@ -91,7 +88,8 @@ __device__ __forceinline__ void mul_field(double2 (&reg)[P], int t, const double
 // alone 6.9e-6, 3.4e-6; both ends 1.5e-5, 2.1e-6; and XI 4.9e-6, 1.9e-6 (the exchange towards
 // frequency space instead 4.0e-6, 1.4e-6 but 8 % longer; both 3.7e-6, 1.1e-6 and 11 %).  256^2
 // with K 8.9e-6, 3.2e-6, with both ends 4.0e-6, 2.7e-6 (3 % longer).  512^2 with K 4.1e-6 (5.4e-6
-// separate; both ends 2.6e-6, 3 % longer).
+// separate; both ends 2.6e-6, 3 % longer).  (With the factors of N / 2 by their own angle the
+// chosen ones are 4.1e-6, 3.0e-6 and 4.3e-6 at 128^2, 256^2 and 512^2.)
 template <int N>
 struct LinePrec {
   using V = typename std::conditional<N == 128 || N == 256, double2, float2>::type;
