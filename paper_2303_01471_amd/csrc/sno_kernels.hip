@@ -24,14 +24,36 @@ __device__ __forceinline__ float gelu_grad(float z) {
 // samples' phases overlap on a CU.  One sample of 128^2, us with 256 and 1024 threads: features
 // and lift 86 and 11 (spread over 8 blocks, each with its own statistics), softmax 33 and 8;
 // the y-contractions, whose column tiles spread over 4 blocks, 19 and 6.6, 13 and 5.4.
-// (A batch's size picks the order of the FP64 sums.)
 constexpr int kFewSamples = 256;
 inline bool few_samples(int batch) { return batch < kFewSamples; }
 
-// block-wide FP64 sum over NT threads
+// FP64 sums over a sample's pixels in one order for either block size, so that a sample's results
+// do not depend on its batch: 1024 strided partial sums (pixel p in sum p mod 1024), added in a
+// tree of halves.  A thread of a 256-thread block holds four of them.
+constexpr int kSumLanes = 1024;
 template <int NT>
-__device__ __forceinline__ double block_sum(double v, double* sh) {
-  sh[threadIdx.x] = v;
+struct LaneSums {
+  static constexpr int K = kSumLanes / NT;
+  double v[K] = {};
+};
+// f(p, sum index k) over the block's pixels
+template <int NT, typename F>
+__device__ __forceinline__ void each_pixel(int npix, F&& f) {
+  constexpr int K = kSumLanes / NT, UNROLL = K == 1 ? 4 : 1;
+#pragma unroll UNROLL
+  for (int p0 = threadIdx.x; p0 < npix; p0 += kSumLanes) {
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      if (k == 0 || p0 + k * NT < npix) f(p0 + k * NT, k);
+  }
+}
+
+// block-wide sum of the partial sums
+template <int NT>
+__device__ __forceinline__ double block_sum(const LaneSums<NT>& s, double* sh) {
+  static_assert(NT == 1024 || NT == 256, "the tree's upper two levels are within a thread or in LDS");
+  if constexpr (NT == 256) sh[threadIdx.x] = (s.v[0] + s.v[2]) + (s.v[1] + s.v[3]);
+  else sh[threadIdx.x] = s.v[0];
   __syncthreads();
   for (int o = NT / 2; o > 0; o >>= 1) {
     if ((int)threadIdx.x < o) sh[threadIdx.x] += sh[threadIdx.x + o];
@@ -61,12 +83,11 @@ __global__ void __launch_bounds__(NT) k_prep(const double* __restrict__ f, int S
   __shared__ double sh[NT];
   const int b = blockIdx.x, npix = S * S;
   const double* fb = f + (long long)b * npix;
-  double s1 = 0.0, s2 = 0.0;
-#pragma unroll 4
-  for (int p = threadIdx.x; p < npix; p += NT) {
-    s1 += fb[p];
-    s2 += fb[p] * fb[p];
-  }
+  LaneSums<NT> s1, s2;
+  each_pixel<NT>(npix, [&](int p, int k) {
+    s1.v[k] += fb[p];
+    s2.v[k] += fb[p] * fb[p];
+  });
   const double mean = block_sum<NT>(s1, sh) / npix;
   const double var = block_sum<NT>(s2, sh) / npix - mean * mean;
   const double inv = 1.0 / sqrt(var > 1e-24 ? var : 1e-24);
@@ -193,13 +214,12 @@ __global__ void __launch_bounds__(NT) k_project_softmax(const T* __restrict__ h,
     }
   }
   mx = block_max<NT>(mx, shf);
-  double s = 0.0;
-#pragma unroll 4
-  for (int p = threadIdx.x; p < npix; p += NT) {
+  LaneSums<NT> s;
+  each_pixel<NT>(npix, [&](int p, int k) {
     const float e = __expf(rb[p] - mx);
     rb[p] = e;
-    s += e;
-  }
+    s.v[k] += e;
+  });
   const double tot = block_sum<NT>(s, sh);
   const float inv = (float)(1.0 / tot);
 #pragma unroll 4
@@ -217,15 +237,14 @@ __global__ void __launch_bounds__(NT) k_loss_grad(const float* __restrict__ rh, 
   const float* t = r + (long long)b * npix;
   float* d = dq + (long long)b * npix;
   const float invb = 1.0f / (float)batch;
-  double l = 0.0, s = 0.0;
-#pragma unroll 4
-  for (int p = threadIdx.x; p < npix; p += NT) {
+  LaneSums<NT> l, s;
+  each_pixel<NT>(npix, [&](int p, int k) {
     const float diff = a[p] - t[p];
     const float g = diff > 0.0f ? invb : (diff < 0.0f ? -invb : 0.0f);
-    l += fabs((double)diff);
-    s += (double)a[p] * g;
+    l.v[k] += fabs((double)diff);
+    s.v[k] += (double)a[p] * g;
     d[p] = g;
-  }
+  });
   const double lt = block_sum<NT>(l, sh);
   const float st = (float)block_sum<NT>(s, sh);
 #pragma unroll 4
@@ -451,12 +470,11 @@ __global__ void __launch_bounds__(NT) k_prep_lift32(const double* __restrict__ f
   __shared__ double sh[NT];
   const int b = blockIdx.x, npix = S * S;
   const double* fb = f + (long long)b * npix;
-  double s1 = 0.0, s2 = 0.0;
-#pragma unroll 4
-  for (int p = threadIdx.x; p < npix; p += NT) {
-    s1 += fb[p];
-    s2 += fb[p] * fb[p];
-  }
+  LaneSums<NT> s1, s2;
+  each_pixel<NT>(npix, [&](int p, int k) {
+    s1.v[k] += fb[p];
+    s2.v[k] += fb[p] * fb[p];
+  });
   const double mean = block_sum<NT>(s1, sh) / npix;
   const double var = block_sum<NT>(s2, sh) / npix - mean * mean;
   const double inv = 1.0 / sqrt(var > 1e-24 ? var : 1e-24);
@@ -756,13 +774,12 @@ __global__ void __launch_bounds__(NT) k_softmax_rows(float* __restrict__ rho, in
 #pragma unroll 4
   for (int p = threadIdx.x; p < npix; p += NT) mx = fmaxf(mx, rb[p]);
   mx = block_max<NT>(mx, shf);
-  double s = 0.0;
-#pragma unroll 4
-  for (int p = threadIdx.x; p < npix; p += NT) {
+  LaneSums<NT> s;
+  each_pixel<NT>(npix, [&](int p, int k) {
     const float e = __expf(rb[p] - mx);
     rb[p] = e;
-    s += e;
-  }
+    s.v[k] += e;
+  });
   const double tot = block_sum<NT>(s, sh);
   const float inv = (float)(1.0 / tot);
 #pragma unroll 4
