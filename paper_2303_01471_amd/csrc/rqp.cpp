@@ -313,7 +313,7 @@ qhd_status qhd_rqp_create(const qhd_rqp_desc* desc, int32_t batch, qhd_rqp* out)
   if (e == hipSuccess) e = hipMalloc(&h->U, sizeof(double) * NP * NP);
   if (e == hipSuccess) e = hipMalloc(&h->lam, sizeof(double) * NP);
   if (e == hipSuccess) e = hipMalloc(&h->tab, sizeof(double) * kRqpStepRun * kRqpMatStride);
-  const int blocks = rqp_observe_blocks(h->N, batch);
+  const int blocks = rqp_observe_blocks(h->N);
   if (e == hipSuccess && blocks > 1)
     e = hipMalloc(&h->part, sizeof(double) * batch * (size_t)blocks * std::max(3, d * NP));
   if (e == hipSuccess) e = hipMalloc(&h->amp, sizeof(double) * NP);

@@ -35,10 +35,12 @@ hipError_t rqp_matrices(int NP, const double* U, const double* lam, const RqpSte
 // `rounds` times the potential factor and the matrix of the next entry of mat1.
 hipError_t rqp_pass(int NP, float2* psi, const double* f, const RqpSet& S, long long total_points,
                     const double* mat0, const double* mat1, int rounds, hipStream_t st);
-// blocks per instance of the readouts: about 2048 blocks over the batch, 1024 points or more each
-inline int rqp_observe_blocks(long long N, int batch) {
-  const long long want = 2048 / batch + 1, most = N / 1024 + 1;
-  return (int)(want < most ? want : most);
+// Blocks per instance of the readouts, by the lattice alone: the order of an instance's sums does
+// not depend on the batch.  4096 points each, at most 256 blocks: enough for one large instance
+// (all readouts of one 16^6 507 us; 9^5: one 61, 256 of them 320), small ones need no second pass.
+inline int rqp_observe_blocks(long long N) {
+  const long long most = N / 4096 + 1;
+  return (int)(most < 256 ? most : 256);
 }
 // part: batch * d * rqp_observe_blocks() * NP doubles, unused with one block per instance
 hipError_t rqp_marginals(int NP, const float2* psi, long long N, int d, int batch, double* part, float* marg,

@@ -536,7 +536,7 @@ hipError_t rqp_pass(int NP, float2* psi, const double* f, const RqpSet& S, long 
 
 hipError_t rqp_marginals(int NP, const float2* psi, long long N, int d, int batch, double* part, float* marg,
                          hipStream_t st) {
-  const int blocks = rqp_observe_blocks(N, batch);
+  const int blocks = rqp_observe_blocks(N);
   QHD_RQP_SWITCH(NP, marginals_np<NP_>(psi, N, d, batch, part, blocks, marg, st))
 }
 
@@ -557,7 +557,7 @@ hipError_t rqp_init(float2* psi, const double* amp, int d, int NP, long long N, 
 
 hipError_t rqp_observe(const float2* psi, const double* f, long long N, int batch, const double* fmin, double tol,
                        double* part, double* out, float* prob, float2* psi_out, double close_turns, hipStream_t st) {
-  const int blocks = rqp_observe_blocks(N, batch);
+  const int blocks = rqp_observe_blocks(N);
   hipLaunchKernelGGL(k_rqp_observe, dim3((unsigned)blocks, (unsigned)(batch < 65535 ? batch : 65535)), dim3(kThreads), 0,
                      st, psi, f, N, fmin, tol, part, out, prob, psi_out, close_turns, batch);
   if (blocks == 1) return hipGetLastError();
