@@ -93,7 +93,7 @@ def counter_means(db: str):
 
 # pass kernel -> (family name used by the library's timing, algorithmic bytes per point);
 # the 2-D kernels' third template argument is the model (0 QHD, 1 QAA), a last boolean
-# one whether the fourth-order stage arithmetic is compiled in
+# one whether it is the general form (fourth-order stages, members on either axis)
 def _model_suffix(m, i=2):
     return "_qaa" if (m.re.groups >= i and m.group(i) == "1") else ""
 
@@ -112,7 +112,8 @@ _FAMILY = [
      lambda m: f"col_pass_2d{_model_suffix(m)}/n{m.group(1)}", 16.0),
     (re.compile(r"k_col_pass_split<(\d+),"), lambda m: f"col_pass_2d/n{m.group(1)}", 16.0),
     (re.compile(r"k_lf_row_2d<(\d+), \d+>"), lambda m: f"row_pass_2d_qaa_lf/n{m.group(1)}", 20.0),
-    (re.compile(r"k_lf_col_2d<(\d+), \d+>"), lambda m: f"col_pass_2d_qaa_lf/n{m.group(1)}", 20.0),
+    (re.compile(r"k_lf_col_(?:2d<(\d+), \d+>|tw<(\d+)>)"),
+     lambda m: f"col_pass_2d_qaa_lf/n{m.group(1) or m.group(2)}", 20.0),
     (re.compile(r"k_line_(?:pass|steps)_1d<(\d+),"), lambda m: f"line_pass_1d/n{m.group(1)}", 24.0),
     # 3-D: the x-pass (psi read and written, f read) and the (y, z)-plane pass
     (re.compile(r"k_xpass_3d<(\d+),"), lambda m: f"xpass_3d/n{m.group(1)}", 24.0),
