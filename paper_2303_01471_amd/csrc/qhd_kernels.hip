@@ -1,7 +1,6 @@
 // HIP kernels of the QHD split-operator engine (gfx950 / CDNA4) beside the 2-D step passes
 // (qhd_kernels_axis.hip): the leapfrog stages of the QAA model, the 1-D steps, the row
 // form of the readouts, uploads, and the per-chunk bookkeeping.
-//
 #include <climits>
 
 #include "launch_util.h"
@@ -653,21 +652,17 @@ hipError_t launch_lf_row_2d(int nx, int ny, const InstDev* inst, int ninst, cons
 
 hipError_t launch_lf_col_2d(int nx, int ny, const InstDev* inst, int ninst, const int* nact, float2* psi, const float* scratch, int s,
                             long long max_steps, int grid_cap, hipStream_t stream) {
-  if (ny == 64 || ny == 128) {
-    const int tw_blocks = blocks_for((long long)ninst * (nx / 8), 4, grid_cap);
-    if (ny == 64)
-      QHD_LAUNCH((k_lf_col_tw<64>), dim3(tw_blocks), dim3(256), 0, stream, inst, nact, ilog2(nx), psi, scratch, s,
-                 max_steps);
-    else
-      QHD_LAUNCH((k_lf_col_tw<128>), dim3(tw_blocks), dim3(256), 0, stream, inst, nact, ilog2(nx), psi, scratch, s,
-                 max_steps);
-    return hipGetLastError();
-  }
-  const int blocks = pass_blocks_col_2d(nx, ny, ninst, grid_cap, kColStaged);
   QHD_SWITCH_N(ny, {
-    constexpr int P_ = pts_per_lane<N_>();
-    QHD_LAUNCH((k_lf_col_2d<N_, P_>), dim3(blocks), dim3(ColCfg<N_, P_>::NT), 0, stream, inst, nact,
-                       ilog2(nx), psi, scratch, s, max_steps);
+    if constexpr (N_ == 64 || N_ == 128) {
+      const int blocks = blocks_for((long long)ninst * (nx / 8), 4, grid_cap);
+      QHD_LAUNCH((k_lf_col_tw<N_>), dim3(blocks), dim3(256), 0, stream, inst, nact, ilog2(nx), psi, scratch, s,
+                 max_steps);
+    } else {
+      constexpr int P_ = pts_per_lane<N_>();
+      const int blocks = pass_blocks_col_2d(nx, ny, ninst, grid_cap, kColStaged);
+      QHD_LAUNCH((k_lf_col_2d<N_, P_>), dim3(blocks), dim3(ColCfg<N_, P_>::NT), 0, stream, inst, nact,
+                 ilog2(nx), psi, scratch, s, max_steps);
+    }
     return hipGetLastError();
   });
 }

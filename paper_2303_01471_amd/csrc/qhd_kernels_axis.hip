@@ -54,14 +54,14 @@ namespace qhd {
 // ------------------------------------------------------------------------------------
 // Row pass: lines along x, one line per TPL lanes.
 
-// 512-point QHD rows with 16 points per lane (R4): one pad slot per 16 line entries (the
+// 512-point QHD rows with 16 points per lane (PAD16): one pad slot per 16 line entries (the
 // radix-16 scatter of the first stage then puts a group of 16 lanes on 16 distinct bank
 // pairs) and a table of first twiddle powers.
 template <int NX, int P, int MODEL>
 struct RowCfg {
-  static constexpr bool R4 = MODEL == kModelQHD && NX == 512 && P == 16;
-  static constexpr int SLOTS = R4 ? NX + NX / 16 : LineLds<NX>::kSlots;
-    static constexpr int WAVES = P == 16 && NX == 512 ? 3 : 1;
+  static constexpr bool PAD16 = MODEL == kModelQHD && NX == 512 && P == 16;
+  static constexpr int SLOTS = PAD16 ? NX + NX / 16 : LineLds<NX>::kSlots;
+  static constexpr int WAVES = P == 16 && NX == 512 ? 3 : 1;
   static constexpr int TPL = NX / P;
   static constexpr int NT = 256;
   static constexpr int LPW = NT / TPL;  // lines per block
@@ -86,8 +86,8 @@ k_row_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
   extern __shared__ double2 etab[];  // tables of the block's instances, sized at launch
   const int ll = threadIdx.x / TPL, t = threadIdx.x % TPL;
   float2* my = lds + (MODEL == kModelQAA ? 0 : ll * SLOTS);
-  using TW = typename std::conditional<RC::R4, TwiddlesLds<NX, P, true>, LineTwiddles<NX, P>>::type;
-  __shared__ double2 twl[MODEL == kModelQAA ? 1 : (RC::R4 ? TwiddlesLds<NX, P, true>::kEntries : LineTwSize<NX, P>::value)];
+  using TW = typename std::conditional<RC::PAD16, TwiddlesLds<NX, P, true>, LineTwiddles<NX, P>>::type;
+  __shared__ double2 twl[MODEL == kModelQAA ? 1 : (RC::PAD16 ? TwiddlesLds<NX, P, true>::kEntries : LineTwSize<NX, P>::value)];
   TW tw;
   if constexpr (MODEL != kModelQAA) load_twiddles(tw, twtab, twl, t);
   // instances of the block's lines: one, or LPW / ny whole ones
@@ -147,7 +147,7 @@ k_row_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
 #pragma unroll
       for (int q = 0; q < P; ++q) assign(reg[q], x[q]);
     } else {
-      using IX = typename std::conditional<RC::R4, Slot16Ix, SlotIx>::type;
+      using IX = typename std::conditional<RC::PAD16, Slot16Ix, SlotIx>::type;
       line_pass<NX, P, false, IX>(reg, t, tw, my, tab, k.prev, k.cpot, fix, fget);
     }
     if (valid && k.active) {
@@ -716,9 +716,10 @@ hipError_t col_pass_qhd(int nx, int ny, int blocks, int v, const PassArgs& a) {
 
 template <bool GEN>
 hipError_t col_pass_qaa(int nx, int ny, int blocks, const PassArgs& a) {
-  if (ny == 64) return go_col_tw<64, kModelQAA, GEN>(blocks, nx, a);
-  if (ny == 128) return go_col_tw<128, kModelQAA, GEN>(blocks, nx, a);
-  QHD_SWITCH_N(ny, { return (go_col_staged<N_, pts_per_lane<N_>(), kModelQAA, GEN>)(blocks, nx, a); });
+  QHD_SWITCH_N(ny, {
+    if constexpr (N_ == 64 || N_ == 128) return (go_col_tw<N_, kModelQAA, GEN>)(blocks, nx, a);
+    else return (go_col_staged<N_, pts_per_lane<N_>(), kModelQAA, GEN>)(blocks, nx, a);
+  });
 }
 
 }  // namespace
