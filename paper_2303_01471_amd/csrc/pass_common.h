@@ -102,7 +102,6 @@ __device__ __forceinline__ double merged_turns(const InstDev& I, long long j, bo
   return beta * kInv2Pi;
 }
 
-
 // Potential phase of the pass that applies V in step j, in turns per unit f.
 // Symmetric scheme: the leading half step of j merged with the trailing half step of
 // j-1 (only the leading half on the entry step, where nothing is pending).
@@ -162,7 +161,6 @@ __device__ __forceinline__ long long step_limit(const InstDev& I, long long max_
 __device__ __forceinline__ bool lf_joins_next(const InstDev& I, int s, long long max_steps) {
   return s % 3 == 2 && s + 1 < step_limit(I, max_steps);  // (a call starts on a whole step)
 }
-
 
 // offset of slot q of lane t on tiled row y (x = t + q*TPL); compile-time stride
 // between slots once a slot spans whole tiles

@@ -10,8 +10,8 @@ namespace qhd {
 
 // What an instance's stored state still owes.  Clean: nothing.  Pending: the trailing
 // potential half step of the last step (and, for the matrix-core classes, F_x^{-1}).
-// OweX / OweY: the kinetic factor of the last stage along x (along y; in 3-D along y and
-// z) and then that half step.  KDone: only that half step, in a class of alternating passes.
+// OweX / OweY, in the 2-D classes of alternating passes: the kinetic factor of the last stage
+// along x (along y) and then that half step.  KDone: only that half step, in such a class.
 enum : int { kModeClean = 0, kModePending = 1, kModeOweX = 2, kModeOweY = 3, kModeKDone = 4 };
 enum : int { kSchemeStrang = 0, kSchemeLie = 1, kSchemeYoshida4 = 2, kSchemeLeapfrog = 3 };
 enum : int { kModelQHD = 0, kModelQAA = 1 };

@@ -22,7 +22,9 @@
 // bytes per grid point); taking both axes of one step in turn, each in a pass of its own,
 // moved 40 and took two launches for the same four line transforms.  The state between
 // passes is in position space and owes the line operator of its last stage along the axis
-// that the last pass did not take (InstDev::mode), and its trailing half step.
+// that the last pass did not take (InstDev::mode), and its trailing half step.  A new state
+// starts on x; the axis that each member takes next is part of its record (InstDev::axis), and
+// where members of a class differ a sub-step launches both axes in the general form of the passes.
 //
 // Lie (V_j, then K_j) and the stages of the fourth-order composition take the same form.
 // QAA (App. C.2): the transverse field is diagonal after a Walsh-Hadamard transform of each

@@ -320,7 +320,9 @@ qhd_status build_dft(qhd_sno_s* m) {
 }
 
 // training at width 32 with 16 modes in BF16: a layer's inverse x-contraction and 1x1 map are one
-// pass, in either direction (any other width or mode count takes the general products)
+// pass, in either direction.  Its inner extents, the width and twice the modes, are both 32, two
+// matrix instructions each; any other width or mode count takes the general products (a step of
+// 32 samples of 128^2 without the gradient's copy: 0.95 ms, with 8 modes 1.66, with 32 2.04)
 bool train32(const qhd_sno_s* m) { return m->train && m->bf16 && m->C == 32 && m->M == 16 && m->S % 32 == 0; }
 
 qhd_status forward(qhd_sno_s* m, const double* f, int B, hipStream_t st) {

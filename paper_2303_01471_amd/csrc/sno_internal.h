@@ -52,7 +52,6 @@ hipError_t sno_prep_lift32(const double* f, int batch, int S, const void* Wl, co
 hipError_t sno_spectral_pointwise32(const void* gx, const void* U, const void* h, const void* W, const float* bias,
                                     int S, long long nrows, void* out, int act, const void* fx, void* T,
                                     const float* wp, const float* bp, float* q, hipStream_t st);
-// per sample, softmax of npix logits in place (as sno_project_softmax forms it)
 // partial gradients of a 1x1 map at width 32, BF16: out[part] (32 x b) = sum over the part's
 // `rows` (a multiple of 64) rows of dz^T x, b <= 32
 hipError_t sno_splitk32(const void* dz, const void* x, int b, int rows, int parts, float* out, hipStream_t st);
@@ -60,6 +59,7 @@ hipError_t sno_splitk32(const void* dz, const void* x, int b, int rows, int part
 // + h W^T + bias and out = GELU(z), or, without out, z = gx U_row + h W (S a power of two >= 32)
 hipError_t sno_train_map32(const void* gx, const void* U, const void* h, const void* W, const float* bias, int S,
                            long long nrows, float* z, void* out, hipStream_t st);
+// per sample, softmax of npix logits in place (as sno_project_softmax forms it)
 hipError_t sno_softmax_rows(float* rho, int batch, int npix, hipStream_t st);
 // width 32, 16 modes, BF16: per row of S pixels (nrows = batch x S), T_row (32 x 32) = fx (32 x S) X_row;
 // S % 16 == 0
