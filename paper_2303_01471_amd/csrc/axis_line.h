@@ -125,12 +125,12 @@ __device__ __forceinline__ void line_kinetic(TIN (&in)[P], TOUT (&out)[P], int t
 }
 
 // A line's whole pass: the owed operator, the potential factor (fget(q): f of slot q) and
-// this step's operator; fix: the owed operator alone.  (fix is set only in general launches, but
-// tested in all: the branch keeps the loads of f behind the owed operator.  Without it 128-point
+// this step's operator; kPassFixUp: the owed operator alone.  (It is set only in general launches,
+// but tested in all: the branch keeps the loads of f behind the owed operator.  Without it 128-point
 // rows take 174 registers instead of 148, and 1024 x 128^2 ran 9 % longer.)
 template <int N, int P, bool BLOCK_SYNC, typename IX, typename TW, typename F>
 __device__ __forceinline__ void line_pass(float2 (&reg)[P], int t, const TW& tw, float2* __restrict__ lds,
-                                          const double2* __restrict__ tab, bool prev, double cpot, int fix, F&& fget) {
+                                          const double2* __restrict__ tab, bool prev, double cpot, int kind, F&& fget) {
   constexpr int H = etab_len<N, kModelQHD>();
   typename LinePrec<N>::V x[P];
   if (prev) {
@@ -139,7 +139,7 @@ __device__ __forceinline__ void line_pass(float2 (&reg)[P], int t, const TW& tw,
 #pragma unroll
     for (int q = 0; q < P; ++q) assign(x[q], reg[q]);
   }
-  if (!fix) {
+  if (kind != kPassFixUp) {
 #pragma unroll
     for (int q = 0; q < P; ++q) x[q] = cmul_fd(x[q], phase_turns_d(cpot * fget(q)));
     line_kinetic<N, P, BLOCK_SYNC, IX>(x, x, t, tw, lds, tab + H);
@@ -155,26 +155,27 @@ __device__ __forceinline__ void line_field(double2 (&reg)[P], int t, const doubl
   line_wht<N, P, double2, LS>(reg, t);
 }
 
-// What a line does in sub-step s in a launch of axis `axis`.  GEN, the general form of a pass:
-// members on either axis (those whose turn it is take their whole pass, the others theirs in a
-// launch of the other axis), fix-up launches (fix: only the owed operator, of the members that
-// owe it) and the stages of the fourth-order scheme.  Without GEN every member takes the launch's
+// What a line does in sub-step s in a launch of axis `axis`.  GEN, the general form of a pass: the
+// stages of the fourth-order scheme, mixed launches (members on either axis: those whose turn it
+// is take their whole pass, the others theirs in a launch of the other axis) and fix-up launches
+// (only the owed operator, of the members that owe it).  In a plain launch every member takes its
 // axis: the test of the member's own one cost 0.5 to 1 % (one 64^2 instance, 128^2 x 1024).
 struct LineTask {
   bool active, prev, entry;
   double cpot;  // turns per unit f of the merged potential factor
 };
 template <bool GEN>
-__device__ __forceinline__ bool line_active(const InstDev& I, long long s, long long max_steps, int axis, int fix) {
-  if (GEN && fix) return pays_owed(I, axis == 0 ? kModeOweX : kModeOweY);
-  return (!GEN || ((I.axis + s) & 1) == axis) && s < step_limit(I, max_steps);
+__device__ __forceinline__ bool line_active(const InstDev& I, long long s, long long max_steps, int axis, int kind) {
+  if (GEN && kind == kPassFixUp) return pays_owed(I, axis == 0 ? kModeOweX : kModeOweY);
+  if (GEN && kind == kPassMixed && ((I.axis + s) & 1) != axis) return false;
+  return s < step_limit(I, max_steps);
 }
 template <bool GEN>
-__device__ __forceinline__ LineTask line_task(const InstDev& I, long long s, long long max_steps, int axis, int fix) {
+__device__ __forceinline__ LineTask line_task(const InstDev& I, long long s, long long max_steps, int axis, int kind) {
   LineTask k;
   k.prev = s > 0 || I.mode == (axis == 0 ? kModeOweX : kModeOweY);
   k.entry = s == 0 && I.mode == kModeClean;
-  k.active = line_active<GEN>(I, s, max_steps, axis, fix);
+  k.active = line_active<GEN>(I, s, max_steps, axis, kind);
   k.cpot = potential_turns<GEN>(I, I.steps_done + s, k.entry);
   return k;
 }

@@ -419,12 +419,12 @@ qhd_status enqueue_chunk(qhd_plan p, long long ks, hipStream_t stream, bool timi
           if (axes & row)
             HIP_TRY(timed_on(st, c.fam_row, points(0), [&] {
               return launch_row_pass_2d(c.nx, c.ny, c.dev, m, na, c.psi, c.f, c.tw_x, s, ks, c.cap_row, c.row_points,
-                                        st, c.model, c.y4 || axes == 3);
+                                        st, c.model, c.y4, axes == 3 ? kPassMixed : kPassPlain);
             }));
           if (axes & col)
             HIP_TRY(timed_on(st, c.fam_col, points(1), [&] {
               return launch_col_pass_2d(c.nx, c.ny, c.dev, m, na, c.psi, c.f, c.tw_y, s, ks, c.cap_col, c.col_variant,
-                                        st, c.model, c.y4 || axes == 3);
+                                        st, c.model, c.y4, axes == 3 ? kPassMixed : kPassPlain);
             }));
         }
       }
@@ -453,10 +453,10 @@ qhd_status settle_axes(qhd_plan p, hipStream_t st) {
     HIP_TRY(launch_count_owing(c.dev, m, owe, owing, st));
     if (start == 0)
       HIP_TRY(launch_col_pass_2d(c.nx, c.ny, c.dev, m, owing, c.psi, c.f, c.tw_y, 0, 1, c.cap_col, c.col_variant, st,
-                                 c.model, true, true));
+                                 c.model, c.y4, kPassFixUp));
     else
       HIP_TRY(launch_row_pass_2d(c.nx, c.ny, c.dev, m, owing, c.psi, c.f, c.tw_x, 0, 1, c.cap_row, c.row_points, st,
-                                 c.model, true, true));
+                                 c.model, c.y4, kPassFixUp));
     HIP_TRY(launch_set_axis(c.dev, m, start, st));
     for (auto& I : c.host)
       if (I.steps_done < I.nsteps) {

@@ -14,6 +14,9 @@ namespace qhd {
 // along x (along y) and then that half step.  KDone: only that half step, in such a class.
 enum : int { kModeClean = 0, kModePending = 1, kModeOweX = 2, kModeOweY = 3, kModeKDone = 4 };
 enum : int { kSchemeStrang = 0, kSchemeLie = 1, kSchemeYoshida4 = 2, kSchemeLeapfrog = 3 };
+// What a launch of an alternating pass does along its axis: the sub-step of every member, only
+// what members that go on owe, or the sub-step of the members whose turn it is.
+enum : int { kPassPlain = 0, kPassFixUp = 1, kPassMixed = 2 };
 enum : int { kModelQHD = 0, kModelQAA = 1 };
 enum : int { kSchedNesterov = 0, kSchedConst = 1, kSchedTable = 2, kSchedLinear = 3 };
 
@@ -80,7 +83,7 @@ struct TimingSink {
 hipError_t launch_row_pass_2d(int nx, int ny, const InstDev* inst, int ninst, const int* nact, float2* psi,
                               const double* f, const double2* tw_nx, int s, long long max_steps,
                               int grid_cap, int points_per_lane, hipStream_t stream, int model = kModelQHD,
-                              bool general = true, bool fix = false);
+                              bool y4 = true, int kind = kPassPlain);
 // Sampled pass timing.  When armed, the next pass launch of this host thread records
 // the two events itself: hipExtLaunchKernelGGL stamps them with the dispatch's own start
 // and end (what a kernel trace reports), where events recorded around a launch would
@@ -119,14 +122,12 @@ hipError_t launch_lf_col_2d(int nx, int ny, const InstDev* inst, int ninst, cons
                             long long max_steps, int grid_cap, hipStream_t stream);
 hipError_t launch_col_pass_2d(int nx, int ny, const InstDev* inst, int ninst, const int* nact, float2* psi,
                               const double* f, const double2* tw_ny, int s, long long max_steps, int grid_cap,
-                              int variant, hipStream_t stream, int model = kModelQHD, bool general = true,
-                              bool fix = false);
-// (general: members of the fourth-order scheme, or on either axis; fix: only what members that
-// go on owe along the axis)
-// *owing = 1 + the last member that a `fix` launch would pay in mode `owe` (0: none)
+                              int variant, hipStream_t stream, int model = kModelQHD, bool y4 = true,
+                              int kind = kPassPlain);
+// *owing = 1 + the last member that a fix-up launch would pay in mode `owe` (0: none)
 hipError_t launch_count_owing(const InstDev* inst, int ninst, int owe, int* owing, hipStream_t stream);
-// the members that go on take `axis` next; after a `fix` launch along the other one: those it
-// paid become kModeKDone
+// the members that go on take `axis` next; after a fix-up launch along the other one: those
+// it paid become kModeKDone
 hipError_t launch_set_axis(InstDev* inst, int ninst, int axis, hipStream_t stream);
 // 1-D: every sub-step of the chunk in one launch
 hipError_t launch_line_steps_1d(int n, const InstDev* inst, int ninst, const int* nact, float2* psi, const double* f,

@@ -80,7 +80,7 @@ template <int NX, int P, int MODEL = kModelQHD, bool GEN = true>
 __global__ void __launch_bounds__((RowCfg<NX, P, MODEL>::NT)) __attribute__((amdgpu_waves_per_eu(RowCfg<NX, P, MODEL>::WAVES)))
 k_row_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, int ny_log2,
               float2* __restrict__ psi, const double* __restrict__ f, const double2* __restrict__ twtab, int s,
-              long long max_steps, int fix) {
+              long long max_steps, int kind) {
   const int ninst = *nact_p;  // members active in this sub-step (device, set per chunk)
   using RC = RowCfg<NX, P, MODEL>;
   constexpr int TPL = RC::TPL, LPW = RC::LPW, SLOTS = RC::SLOTS, H = etab_len<NX, MODEL>();
@@ -134,14 +134,14 @@ k_row_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
       __syncthreads();
       cached = i0;
     }
-    const LineTask k = line_task<GEN>(I, s, max_steps, 0, fix);
+    const LineTask k = line_task<GEN>(I, s, max_steps, 0, kind);
     const double2* tab = etab + (i - i0) * 2 * H;
     if constexpr (MODEL == kModelQAA) {
       double2 x[P];
 #pragma unroll
       for (int q = 0; q < P; ++q) assign(x[q], reg[q]);
       if (k.prev) line_field<NX, P>(x, t, tab);
-      if (!fix) {
+      if (kind != kPassFixUp) {
 #pragma unroll
         for (int q = 0; q < P; ++q) x[q] = cmul_fd(x[q], phase_turns_d(k.cpot * fget(q)));
         line_field<NX, P>(x, t, tab + H);
@@ -150,7 +150,7 @@ k_row_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
       for (int q = 0; q < P; ++q) assign(reg[q], x[q]);
     } else {
       using IX = typename std::conditional<RC::PAD16, Slot16Ix, SlotIx>::type;
-      line_pass<NX, P, false, IX>(reg, t, tw, my, tab, k.prev, k.cpot, fix, fget);
+      line_pass<NX, P, false, IX>(reg, t, tw, my, tab, k.prev, k.cpot, kind, fget);
     }
     if (valid && k.active) {
 #pragma unroll
@@ -172,7 +172,7 @@ template <int NY, int P, int MODEL = kModelQHD, bool GEN = true>
 __global__ void __launch_bounds__((ColCfg<NY, P>::NT)) __attribute__((amdgpu_waves_per_eu(ColCfg<NY, P>::MIN_WAVES)))
 k_col_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, int nx_log2,
               float2* __restrict__ psi, const double* __restrict__ f, const double2* __restrict__ twtab, int s,
-              long long max_steps, int fix) {
+              long long max_steps, int kind) {
   const int ninst = *nact_p;  // members active in this sub-step (device, set per chunk)
   using C = ColCfg<NY, P>;
   constexpr int TPL = C::TPL, ITEMS = C::ITEMS, NT = C::NT, STRIDE = C::STRIDE, SUBS = C::SUBS;
@@ -189,7 +189,7 @@ k_col_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
   long long begin, end;
   block_share(total, ITEMS, begin, end);
   int cached = -1, cached_n = 0;
-  auto live = [&](const InstDev& I) { return line_active<GEN>(I, s, max_steps, 1, fix); };
+  auto live = [&](const InstDev& I) { return line_active<GEN>(I, s, max_steps, 1, kind); };
   for (long long g0 = begin; g0 < end; g0 += ITEMS) {
     const long long glast = g0 + ITEMS <= end ? g0 + ITEMS - 1 : end - 1;
     const int i0 = (int)(g0 >> tc_log2), count = (int)(glast >> tc_log2) - i0 + 1;
@@ -233,7 +233,7 @@ k_col_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
       const int i = (int)(gc >> tc_log2), tc = (int)(gc & (tcols - 1));
       const InstDev& I = inst[i];
       const int x = tc * 8 + (line & 7);
-      const LineTask k = line_task<GEN>(I, s, max_steps, 1, fix);
+      const LineTask k = line_task<GEN>(I, s, max_steps, 1, kind);
       const double2* tab = etab + (i - i0) * 2 * H;
       const double* __restrict__ fl = f + I.psi_off;
       float2 reg[P];
@@ -245,7 +245,7 @@ k_col_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
 #pragma unroll
         for (int q = 0; q < P; ++q) assign(kd[q], reg[q]);
         if (k.prev) line_field<NY, P>(kd, t, tab);
-        if (!fix) {
+        if (kind != kPassFixUp) {
 #pragma unroll
           for (int q = 0; q < P; ++q) kd[q] = cmul_fd(kd[q], phase_turns_d(k.cpot * fl[tile_index(x, t + q * TPL, nx)]));
           line_field<NY, P>(kd, t, tab + H);
@@ -253,7 +253,7 @@ k_col_axis_2d(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
 #pragma unroll
         for (int q = 0; q < P; ++q) assign(reg[q], kd[q]);
       } else {
-        line_pass<NY, P, false, SlotIx>(reg, t, tw, my, tab, k.prev, k.cpot, fix,
+        line_pass<NY, P, false, SlotIx>(reg, t, tw, my, tab, k.prev, k.cpot, kind,
                                         [&](int q) { return fl[tile_index(x, t + q * TPL, nx)]; });
       }
 #pragma unroll
@@ -306,7 +306,7 @@ template <int NY, bool GEN>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(6)))
 k_col_axis_split(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, int nx_log2,
                  float2* __restrict__ psi, const double* __restrict__ f, const double2* __restrict__ twtab, int s,
-                 long long max_steps, int fix) {
+                 long long max_steps, int kind) {
   const int ninst = *nact_p;  // members active in this sub-step (device, set per chunk)
   using C = ColSplitCfg<NY>;
   constexpr int P = C::P, TPL = C::TPL, STRIDE = C::STRIDE, H = NY / 2 + 1;
@@ -355,7 +355,7 @@ k_col_axis_split(const InstDev* __restrict__ inst, const int* __restrict__ nact_
   for (long long g0 = begin; g0 < end; ++g0) {
     const int i = (int)(g0 >> tc_log2), tc = (int)(g0 & (tcols - 1));
     const InstDev& I = inst[i];
-    const LineTask k = line_task<GEN>(I, s, max_steps, 1, fix);
+    const LineTask k = line_task<GEN>(I, s, max_steps, 1, kind);
     if (!k.active) continue;  // block-uniform
     const LaneView<float2> pv(psi + I.psi_off + tc * 64, lane);
     const LaneView<double> fv(f + I.psi_off + tc * 64, lane);
@@ -375,7 +375,7 @@ k_col_axis_split(const InstDev* __restrict__ inst, const int* __restrict__ nact_
 #pragma unroll
       for (int q = 0; q < P; ++q) assign(v[q], x[q]);
     }
-    if (!fix) {
+    if (kind != kPassFixUp) {
 #pragma unroll
       for (int q = 0; q < P; ++q)
         v[q] = cmul_fd(v[q], phase_turns_d(k.cpot * fv.load((wave + 8 * q) * tcols * 64)));
@@ -414,7 +414,7 @@ template <int NY, int P, int MODEL, bool GEN>
 __global__ void __launch_bounds__((ColTwCfg<NY, P>::NT)) __attribute__((amdgpu_waves_per_eu(ColTwCfg<NY, P>::MIN_WAVES)))
 k_col_axis_tw(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, int nx_log2,
               float2* __restrict__ psi, const double* __restrict__ f, const double2* __restrict__ twtab, int s,
-              long long max_steps, int fix) {
+              long long max_steps, int kind) {
   const int ninst = *nact_p;  // members active in this sub-step (device, set per chunk)
   using C = ColTwCfg<NY, P>;
   constexpr int W = C::W, ITEMS = C::ITEMS, STRIDE = C::STRIDE, H = etab_len<NY, MODEL>();
@@ -459,7 +459,7 @@ k_col_axis_tw(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
       cached = i0;
       cached_n = count;
     }
-    const LineTask k = line_task<GEN>(I, s, max_steps, 1, fix);
+    const LineTask k = line_task<GEN>(I, s, max_steps, 1, kind);
     const bool active = valid && k.active;
     const double2* tab = etab + (i - i0) * 2 * H;
     if constexpr (MODEL == kModelQAA) {
@@ -467,7 +467,7 @@ k_col_axis_tw(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
 #pragma unroll
       for (int q = 0; q < P; ++q) assign(reg[q], in[q]);
       if (k.prev) line_field<NY, P, 8>(reg, t, tab);
-      if (!fix) {
+      if (kind != kPassFixUp) {
 #pragma unroll
         for (int q = 0; q < P; ++q) reg[q] = cmul_fd(reg[q], phase_turns_d(k.cpot * fv.load(q * W * tcols * 64)));
         line_field<NY, P, 8>(reg, t, tab + H);
@@ -481,7 +481,7 @@ k_col_axis_tw(const InstDev* __restrict__ inst, const int* __restrict__ nact_p, 
         }
       }
     } else {
-      line_pass<NY, P, (W > 1), SlotIx>(in, t, tw, my, tab, k.prev, k.cpot, fix,
+      line_pass<NY, P, (W > 1), SlotIx>(in, t, tw, my, tab, k.prev, k.cpot, kind,
                                         [&](int q) { return fv.load(q * W * tcols * 64); });
       if (active) {
 #pragma unroll
@@ -661,7 +661,7 @@ struct PassArgs {
   const double2* tw;
   int s;
   long long max_steps;
-  int fix;
+  int kind;
   hipStream_t stream;
 };
 
@@ -671,7 +671,7 @@ hipError_t go_row(int blocks, int ny, const PassArgs& a) {
   const int per_block = lpw > ny ? lpw / ny : 1;
   const size_t dyn = (size_t)per_block * 2 * etab_len<N, MODEL>() * sizeof(double2);
   QHD_LAUNCH((k_row_axis_2d<N, P, MODEL, GEN>), dim3(blocks), dim3(RowCfg<N, P, MODEL>::NT), dyn, a.stream, a.inst, a.nact, ilog2(ny), a.psi,
-             a.f, a.tw, a.s, a.max_steps, a.fix);
+             a.f, a.tw, a.s, a.max_steps, a.kind);
   return hipGetLastError();
 }
 
@@ -686,7 +686,7 @@ hipError_t row_pass_qhd(int nx, int ny, int blocks, int points, const PassArgs& 
 template <int N, int P, int MODEL, bool GEN>
 hipError_t go_col_staged(int blocks, int nx, const PassArgs& a) {
   QHD_LAUNCH((k_col_axis_2d<N, P, MODEL, GEN>), dim3(blocks), dim3(ColCfg<N, P>::NT), 0, a.stream, a.inst, a.nact,
-             ilog2(nx), a.psi, a.f, a.tw, a.s, a.max_steps, a.fix);
+             ilog2(nx), a.psi, a.f, a.tw, a.s, a.max_steps, a.kind);
   return hipGetLastError();
 }
 
@@ -695,7 +695,7 @@ hipError_t go_col_tw(int blocks, int nx, const PassArgs& a) {
   if constexpr (N >= 64 && (MODEL == kModelQHD || N <= 128)) {
     constexpr int P_ = col_tw_p<N>();
     QHD_LAUNCH((k_col_axis_tw<N, P_, MODEL, GEN>), dim3(blocks), dim3(ColTwCfg<N, P_>::NT), 0, a.stream, a.inst, a.nact,
-               ilog2(nx), a.psi, a.f, a.tw, a.s, a.max_steps, a.fix);
+               ilog2(nx), a.psi, a.f, a.tw, a.s, a.max_steps, a.kind);
     return hipGetLastError();
   } else {
     return hipErrorInvalidValue;
@@ -707,7 +707,7 @@ hipError_t col_pass_qhd(int nx, int ny, int blocks, int v, const PassArgs& a) {
   if (v == kColTileWave) QHD_SWITCH_N(ny, { return (go_col_tw<N_, kModelQHD, GEN>)(blocks, nx, a); });
   if (v == kColSplit) {
     QHD_LAUNCH((k_col_axis_split<512, GEN>), dim3(blocks), dim3(ColSplitCfg<512>::NT), 0, a.stream, a.inst, a.nact,
-               ilog2(nx), a.psi, a.f, a.tw, a.s, a.max_steps, a.fix);
+               ilog2(nx), a.psi, a.f, a.tw, a.s, a.max_steps, a.kind);
     return hipGetLastError();
   }
   if (v == kColStaged16)
@@ -728,9 +728,9 @@ hipError_t col_pass_qaa(int nx, int ny, int blocks, const PassArgs& a) {
 
 hipError_t launch_row_pass_2d(int nx, int ny, const InstDev* inst, int ninst, const int* nact, float2* psi,
                               const double* f, const double2* tw, int s, long long max_steps, int grid_cap,
-                              int points_per_lane, hipStream_t stream, int model, bool general, bool fix) {
-  const PassArgs a{inst, nact, psi, f, tw, s, max_steps, fix ? 1 : 0, stream};
-  general = general || fix;
+                              int points_per_lane, hipStream_t stream, int model, bool y4, int kind) {
+  const PassArgs a{inst, nact, psi, f, tw, s, max_steps, kind, stream};
+  const bool general = y4 || kind != kPassPlain;
   if (model == kModelQAA) {  // the QAA model runs the symmetric scheme or leapfrog
     const int blocks = pass_blocks_row_2d(nx, ny, ninst, grid_cap, 8);
     if (general) QHD_SWITCH_N(nx, { return (go_row<N_, pts_per_lane<N_>(), kModelQAA, true>)(blocks, ny, a); });
@@ -743,9 +743,9 @@ hipError_t launch_row_pass_2d(int nx, int ny, const InstDev* inst, int ninst, co
 
 hipError_t launch_col_pass_2d(int nx, int ny, const InstDev* inst, int ninst, const int* nact, float2* psi,
                               const double* f, const double2* tw, int s, long long max_steps, int grid_cap,
-                              int variant, hipStream_t stream, int model, bool general, bool fix) {
-  const PassArgs a{inst, nact, psi, f, tw, s, max_steps, fix ? 1 : 0, stream};
-  general = general || fix;
+                              int variant, hipStream_t stream, int model, bool y4, int kind) {
+  const PassArgs a{inst, nact, psi, f, tw, s, max_steps, kind, stream};
+  const bool general = y4 || kind != kPassPlain;
   if (model == kModelQAA) {
     // 64- and 128-point Walsh-Hadamard columns lie in one wavefront of the tile-wave form;
     // the others are staged (in-wave shuffles along a line)
