@@ -1007,8 +1007,9 @@ qhd_status qhd_plan_create(const qhd_instance* inst, int32_t batch, const qhd_pl
           // measured defaults (uniform batches of 256 instances per size on MI355X): a block
           // fills its kinetic tables once per instance that it meets, against the balance of
           // many short blocks.  us per step, both axes' caps 1024 / 4096 / 6144 / 16384:
-          // 263 x 512^2 532 / 514 / 505 / 519, 243 x 256^2 107 / 104 / 102 / 105, 262 x 128^2
-          // 36 / 33 / 33 / 33, 1024 x 64^2 26 / 28 / 29 / 28; 4 x 1024^2 at 512 / 1024 / 6144: 44 / 47 / 48
+          // 263 x 512^2 490 / 473 / 467 / 470, 243 x 256^2 102 / 97 / 97 / 98, 262 x 128^2
+          // 38 / 33 / 33 / 33, 1024 x 64^2 23.6 / 24.0 / 24.4 / 24.1; 4 x 1024^2 at 512 / 1024 / 6144: 44.5 /
+          // 45.0 / 45.1
           auto cap = [](int n) { return n >= 1024 ? 512 : (n >= 256 ? 6144 : (n >= 128 ? 4096 : 1024)); };
           c.cap_row = cap(c.nx);
           c.cap_col = cap(c.ny);

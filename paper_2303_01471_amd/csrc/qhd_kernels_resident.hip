@@ -26,8 +26,8 @@
 namespace qhd {
 
 // MANY (128 x 32 and 32 x 128, more members than CUs): 256 threads, so that two instances fit a
-// CU beside each other (us per step, 512 and 256 threads: 2000 x 128 x 32 58 and 47, 2000 x 32 x
-// 128 45 and 38; one instance 7.4 and 8.4, 5.6 and 6.3)
+// CU beside each other (us per step, 512 and 256 threads: 2000 x 128 x 32 53 and 42, 2000 x 32 x
+// 128 47 and 38; one instance 6.6 and 7.6, 5.9 and 6.4)
 template <int NX, int NY, int MODEL, bool MANY>
 struct ResCfg {
   // 128-point lines take 16 points per lane (radices 8 and 16: one exchange per transform)
@@ -35,7 +35,7 @@ struct ResCfg {
   static constexpr int TX = NX / PX, TY = NY / PY;             // lanes per row / column line
   static constexpr int LANES = NX * NY / PX > NX * NY / PY ? NX * NY / PX : NX * NY / PY;
   // 16 points need more than the 128 registers of a 1024-thread block (1024 and 512 threads, us
-  // per step: 1000 x 128 x 64 67 and 47, 1000 x 64 x 128 60 and 42, 512 x 128^2 55 and 50)
+  // per step: 1000 x 128 x 64 64 and 42, 1000 x 64 x 128 62 and 42, 512 x 128^2 57 and 46)
   static constexpr int MAXT = MANY ? 256 : PX == 16 || PY == 16 ? 512 : 1024;
   static constexpr int NT = LANES < MAXT ? LANES : MAXT;
   static constexpr int RS = ((NX + NX / 8) | 1);               // row stride in slots (odd)
